@@ -44,9 +44,11 @@
 namespace kry {
 
 constexpr int NLOAD = 2;       // DMA loader wavefronts per workgroup
-constexpr int GWG = 64 * (2 + NLOAD);   // one wavefront per SIMD
+constexpr int GWG = 64 * 7;    // wavefronts of a sweep workgroup (roles below)
 constexpr int NFACE = 40;      // >= TJ + TK for every tiling used
-constexpr int DB = 16;         // boundary ring depth (steps)
+
+// a cell of zeros: the right-hand side of lanes and steps with no cell
+static __device__ __align__(16) const double zero_cell[4] = {0.0, 0.0, 0.0, 0.0};
 
 // ---------------------------------------------------------------------------
 // setup
@@ -511,9 +513,8 @@ int ilu_grid_factor_setup(hipStream_t s, const MAT_ *A, const double *d_val, Ilu
 // ---------------------------------------------------------------------------
 // sweeps: one workgroup per tile, wavefront-specialised
 //   wave 0            compute: consumes one hyperplane step at a time from
-//                     LDS, exchanges neighbour values across lanes, stores
-//                     the step's results (one contiguous row per component)
-//                     and publishes the face cells; it issues no loads
+//                     LDS and leaves its result in LDS; it touches no global
+//                     memory and waits for nothing but its operands
 //   wave 1            boundary: polls the face buffers of the two upstream
 //                     tiles and stages the values in LDS
 //   waves 2, 3        loaders: copy each step's factor planes (and the
@@ -523,10 +524,32 @@ int ilu_grid_factor_setup(hipStream_t s, const MAT_ *A, const double *d_val, Ilu
 //                     DMA loads, several steps in flight per wavefront and
 //                     no register staging; when a tile is done they re-arm
 //                     the other sweep's face slots of that tile
+//   wave 4            only passes the tile barriers: wavefronts go to the
+//                     four SIMDs in turn, and the compute wavefront keeps
+//                     its SIMD to itself
+//   wave 5            publisher: takes each step's result from LDS and
+//                     publishes the face cells; in the forward sweep it
+//                     also stores the tile-step rows the backward sweep reads
+//   wave 6            backward only, writer: takes the results of a few
+//                     steps at a time from LDS and stores them to the
+//                     caller's vector in natural order, with its epilogue
+//
+// Result ring.  Slot t of YRing holds what step t reads: the tile's results
+// of step t - 1 in the interior of a (TK + 1) x (TJ + 1) array of cells, and
+// in its first row and column the neighbouring tiles' face values for step
+// t, put there by the boundary wavefront.  A lane finds its j- and
+// k-neighbours at fixed places of the slot whether they belong to the tile
+// or not, so the exchange is two LDS writes and four reads a step with no
+// selects, and the same slots feed the publisher and the writer.
+//
+// What bounds a step: the compute wavefront issues about one instruction
+// every four cycles, so the step's length is its instruction count plus the
+// LDS round trip of the neighbours' results.
+//
 // Ring slots carry the step's stamp (a running step count of the
-// workgroup), so no slot is ever reset.  Four wavefronts per workgroup and
-// one workgroup per CU (the ring fills the LDS) give every role a SIMD of
-// its own: a spinning wavefront never takes issue slots from another.
+// workgroup), so no slot is ever reset.  LDS operations of one wavefront
+// execute in order, so a progress word written after the reads (or writes)
+// it stands for needs no wait in between.
 // ---------------------------------------------------------------------------
 // ring slots for steps of SB bytes (120 KiB of ring, 2 to 8 slots)
 template <int SB>
@@ -598,18 +621,30 @@ struct RhsStage {
     static constexpr int LS = W == 12 ? 16 : 4;
     static constexpr int NP = CB / W;            // DMA instructions per step
     static constexpr int BYTES = NP * 64 * LS;
-    static __device__ __forceinline__ uint32_t dword(const char *rb, int lane, int d) {
-        const int off = 4 * d;
-        return *reinterpret_cast<const uint32_t *>(rb + (off / W) * 64 * LS + lane * LS + off % W);
-    }
+    // the lane's BS values
     template <typename TC>
-    static __device__ __forceinline__ TC value(const char *rb, int lane, int r) {
-        if constexpr (sizeof(TIN) == 8) {
-            const uint64_t u = (static_cast<uint64_t>(dword(rb, lane, 2 * r + 1)) << 32) |
-                               dword(rb, lane, 2 * r);
-            return static_cast<TC>(__longlong_as_double(static_cast<long long>(u)));
-        } else {
-            return static_cast<TC>(__uint_as_float(dword(rb, lane, r)));
+    static __device__ __forceinline__ void read(const char *rb, int lane, TC *v) {
+        uint32_t d[CB / 4 + 2];
+#pragma unroll
+        for (int q = 0; q < NP; q++) {
+            const char *p = rb + q * 64 * LS + lane * LS;
+            if constexpr (W == 12) {   // the fourth dword of a piece is never written
+                const uint4 u = *reinterpret_cast<const uint4 *>(p);
+                d[3 * q] = u.x;
+                d[3 * q + 1] = u.y;
+                d[3 * q + 2] = u.z;
+            } else {
+                d[q] = *reinterpret_cast<const uint32_t *>(p);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < BS; r++) {
+            if constexpr (sizeof(TIN) == 8) {
+                const uint64_t u = (static_cast<uint64_t>(d[2 * r + 1]) << 32) | d[2 * r];
+                v[r] = static_cast<TC>(__longlong_as_double(static_cast<long long>(u)));
+            } else {
+                v[r] = static_cast<TC>(__uint_as_float(d[r]));
+            }
         }
     }
     static __device__ __forceinline__ void load(const TIN *cell, char *dst) {
@@ -635,24 +670,120 @@ __device__ __forceinline__ void lds_flag_put(int *p, int v) {
     asm volatile("ds_write_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : : "v"(a), "v"(v) : "memory");
 }
 
+// Progress word of a role: every lane writes the value to its own word, so
+// the store needs no exec mask and meets no bank conflict; readers take
+// word 0.
+struct Progress {
+    int w[64];
+};
+__device__ __forceinline__ void progress_put(Progress &p, int lane, int v) {
+    const unsigned a = (unsigned)(size_t)((__attribute__((address_space(3))) int *)(p.w + lane));
+    asm volatile("ds_write_b32 %0, %1" : : "v"(a), "v"(v) : "memory");
+}
+__device__ __forceinline__ int progress_get(const Progress &p) {
+    return __builtin_amdgcn_readfirstlane(lds_get(const_cast<int *>(p.w)));
+}
+// wait until the progress word reaches v (it is kept by a wavefront of this
+// workgroup that waits only on earlier steps)
+__device__ __forceinline__ void progress_wait(const Progress &p, int v, int &seen, int *err) {
+    for (uint32_t it = 0; seen < v; ++it) {
+        seen = progress_get(p);
+        if (it > 4 * SPIN_LIMIT) {
+            __hip_atomic_store(err, ERR_STALL_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            break;
+        }
+    }
+    asm volatile("" : : : "memory");
+}
+
+// The result ring (see the head of this section): DY slots of CELLS cells.
+// A cell's BS values are one 16-byte piece and, for three doubles, an
+// 8-byte piece in a second plane, so a cell moves in one or two LDS
+// instructions.  CELLS >= (TK + 1)(TJ + 1) for every tiling, idle lanes
+// included (at most 99), and makes the slot strides (408 and 204 words) hit
+// distinct banks when a wavefront reads a few consecutive slots at once.
+template <typename TC, int BS>
+struct YRing {
+    static constexpr int DY = BS == 1 ? 32 : 16;
+    static constexpr int CELLS = 102;
+    static constexpr int WA = BS == 3 ? 16 : (int)sizeof(TC);
+    static constexpr int WB = BS == 3 && sizeof(TC) == 8 ? 8 : 0;
+    static constexpr int BYTES = DY * CELLS * (WA + WB);
+    static __device__ __forceinline__ int slot(int t) { return t & (DY - 1); }
+    static __device__ __forceinline__ void load(const char *ring, int s, int cell, TC (&v)[BS]) {
+        const char *p = ring + s * (CELLS * WA) + cell * WA;
+        if constexpr (BS == 1) {
+            v[0] = *reinterpret_cast<const TC *>(p);
+        } else if constexpr (sizeof(TC) == 8) {
+            const double2 a = *reinterpret_cast<const double2 *>(p);
+            v[0] = a.x;
+            v[1] = a.y;
+            v[2] = *reinterpret_cast<const double *>(ring + DY * CELLS * WA + s * (CELLS * WB) + cell * WB);
+        } else {
+            const float4 a = *reinterpret_cast<const float4 *>(p);
+            v[0] = a.x;
+            v[1] = a.y;
+            v[2] = a.z;
+        }
+    }
+    static __device__ __forceinline__ void store(char *ring, int s, int cell, const TC (&v)[BS]) {
+        char *p = ring + s * (CELLS * WA) + cell * WA;
+        if constexpr (BS == 1) {
+            *reinterpret_cast<TC *>(p) = v[0];
+        } else if constexpr (sizeof(TC) == 8) {
+            *reinterpret_cast<double2 *>(p) = make_double2(v[0], v[1]);
+            *reinterpret_cast<double *>(ring + DY * CELLS * WA + s * (CELLS * WB) + cell * WB) = v[2];
+        } else {
+            *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], 0.0f);
+        }
+    }
+};
+
+// Stamps of a step slot: .x = boundary staged for step t (slot t), .y =
+// planes loaded for step t + 1 (slot t), one 8-byte word so the compute
+// wavefront checks both with one read and one compare.
+union StepFlag {
+    int h[2];
+    unsigned long long u;
+};
+__device__ __forceinline__ unsigned long long step_flag_get(const StepFlag &f) {
+    return __hip_atomic_load(const_cast<unsigned long long *>(&f.u), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// wait for both stamps; pre = the flag read ahead during the previous step
+__device__ __forceinline__ void step_wait(unsigned long long pre, const StepFlag &f, int st, int *err) {
+    const unsigned long long want =
+        (static_cast<unsigned long long>(static_cast<unsigned>(st + 1)) << 32) | static_cast<unsigned>(st);
+    if (__builtin_amdgcn_ballot_w64(pre != want) != 0)
+        for (uint32_t it = 0; __builtin_amdgcn_ballot_w64(step_flag_get(f) != want) != 0; ++it)
+            if (it > 4 * SPIN_LIMIT) {
+                __hip_atomic_store(err, ERR_STALL_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+    asm volatile("" : : : "memory");
+}
+
 // Loader loop of one tile: steps t = w, w + NLOAD, ... of S; issue(t) starts
 // the DMA of step t into ring slot t % D (P instructions); at most K steps of
-// this wavefront in flight; a step is stamped in full[] once its DMA landed.
-// Slot t % D is free once the compute wavefront has consumed step t - D.
+// this wavefront in flight; a step is stamped once its DMA landed.  Slot
+// t % D is free once the compute wavefront has finished step t - D (its
+// planes are read during the step before, those of step 0 before step 0).
 // The wait counts assume no other vector memory operation of the wavefront
 // is outstanding when the loop starts.
-template <int D, int P, int K, typename F>
-__device__ __forceinline__ void loader_loop(int w, int S, int base, int *cons, int *full, int lane,
-                                            int *err, F &&issue) {
+template <int D, int P, int K, int DY, typename F>
+__device__ __forceinline__ void loader_loop(int w, int S, int base, const Progress &done_p,
+                                            StepFlag (&fl)[DY], int lane, int *err, F &&issue) {
     // the wave's vector memory counter holds at most 63 outstanding
     // instructions: every DMA of the K steps in flight must fit in it
     static_assert(K >= 1 && K <= 4 && K * P <= 63, "in-flight DMA within the vmcnt range");
+    static_assert(D < DY, "the stamps of the steps in the ring are distinct slots");
     int next = w, done = w;
     uint32_t idle = 0;
     wait_vm<0>();
     while (done < S) {
         while (next < S && next - done < K * NLOAD &&
-               __builtin_amdgcn_readfirstlane(lds_flag_get(cons)) >= base + next - D + 1) {
+               (next < D || __builtin_amdgcn_readfirstlane(lds_flag_get(done_p.w)) >=
+                                base + (next - D > 1 ? next - D : 1))) {
             issue(next);
             next += NLOAD;
         }
@@ -672,9 +803,12 @@ __device__ __forceinline__ void loader_loop(int w, int S, int base, int *cons, i
         if constexpr (K >= 3) { if (inflight == 3) wait_vm<(K >= 3 ? 2 * P : 0)>(); }
         if constexpr (K >= 2) { if (inflight == 2) wait_vm<(K >= 2 ? P : 0)>(); }
         if (inflight == 1) wait_vm<0>();
-        if (lane == 0) lds_flag_put(&full[done % D], base + done);
+        if (lane == 0) lds_flag_put(&fl[(done + DY - 1) & (DY - 1)].h[1], base + done);
         done += NLOAD;
     }
+    // the last step has no next planes to wait for: stamp them all the same
+    // (step S belongs to wavefront S % NLOAD)
+    if (S % NLOAD == w && lane == 0) lds_flag_put(&fl[(S + DY - 1) & (DY - 1)].h[1], base + S);
 }
 
 // acc -= B y for block b of the planes in v
@@ -684,26 +818,6 @@ __device__ __forceinline__ void block_sub(TC (&acc)[BS], const TC (&v)[NV], int 
     for (int r = 0; r < BS; r++)
 #pragma unroll
         for (int c = 0; c < BS; c++) acc[r] -= v[b * BS * BS + r * BS + c] * y[c];
-}
-
-// value held by the next lower lane (UP = false) or the next higher lane
-// (UP = true) of the wavefront, by whole-wave DPP shifts (no LDS traffic);
-// the lane at the end of the wave receives 0
-template <bool UP>
-__device__ __forceinline__ int lane_shift1(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, UP ? 0x130 : 0x138, 0xF, 0xF, true);
-}
-template <bool UP>
-__device__ __forceinline__ float lane_shift1(float v) {
-    return __int_as_float(lane_shift1<UP>(__float_as_int(v)));
-}
-template <bool UP>
-__device__ __forceinline__ double lane_shift1(double v) {
-    const long long u = __double_as_longlong(v);
-    const int lo = lane_shift1<UP>(static_cast<int>(u & 0xffffffffll));
-    const int hi = lane_shift1<UP>(static_cast<int>(u >> 32));
-    return __longlong_as_double((static_cast<long long>(hi) << 32) |
-                                static_cast<unsigned int>(lo));
 }
 
 // Boundary role.  Lane f of the NF face lanes serves face entry f; `src`
@@ -723,12 +837,18 @@ __device__ __forceinline__ double lane_shift1(double v) {
 // NF * BS values of a full read: these agent-scope loads bypass the L2,
 // and with every tile's boundary wavefront polling, full reads cost 11 to
 // 14% of the sweep time at 256 x 256 x 128.
+// `cell` is the lane's halo cell of a ring slot; step t may be staged once
+// `prog` (and `prog2` where it is given) shows that slot t's results of
+// step t - DY - 1 have been taken from the ring, which also means that the
+// compute wavefront is past step t - DY.
 template <typename TC, int BS>
 __device__ void boundary_role(int S, int nx, int base, int lane, int NF, const TC *src, int lag,
-                              TC (&bring)[DB][NFACE][BS], int *bfull, int *bcons, int *err) {
+                              char *yring, int cell, StepFlag (&fl)[YRing<TC, BS>::DY],
+                              const Progress &prog, const Progress *prog2, int *err) {
     using U = typename Bits<TC>::U;
+    using YR = YRing<TC, BS>;
     const U *q = reinterpret_cast<const U *>(src);
-    const int G = (64 / NF) < DB ? (64 / NF) : DB;
+    const int G = (64 / NF) < YR::DY ? (64 / NF) : YR::DY;
     const int f = lane % NF, g = lane / NF;
     const bool lane_ok = g < G;
     const uint64_t gmask = (NF >= 64 ? ~0ull : ((1ull << NF) - 1ull)) << (lane_ok ? g * NF : 0);
@@ -766,16 +886,15 @@ __device__ void boundary_role(int S, int nx, int base, int lane, int NF, const T
                     ready = ready && u != Bits<TC>::sentinel;
                 }
             }
-            // the slot of step ts held step ts - DB: it must have been read
-            ready = ready && lds_get(bcons) >= base + ts - DB + 1;
+            const int need = base + ts - YR::DY + 1;
+            ready = ready && lds_get(const_cast<int *>(prog.w)) >= need &&
+                    (!prog2 || lds_get(const_cast<int *>(prog2->w)) >= need);
         }
         const bool go = active && (__ballot(ready) & gmask) == gmask;
         lds_acquire();
-        if (go)
-#pragma unroll
-            for (int r = 0; r < BS; r++) bring[ts % DB][f][r] = vals[r];
+        if (go) YR::store(yring, YR::slot(ts), cell, vals);
         lds_release();
-        if (go && f == 0) lds_put(&bfull[ts % DB], base + ts);
+        if (go && f == 0) lds_put(&fl[YR::slot(ts)].h[0], base + ts);
         if (go) ts += G;
         if (__ballot(go) != 0) {
             idle = 0;
@@ -828,82 +947,56 @@ __device__ __forceinline__ void grid_fwd_body(const GridTiles &G, const TF *__re
     // ring step: NM factor planes of TF, then the step's right-hand-side
     // cells as gathered by the DMA pieces of RhsStage
     using RS = RhsStage<TIN, BS>;
+    using YR = YRing<TC, BS>;
+    constexpr int DY = YR::DY;
     constexpr int PB = pad256(NM * 64 * (int)sizeof(TF));
     constexpr int SB = (PB + RS::BYTES + 15) / 16 * 16;
     constexpr int D = ring_slots<SB>();
     constexpr int P = dma_count(PB) + RS::NP;                  // DMA instructions per step
     constexpr int K = (D / NLOAD) < (63 / P) ? (D / NLOAD) : (63 / P);
     __shared__ __attribute__((aligned(16))) char ringb[D * SB];
-    __shared__ TC bring[DB][NFACE][BS];
-    __shared__ int full[D], bfull[DB], cons, bcons, tile;
+    __shared__ __attribute__((aligned(16))) char yring[YR::BYTES];
+    __shared__ StepFlag fl[DY];
+    __shared__ Progress done_p, pub_p;   // steps computed, steps taken by the publisher
+    __shared__ int tile;
     // wave-uniform role index (an SGPR), so the roles are real branches
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (blk == 0 && (int)threadIdx.x < G.NQ) other_ctr[threadIdx.x] = 0;
-    if (threadIdx.x < D) full[threadIdx.x] = -1;
-    if (threadIdx.x < DB) bfull[threadIdx.x] = -1;
-    if (threadIdx.x == 0) {
-        cons = 0;
-        bcons = 0;
-    }
+    if (threadIdx.x < DY) fl[threadIdx.x].h[0] = fl[threadIdx.x].h[1] = -1;
+    if (threadIdx.x < 64) done_p.w[threadIdx.x] = pub_p.w[threadIdx.x] = 0;
     const int TJ = G.TJ, TK = G.TK, NF = G.NF, nx = G.nx, S = G.S;
-    const int64_t sJ = G.nx, sK = (int64_t)G.nx * G.ny;
     const int jj = lane % TJ, kk = lane / TJ;
+    const int own = (kk + 1) * (TJ + 1) + jj + 1;   // this lane's cell of a ring slot
     if (wave == 0) {
         // ---- compute ----
-        // face entries this lane publishes (high faces feed tiles J+1, K+1)
-        const int fj = jj == TJ - 1 && kk < TK ? kk : -1;
-        const int fk = kk == TK - 1 ? TK + jj : -1;
-        const int oj = fj * BS, ok = fk * BS;
-        for (int base = 0;; base += S) {
+        auto read_step = [&](const char *sl, TC (&v)[NV]) {
+            const TF *pl = reinterpret_cast<const TF *>(sl);
+#pragma unroll
+            for (int e = 0; e < NM; e++) v[e] = cvt<TC, TF>(pl[e * 64 + lane]);
+            RS::template read<TC>(sl + PB, lane, v + NM);
+        };
+        for (int base = 0;; base += S + 1) {
             const int T = next_tile(G, ctr, &tile, false, blk);
             if (T < 0) break;
-            TC *yrow = yt + (int64_t)T * S * BS * 64 + lane;
-            TC *frow = ff + (int64_t)T * S * NF * BS;
-            // the right-hand side of a lane outside the grid, or of a step
-            // outside its line, is zero (its staged words are not loaded)
-            const int JK = G.order[T];
-            const bool lane_ok = lane < TJ * TK && (JK & 0xffff) * TJ + jj < G.ny &&
-                                 (JK >> 16) * TK + kk < G.nz;
-            auto read_step = [&](int t, TC (&v)[NV]) {
-                const char *sl = ringb + (t % D) * SB;
-                const TF *pl = reinterpret_cast<const TF *>(sl);
-#pragma unroll
-                for (int e = 0; e < NM; e++) v[e] = cvt<TC, TF>(pl[e * 64 + lane]);
-                const int i = t - jj - kk;
-                const bool ok = lane_ok && i >= 0 && i < nx;
-#pragma unroll
-                for (int r = 0; r < BS; r++) {
-                    const TC x = RS::template value<TC>(sl + PB, lane, r);
-                    v[NM + r] = ok ? x : TC(0);
-                }
-            };
             TC yp[BS];
 #pragma unroll
             for (int r = 0; r < BS; r++) yp[r] = TC(0);
-            int pa = -2, pb = -2;   // stamps of the next step, read one step early
+            YR::store(yring, 0, own, yp);   // no results before step 0
+            progress_put(done_p, lane, base);
+            unsigned long long pre = ~0ull;   // flag of the next step, read one step early
+            int slot = D > 1 ? SB : 0;        // byte offset of step t + 1's planes
             // step t computes with the planes in vc and reads the planes of
             // step t + 1 into vn; the two arrays swap roles every step
             auto step = [&](int t, const TC (&vc)[NV], TC (&vn)[NV]) {
-                const int st = base + t, bslot = t % DB;
-                const bool more = t + 1 < S;
-                // this step's boundary and the next step's planes: one poll,
-                // skipped when the stamps read during the previous step show both
-                lds_wait_pair_pre(pa, pb, &bfull[bslot], st, &full[(t + 1) % D], more ? st + 1 : -1,
-                                  err);
+                const int st = base + t;
+                step_wait(pre, fl[YR::slot(t)], st, err);
                 TC yj[BS], yk[BS];
-#pragma unroll
-                for (int r = 0; r < BS; r++) {
-                    const TC bj = bring[bslot][kk < TK ? kk : 0][r];
-                    const TC bk = bring[bslot][TK + jj][r];
-                    yj[r] = lane_shift1<false>(yp[r]);
-                    yk[r] = __shfl_up(yp[r], TJ, 64);
-                    if (jj == 0) yj[r] = bj;
-                    if (kk == 0) yk[r] = bk;
-                }
-                if (more) read_step(t + 1, vn);
-                pa = lds_get(&bfull[(t + 1) % DB]);
-                pb = t + 2 < S ? lds_get(&full[(t + 2) % D]) : -1;
+                YR::load(yring, YR::slot(t), own - (TJ + 1), yk);
+                YR::load(yring, YR::slot(t), own - 1, yj);
+                read_step(ringb + slot, vn);
+                slot = slot == (D - 1) * SB ? 0 : slot + SB;
+                pre = step_flag_get(fl[YR::slot(t + 1)]);
                 TC acc[BS];
 #pragma unroll
                 for (int r = 0; r < BS; r++) acc[r] = vc[NM + r];
@@ -911,27 +1004,13 @@ __device__ __forceinline__ void grid_fwd_body(const GridTiles &G, const TF *__re
                 block_sub<BS>(acc, vc, 1, yj);
                 block_sub<BS>(acc, vc, 2, yp);
 #pragma unroll
-                for (int r = 0; r < BS; r++) {
-                    yp[r] = acc[r];
-                    yrow[(t * BS + r) * 64] = acc[r];
-                }
-                {
-                    TC pub[BS];
-                    unsentinel<TC, BS>(acc, pub);
-                    TC *ft = frow + (int64_t)t * NF * BS;
-                    if (fj >= 0) publish_checked<TC, BS>(ft + oj, pub);
-                    if (fk >= 0) publish_checked<TC, BS>(ft + ok, pub);
-                }
-                // every LDS read of this step has returned: hand both slots back
-                lds_release();
-                if (lane == 0) {
-                    lds_put(&bcons, st + 1);
-                    lds_put(&cons, more ? st + 2 : st + 1);
-                }
+                for (int r = 0; r < BS; r++) yp[r] = acc[r];
+                YR::store(yring, YR::slot(t + 1), own, yp);
+                progress_put(done_p, lane, st + 1);
             };
             TC va[NV], vb[NV];
-            lds_wait_eq(&full[0], base, err);
-            read_step(0, va);
+            lds_wait_eq(&fl[DY - 1].h[1], base, err);
+            read_step(ringb, va);
             int t = 0;
             for (; t + 1 < S; t += 2) {
                 step(t, va, vb);
@@ -942,7 +1021,8 @@ __device__ __forceinline__ void grid_fwd_body(const GridTiles &G, const TF *__re
     } else if (wave == 1) {
         // ---- boundary: faces of tiles (J-1, K) and (J, K-1) ----
         const int f = lane % NF;
-        for (int base = 0;; base += S) {
+        const int cell = f < TK ? (f + 1) * (TJ + 1) : f - TK + 1;
+        for (int base = 0;; base += S + 1) {
             const int T = next_tile(G, ctr, &tile, false, blk);
             if (T < 0) break;
             const int JK = G.order[T];
@@ -959,12 +1039,12 @@ __device__ __forceinline__ void grid_fwd_body(const GridTiles &G, const TF *__re
                     src = ff + (((int64_t)G.tidx[J * G.NK + K - 1] * S + (TK - 1)) * NF + f) * BS;
                 lag = q;
             }
-            boundary_role<TC, BS>(S, nx, base, lane, NF, src, lag, bring, bfull, &bcons, err);
+            boundary_role<TC, BS>(S, nx, base, lane, NF, src, lag, yring, cell, fl, pub_p, nullptr, err);
         }
-    } else {
+    } else if (wave < 2 + NLOAD) {
         // ---- loaders: DMA of steps w, w + NLOAD, ... ----
         const int w = wave - 2;
-        for (int base = 0;; base += S) {
+        for (int base = 0;; base += S + 1) {
             const int T = next_tile(G, ctr, &tile, false, blk);
             if (T < 0) break;
             const int JK = G.order[T];
@@ -973,31 +1053,131 @@ __device__ __forceinline__ void grid_fwd_body(const GridTiles &G, const TF *__re
             const int64_t cl = lane_ok ? vsJ * j + vsK * k : 0;
             const TF *lb = Lt + (int64_t)T * S * NM * 64;
             // every step issues the same P instructions (the wait counts
-            // assume it): a lane with no cell loads b[0], which the compute
-            // wavefront discards
+            // assume it): a lane with no cell loads zeros
             auto issue = [&](int t) {
                 char *sl = ringb + (t % D) * SB;
                 dma_block<PB>(lb + (int64_t)t * NM * 64, sl, lane);
                 const int i = t - jj - kk;
                 const bool ok = lane_ok && i >= 0 && i < nx;
-                RS::load(b + (ok ? (cl + i) * BS : 0), sl + PB);
+                RS::load(ok ? b + (cl + i) * BS : reinterpret_cast<const TIN *>(zero_cell), sl + PB);
             };
-            loader_loop<D, P, K>(w, S, base, &cons, full, lane, err, issue);
+            loader_loop<D, P, K>(w, S, base, done_p, fl, lane, err, issue);
             // the backward sweep's face slots of this tile start unwritten
             TC *fr = fb + (int64_t)T * S * NF * BS;
             for (int64_t e = w * 64 + lane; e < (int64_t)S * NF * BS; e += NLOAD * 64)
                 fr[e] = sentinel_value<TC>();
         }
+    } else if (wave == 5) {
+        // ---- publisher: high faces feed tiles J+1, K+1 ----
+        const int fj = jj == TJ - 1 && kk < TK ? kk : -1;
+        const int fk = kk == TK - 1 ? TK + jj : -1;
+        for (int base = 0;; base += S + 1) {
+            const int T = next_tile(G, ctr, &tile, false, blk);
+            if (T < 0) break;
+            TC *yrow = yt + (int64_t)T * S * BS * 64 + lane;
+            TC *frow = ff + (int64_t)T * S * NF * BS;
+            int seen = base;
+            for (int t = 0; t < S; t++) {
+                progress_wait(done_p, base + t + 1, seen, err);
+                TC y[BS], pub[BS];
+                YR::load(yring, YR::slot(t + 1), own, y);
+                progress_put(pub_p, lane, base + t + 1);
+                unsentinel<TC, BS>(y, pub);
+                TC *ft = frow + (int64_t)t * NF * BS;
+                if (fj >= 0) publish_checked<TC, BS>(ft + fj * BS, pub);
+                if (fk >= 0) publish_checked<TC, BS>(ft + fk * BS, pub);
+#pragma unroll
+                for (int r = 0; r < BS; r++) yrow[(t * BS + r) * 64] = y[r];
+            }
+        }
+    } else {
+        while (next_tile(G, ctr, &tile, false, blk) >= 0) {
+        }
     }
 }
 
-template <int BS, typename TF, typename TD, typename TC, typename TO>
+// cells of a grid written by the backward sweep: those with i in [i0, i1),
+// j in [j0, j1), k in [k0, k1), at (i + j vsJ + k vsK) BS of the output (all
+// of a whole grid's; a subdomain's owned cells under RAS)
+struct OutBox {
+    int i0, i1, j0, j1, k0, k1;
+    int64_t vsJ, vsK;
+};
+
+// Writer role of the backward sweep.  It takes CK steps of a tile at a time
+// from the result ring, a lane one cell of a group of 64 / CK lines, so that
+// a store covers runs of CK consecutive cells of each line (96 bytes for
+// three doubles): the run of the next CK steps completes the cache lines in
+// the XCD's L2.  The epilogues of ilu_apply: ADD 0 xo = x; 1 add_out =
+// add_in + x; 2 add_out = (add_in[cell], 0, 0) + x.  Their operands are
+// loaded before the wait for the steps, off everyone's critical path.
+template <int BS, typename TC, typename TO, int ADD, typename TAI, typename TAO>
+__device__ __forceinline__ void writer_role(const GridTiles &G, int T, int base, int lane,
+                                            const char *yring, const Progress &done_p, Progress &wr_p,
+                                            const OutBox &box, TO *__restrict__ xo,
+                                            const TAI *__restrict__ add_in,
+                                            TAO *__restrict__ add_out, int *err) {
+    using YR = YRing<TC, BS>;
+    constexpr int CK = YR::DY / 4, LPI = 64 / CK, NA = ADD == 1 ? BS : 1;
+    const int TJ = G.TJ, TK = G.TK, S = G.S;
+    const int JK = G.order[T];
+    const int j0 = (JK & 0xffff) * TJ, k0 = (JK >> 16) * TK;
+    const int rTJ = 65536 / TJ + 1;   // l / TJ = (l rTJ) >> 16 for l < 64, TJ <= 8
+    int seen = base;
+    for (int c0 = 0; c0 < S; c0 += CK) {
+        const int tau = c0 + lane % CK;
+        int64_t off[CK];
+        int cell[CK];
+        TAI ain[ADD ? CK : 1][NA];
+#pragma unroll
+        for (int g = 0; g < CK; g++) {
+            const int l = g * LPI + lane / CK;
+            const int kk = (l * rTJ) >> 16, jj = l - kk * TJ;
+            const int i = S - 1 - tau - jj - kk, j = j0 + jj, k = k0 + kk;
+            const bool ok = tau < S && l < TJ * TK && i >= box.i0 && i < box.i1 && j >= box.j0 &&
+                            j < box.j1 && k >= box.k0 && k < box.k1;
+            off[g] = ok ? i + box.vsJ * j + box.vsK * k : -1;
+            cell[g] = ((kk < TK ? TK - 1 - kk : kk) + 1) * (TJ + 1) + TJ - jj;
+            if (ADD)
+#pragma unroll
+                for (int r = 0; r < NA; r++) ain[g][r] = ok ? add_in[off[g] * NA + r] : TAI(0);
+        }
+        const int upto = base + (c0 + CK < S ? c0 + CK : S);
+        progress_wait(done_p, upto, seen, err);
+#pragma unroll
+        for (int g = 0; g < CK; g++) {
+            TC v[BS];
+            YR::load(yring, YR::slot(tau + 1), cell[g], v);
+            if (off[g] < 0) continue;
+#pragma unroll
+            for (int r = 0; r < BS; r++) {
+                if (ADD == 0) xo[off[g] * BS + r] = static_cast<TO>(v[r]);
+                if (ADD == 1)
+                    add_out[off[g] * BS + r] = static_cast<TAO>(ain[g][r]) + static_cast<TAO>(v[r]);
+                if (ADD == 2) {
+                    const TC base0 = (r == 0) ? static_cast<TC>(ain[g][0]) : TC(0);
+                    add_out[off[g] * BS + r] = static_cast<TAO>(base0 + v[r]);
+                }
+            }
+        }
+        asm volatile("" : : : "memory");
+        progress_put(wr_p, lane, upto);
+    }
+}
+
+template <int BS, typename TF, typename TD, typename TC, typename TO, int ADD, typename TAI,
+          typename TAO>
 __device__ __forceinline__ void grid_bwd_body(const GridTiles &G, const TF *__restrict__ Ut,
-                                              const TD *__restrict__ Dt, TC *yt, TC *fb, TC *ff,
-                                              int *ctr, int *other_ctr, int *err, int blk) {
+                                              const TD *__restrict__ Dt, const TC *yt, TC *fb, TC *ff,
+                                              int *ctr, int *other_ctr, int *err, int blk,
+                                              const OutBox &box, TO *__restrict__ xo,
+                                              const TAI *__restrict__ add_in,
+                                              TAO *__restrict__ add_out) {
     constexpr int B2 = BS * BS, NM = 3 * B2, NV = NM + B2 + BS;
     // ring step: NM factor planes of TF, B2 diagonal-inverse planes of TD,
     // BS forward-result planes of TC
+    using YR = YRing<TC, BS>;
+    constexpr int DY = YR::DY;
     constexpr int PB = pad256(NM * 64 * (int)sizeof(TF)), DBY = B2 * 64 * (int)sizeof(TD);
     constexpr int YB = BS * 64 * (int)sizeof(TC);
     constexpr int SB = PB + DBY + YB;
@@ -1005,100 +1185,72 @@ __device__ __forceinline__ void grid_bwd_body(const GridTiles &G, const TF *__re
     constexpr int P = dma_count(PB) + dma_count(DBY) + dma_count(YB);
     constexpr int K = (D / NLOAD) < (63 / P) ? (D / NLOAD) : (63 / P);
     __shared__ __attribute__((aligned(16))) char ringb[D * SB];
-    __shared__ TC bring[DB][NFACE][BS];
-    __shared__ int full[D], bfull[DB], cons, bcons, tile;
+    __shared__ __attribute__((aligned(16))) char yring[YR::BYTES];
+    __shared__ StepFlag fl[DY];
+    __shared__ Progress done_p, pub_p, wr_p;   // computed, published, written
+    __shared__ int tile;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (blk == 0 && (int)threadIdx.x < G.NQ) other_ctr[threadIdx.x] = 0;
-    if (threadIdx.x < D) full[threadIdx.x] = -1;
-    if (threadIdx.x < DB) bfull[threadIdx.x] = -1;
-    if (threadIdx.x == 0) {
-        cons = 0;
-        bcons = 0;
-    }
+    if (threadIdx.x < DY) fl[threadIdx.x].h[0] = fl[threadIdx.x].h[1] = -1;
+    if (threadIdx.x < 64) done_p.w[threadIdx.x] = pub_p.w[threadIdx.x] = wr_p.w[threadIdx.x] = 0;
     const int TJ = G.TJ, TK = G.TK, NF = G.NF, nx = G.nx, S = G.S;
     const int jj = lane % TJ, kk = lane / TJ;
+    // the ring slots hold the tile mirrored in j and k, so the +1 neighbours
+    // sit where the forward sweep has its -1 neighbours
+    const int own = ((kk < TK ? TK - 1 - kk : kk) + 1) * (TJ + 1) + TJ - jj;
     if (wave == 0) {
         // ---- compute ----
-        // face entries this lane publishes (low faces feed tiles J-1, K-1)
-        const int fj = jj == 0 && kk < TK ? kk : -1;
-        const int fk = kk == 0 ? TK + jj : -1;
-        const int oj = fj * BS, ok = fk * BS;
-        for (int base = 0;; base += S) {
+        auto read_step = [&](const char *sl, TC (&v)[NV]) {
+            const TF *pu = reinterpret_cast<const TF *>(sl);
+            const TD *pd = reinterpret_cast<const TD *>(sl + PB);
+            const TC *py = reinterpret_cast<const TC *>(sl + PB + DBY);
+#pragma unroll
+            for (int e = 0; e < NM; e++) v[e] = cvt<TC, TF>(pu[e * 64 + lane]);
+#pragma unroll
+            for (int e = 0; e < B2; e++) v[NM + e] = static_cast<TC>(pd[e * 64 + lane]);
+#pragma unroll
+            for (int r = 0; r < BS; r++) v[NM + B2 + r] = py[r * 64 + lane];
+        };
+        for (int base = 0;; base += S + 1) {
             const int T = next_tile(G, ctr, &tile, true, blk);   // reverse tile order
             if (T < 0) break;
-            TC *yrow = yt + (int64_t)T * S * BS * 64 + lane;
-            TC *frow = fb + (int64_t)T * S * NF * BS;
-            auto read_step = [&](int t, TC (&v)[NV]) {
-                const char *sl = ringb + (t % D) * SB;
-                const TF *pu = reinterpret_cast<const TF *>(sl);
-                const TD *pd = reinterpret_cast<const TD *>(sl + PB);
-                const TC *py = reinterpret_cast<const TC *>(sl + PB + DBY);
-#pragma unroll
-                for (int e = 0; e < NM; e++) v[e] = cvt<TC, TF>(pu[e * 64 + lane]);
-#pragma unroll
-                for (int e = 0; e < B2; e++) v[NM + e] = static_cast<TC>(pd[e * 64 + lane]);
-#pragma unroll
-                for (int r = 0; r < BS; r++) v[NM + B2 + r] = py[r * 64 + lane];
-            };
             TC xp[BS];
 #pragma unroll
             for (int r = 0; r < BS; r++) xp[r] = TC(0);
-            int pa = -2, pb = -2;   // stamps of the next step, read one step early
+            YR::store(yring, 0, own, xp);
+            progress_put(done_p, lane, base);
+            unsigned long long pre = ~0ull;
+            int slot = D > 1 ? SB : 0;
             auto step = [&](int t, const TC (&vc)[NV], TC (&vn)[NV]) {
-                const int st = base + t, bslot = t % DB;
-                const bool more = t + 1 < S;
-                lds_wait_pair_pre(pa, pb, &bfull[bslot], st, &full[(t + 1) % D], more ? st + 1 : -1,
-                                  err);
+                const int st = base + t;
+                step_wait(pre, fl[YR::slot(t)], st, err);
                 TC xj[BS], xk[BS];
-#pragma unroll
-                for (int r = 0; r < BS; r++) {
-                    const TC bj = bring[bslot][kk < TK ? kk : 0][r];
-                    const TC bk = bring[bslot][TK + jj][r];
-                    xj[r] = lane_shift1<true>(xp[r]);
-                    xk[r] = __shfl_down(xp[r], TJ, 64);
-                    if (jj == TJ - 1) xj[r] = bj;
-                    if (kk == TK - 1) xk[r] = bk;
-                }
-                if (more) read_step(t + 1, vn);
-                pa = lds_get(&bfull[(t + 1) % DB]);
-                pb = t + 2 < S ? lds_get(&full[(t + 2) % D]) : -1;
+                YR::load(yring, YR::slot(t), own - 1, xj);
+                YR::load(yring, YR::slot(t), own - (TJ + 1), xk);
+                read_step(ringb + slot, vn);
+                slot = slot == (D - 1) * SB ? 0 : slot + SB;
+                pre = step_flag_get(fl[YR::slot(t + 1)]);
                 TC acc[BS];
 #pragma unroll
                 for (int r = 0; r < BS; r++) acc[r] = vc[NM + B2 + r];
                 block_sub<BS>(acc, vc, 0, xp);
                 block_sub<BS>(acc, vc, 1, xj);
                 block_sub<BS>(acc, vc, 2, xk);
-                TC res[BS];
+                // neighbours consume the value as the caller's output type
 #pragma unroll
                 for (int r = 0; r < BS; r++) {
                     TC sum = TC(0);
 #pragma unroll
                     for (int q = 0; q < BS; q++) sum += vc[NM + r * BS + q] * acc[q];
-                    res[r] = sum;
+                    xp[r] = static_cast<TC>(static_cast<TO>(sum));
                 }
-                // neighbours consume the value as the caller's output type
-#pragma unroll
-                for (int r = 0; r < BS; r++) {
-                    xp[r] = static_cast<TC>(static_cast<TO>(res[r]));
-                    yrow[((S - 1 - t) * BS + r) * 64] = res[r];
-                }
-                {
-                    TC pub[BS];
-                    unsentinel<TC, BS>(xp, pub);
-                    TC *ft = frow + (int64_t)t * NF * BS;
-                    if (fj >= 0) publish_checked<TC, BS>(ft + oj, pub);
-                    if (fk >= 0) publish_checked<TC, BS>(ft + ok, pub);
-                }
-                lds_release();
-                if (lane == 0) {
-                    lds_put(&bcons, st + 1);
-                    lds_put(&cons, more ? st + 2 : st + 1);
-                }
+                YR::store(yring, YR::slot(t + 1), own, xp);
+                progress_put(done_p, lane, st + 1);
             };
             TC va[NV], vb[NV];
-            lds_wait_eq(&full[0], base, err);
-            read_step(0, va);
+            lds_wait_eq(&fl[DY - 1].h[1], base, err);
+            read_step(ringb, va);
             int t = 0;
             for (; t + 1 < S; t += 2) {
                 step(t, va, vb);
@@ -1109,7 +1261,8 @@ __device__ __forceinline__ void grid_bwd_body(const GridTiles &G, const TF *__re
     } else if (wave == 1) {
         // ---- boundary: faces of tiles (J+1, K) and (J, K+1) ----
         const int f = lane % NF;
-        for (int base = 0;; base += S) {
+        const int cell = f < TK ? (TK - f) * (TJ + 1) : TJ - (f - TK);
+        for (int base = 0;; base += S + 1) {
             const int T = next_tile(G, ctr, &tile, true, blk);
             if (T < 0) break;
             const int JK = G.order[T];
@@ -1126,12 +1279,12 @@ __device__ __forceinline__ void grid_bwd_body(const GridTiles &G, const TF *__re
                     src = fb + (((int64_t)G.tidx[J * G.NK + K + 1] * S + (TK - 1)) * NF + f) * BS;
                 lag = TJ - 1 - q;
             }
-            boundary_role<TC, BS>(S, nx, base, lane, NF, src, lag, bring, bfull, &bcons, err);
+            boundary_role<TC, BS>(S, nx, base, lane, NF, src, lag, yring, cell, fl, pub_p, &wr_p, err);
         }
-    } else {
+    } else if (wave < 2 + NLOAD) {
         // ---- loaders: DMA of U blocks, diagonal inverses, forward result ----
         const int w = wave - 2;
-        for (int base = 0;; base += S) {
+        for (int base = 0;; base += S + 1) {
             const int T = next_tile(G, ctr, &tile, true, blk);
             if (T < 0) break;
             const TF *ub = Ut + (int64_t)T * S * NM * 64;
@@ -1144,57 +1297,42 @@ __device__ __forceinline__ void grid_bwd_body(const GridTiles &G, const TF *__re
                 // the forward result of the same cells: forward step S - 1 - t
                 dma_block<YB>(yb + (int64_t)(S - 1 - t) * BS * 64, sl + PB + DBY, lane);
             };
-            loader_loop<D, P, K>(w, S, base, &cons, full, lane, err, issue);
+            loader_loop<D, P, K>(w, S, base, done_p, fl, lane, err, issue);
             // the forward sweep's face slots of this tile start unwritten
             TC *fr = ff + (int64_t)T * S * NF * BS;
             for (int64_t e = w * 64 + lane; e < (int64_t)S * NF * BS; e += NLOAD * 64)
                 fr[e] = sentinel_value<TC>();
         }
-    }
-}
-
-// Copy the tile-step-major result to natural order, with the caller's
-// epilogue (the add modes of ilu_apply): one block per (tile, 8 steps),
-// reads in contiguous 64-lane rows.
-// cells of a grid written by an untile: those with i in [i0, i1), j in
-// [j0, j1), k in [k0, k1), at (i + j vsJ + k vsK) BS of the output
-struct UntileBox {
-    int i0, i1, j0, j1, k0, k1;
-    int64_t vsJ, vsK;
-};
-
-// natural-order copy of the tile-step result of one grid with the fused
-// epilogue, restricted to the cells of `box` (all of them for a whole grid;
-// a subdomain's owned cells under RAS)
-template <int BS, typename TC, typename TO, int ADD, typename TAI, typename TAO>
-__device__ __forceinline__ void grid_untile_body(const GridTiles &G, const TC *__restrict__ yt,
-                                                 TO *__restrict__ xo,
-                                                 const TAI *__restrict__ add_in,
-                                                 TAO *__restrict__ add_out, const UntileBox &box,
-                                                 int blk) {
-    const int nchunk = (G.S + 7) / 8;
-    const int T = blk / nchunk, t0 = (blk % nchunk) * 8;
-    const int lane = threadIdx.x & 63;
-    const int JK = G.order[T];
-    const int jj = lane % G.TJ, kk = lane / G.TJ;
-    const int j = (JK & 0xffff) * G.TJ + jj, k = (JK >> 16) * G.TK + kk;
-    if (lane >= G.TJ * G.TK || j >= G.ny || k >= G.nz) return;
-    if (j < box.j0 || j >= box.j1 || k < box.k0 || k >= box.k1) return;
-    const int64_t cl = box.vsJ * j + box.vsK * k;
-    for (int t = t0 + (threadIdx.x >> 6); t < t0 + 8 && t < G.S; t += 4) {
-        const int i = t - jj - kk;
-        if (i < box.i0 || i >= box.i1 || i >= G.nx) continue;
-        const int64_t c = cl + i;
-        const TC *src = yt + ((int64_t)T * G.S + t) * BS * 64 + lane;
-#pragma unroll
-        for (int r = 0; r < BS; r++) {
-            const TC v = src[r * 64];
-            if (ADD == 0) xo[c * BS + r] = static_cast<TO>(v);
-            if (ADD == 1) add_out[c * BS + r] = static_cast<TAO>(add_in[c * BS + r]) + static_cast<TAO>(v);
-            if (ADD == 2) {
-                const TC base0 = (r == 0) ? static_cast<TC>(add_in[c]) : TC(0);
-                add_out[c * BS + r] = static_cast<TAO>(base0 + v);
+    } else if (wave == 5) {
+        // ---- publisher: low faces feed tiles J-1, K-1 ----
+        const int fj = jj == 0 && kk < TK ? kk : -1;
+        const int fk = kk == 0 ? TK + jj : -1;
+        for (int base = 0;; base += S + 1) {
+            const int T = next_tile(G, ctr, &tile, true, blk);
+            if (T < 0) break;
+            TC *frow = fb + (int64_t)T * S * NF * BS;
+            int seen = base;
+            for (int t = 0; t < S; t++) {
+                progress_wait(done_p, base + t + 1, seen, err);
+                TC x[BS], pub[BS];
+                YR::load(yring, YR::slot(t + 1), own, x);
+                progress_put(pub_p, lane, base + t + 1);
+                unsentinel<TC, BS>(x, pub);
+                TC *ft = frow + (int64_t)t * NF * BS;
+                if (fj >= 0) publish_checked<TC, BS>(ft + fj * BS, pub);
+                if (fk >= 0) publish_checked<TC, BS>(ft + fk * BS, pub);
             }
+        }
+    } else if (wave == 6) {
+        // ---- writer ----
+        for (int base = 0;; base += S + 1) {
+            const int T = next_tile(G, ctr, &tile, true, blk);
+            if (T < 0) break;
+            writer_role<BS, TC, TO, ADD, TAI, TAO>(G, T, base, lane, yring, done_p, wr_p, box, xo,
+                                                   add_in, add_out, err);
+        }
+    } else {
+        while (next_tile(G, ctr, &tile, true, blk) >= 0) {
         }
     }
 }
@@ -1207,67 +1345,16 @@ __global__ __launch_bounds__(GWG) void k_grid_fwd(GridTiles G, const TF *__restr
                                    (int64_t)G.nx * G.ny);
 }
 
-template <int BS, typename TF, typename TD, typename TC, typename TO>
+template <int BS, typename TF, typename TD, typename TC, typename TO, int ADD, typename TAI,
+          typename TAO>
 __global__ __launch_bounds__(GWG) void k_grid_bwd(GridTiles G, const TF *__restrict__ Ut,
-                                                  const TD *__restrict__ Dt, TC *yt, TC *fb,
-                                                  TC *ff, int *ctr, int *other_ctr, int *err) {
-    grid_bwd_body<BS, TF, TD, TC, TO>(G, Ut, Dt, yt, fb, ff, ctr, other_ctr, err, blockIdx.x);
-}
-
-// Natural-order copy of a whole grid's tile-step result with the epilogue
-// of ilu_apply.  A block takes UNT_CH consecutive steps of one tile (16: a
-// 25 KB LDS tile, six blocks per CU; 32 steps, three blocks per CU, took
-// 50% longer at 256 x 256 x 128): it reads
-// them as contiguous rows into LDS, line by line (line = lane of the tile),
-// then writes each line's UNT_CH cells as one contiguous run, so a wavefront
-// store covers one line's 16 cells (384 contiguous bytes in FP64) instead
-// of one cell of 64 different lines.  Blocks b,
-// b + 8, b + 16, ... run on one XCD; the chunks of one tile are given to
-// consecutive blocks of the same XCD, so the cache line that two chunks of
-// a line share is completed in that XCD's L2 before it is written back.
-constexpr int UNT_CH = 16;
-
-template <int BS, typename TC, typename TO, int ADD, typename TAI, typename TAO>
-__global__ __launch_bounds__(256) void k_grid_untile(GridTiles G, const TC *__restrict__ yt,
-                                                     TO *__restrict__ xo,
-                                                     const TAI *__restrict__ add_in,
-                                                     TAO *__restrict__ add_out) {
-    constexpr int LV = UNT_CH * BS;   // values of one line in a chunk
-    constexpr int LS = LV + 1;        // odd LDS stride: the row writes hit distinct banks
-    __shared__ TC lds[64 * LS];
-    const int nchunk = (G.S + UNT_CH - 1) / UNT_CH;
-    const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
-    const int T = 8 * (idx / nchunk) + xcd, c = idx % nchunk;
-    if (T >= G.ntiles) return;
-    const int t0 = c * UNT_CH, nt = min(UNT_CH, G.S - t0);
-    const TC *src = yt + ((int64_t)T * G.S + t0) * BS * 64;
-    for (int e = threadIdx.x; e < nt * BS * 64; e += 256) {
-        const int tl = e / (BS * 64), r = (e / 64) % BS, ln = e % 64;
-        lds[ln * LS + tl * BS + r] = src[e];
-    }
-    __syncthreads();
-    const int JK = G.order[T];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t vsK = (int64_t)G.nx * G.ny;
-    for (int l = wv; l < G.TJ * G.TK; l += 4) {
-        const int jj = l % G.TJ, kk = l / G.TJ;
-        const int j = (JK & 0xffff) * G.TJ + jj, k = (JK >> 16) * G.TK + kk;
-        if (j >= G.ny || k >= G.nz) continue;
-        const int xs = t0 - jj - kk;   // x of the line's first cell in this chunk
-        const int64_t cl = vsK * k + (int64_t)G.nx * j;
-        for (int e = lane; e < nt * BS; e += 64) {
-            const int x = xs + e / BS, r = e % BS;
-            if (x < 0 || x >= G.nx) continue;
-            const TC v = lds[l * LS + e];
-            const int64_t o = (cl + x) * BS + r;
-            if (ADD == 0) xo[o] = static_cast<TO>(v);
-            if (ADD == 1) add_out[o] = static_cast<TAO>(add_in[o]) + static_cast<TAO>(v);
-            if (ADD == 2) {
-                const TC base0 = (r == 0) ? static_cast<TC>(add_in[cl + x]) : TC(0);
-                add_out[o] = static_cast<TAO>(base0 + v);
-            }
-        }
-    }
+                                                  const TD *__restrict__ Dt, const TC *yt, TC *fb,
+                                                  TC *ff, int *ctr, int *other_ctr, int *err,
+                                                  TO *__restrict__ xo, const TAI *__restrict__ add_in,
+                                                  TAO *__restrict__ add_out) {
+    const OutBox box{0, G.nx, 0, G.ny, 0, G.nz, G.nx, (int64_t)G.nx * G.ny};
+    grid_bwd_body<BS, TF, TD, TC, TO, ADD, TAI, TAO>(G, Ut, Dt, yt, fb, ff, ctr, other_ctr, err,
+                                                     blockIdx.x, box, xo, add_in, add_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1275,17 +1362,16 @@ __global__ __launch_bounds__(256) void k_grid_untile(GridTiles G, const TC *__re
 // owns the workgroups [wg0, wg0 + wgs) of each kernel (multiples of
 // GRID_QUEUES, so a workgroup's queue, and XCD, keep their mapping)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int find_grid(const GridMulti *__restrict__ d, int ngrid, int blk,
-                                         int GridMulti::*wg0) {
+__device__ __forceinline__ int find_grid(const GridMulti *__restrict__ d, int ngrid, int blk) {
     int g = 0;
-    while (g + 1 < ngrid && blk >= d[g + 1].*wg0) g++;
+    while (g + 1 < ngrid && blk >= d[g + 1].wg0) g++;
     return g;
 }
 
 template <int BS>
 __global__ __launch_bounds__(GWG) void k_grid_fwd_multi(const GridMulti *__restrict__ d, int ngrid,
                                                         const double *__restrict__ v, int *err) {
-    const int g = find_grid(d, ngrid, blockIdx.x, &GridMulti::wg0);
+    const int g = find_grid(d, ngrid, blockIdx.x);
     const GridMulti D = d[g];
     grid_fwd_body<BS, double, double, double>(D.G, D.lt, v + D.boff, D.yt, D.ff, D.fb, D.ctr,
                                               D.ctr + D.G.NQ, err, blockIdx.x - D.wg0, D.vsJ,
@@ -1294,33 +1380,23 @@ __global__ __launch_bounds__(GWG) void k_grid_fwd_multi(const GridMulti *__restr
 
 template <int BS>
 __global__ __launch_bounds__(GWG) void k_grid_bwd_multi(const GridMulti *__restrict__ d, int ngrid,
-                                                        int *err) {
-    const int g = find_grid(d, ngrid, blockIdx.x, &GridMulti::wg0);
+                                                        double *__restrict__ z, int *err) {
+    const int g = find_grid(d, ngrid, blockIdx.x);
     const GridMulti D = d[g];
-    grid_bwd_body<BS, double, double, double, double>(D.G, D.ut, D.dt, D.yt, D.fb, D.ff,
-                                                      D.ctr + D.G.NQ, D.ctr, err,
-                                                      blockIdx.x - D.wg0);
+    const OutBox box{D.oi0, D.oi1, D.oj0, D.oj1, D.ok0, D.ok1, D.vsJ, D.vsK};
+    grid_bwd_body<BS, double, double, double, double, 0, double, double>(
+        D.G, D.ut, D.dt, D.yt, D.fb, D.ff, D.ctr + D.G.NQ, D.ctr, err, blockIdx.x - D.wg0, box,
+        z + D.boff, nullptr, nullptr);
 }
 
-template <int BS>
-__global__ __launch_bounds__(256) void k_grid_untile_multi(const GridMulti *__restrict__ d,
-                                                           int ngrid, double *__restrict__ z) {
-    const int g = find_grid(d, ngrid, blockIdx.x, &GridMulti::ub0);
-    const GridMulti D = d[g];
-    const UntileBox box{D.oi0, D.oi1, D.oj0, D.oj1, D.ok0, D.ok1, D.vsJ, D.vsK};
-    grid_untile_body<BS, double, double, 0, double, double>(D.G, D.yt, z + D.boff, nullptr,
-                                                            nullptr, box, blockIdx.x - D.ub0);
-}
-
-int grid_multi_launch_size(const IluFactor &F, int *wgs, int *untile_blocks) {
+int grid_multi_launch_size(const IluFactor &F, int *wgs) {
     if (!F.grid) return set_error(KRY_ERR_ARG, "grid_multi: not a grid-tiled factor");
     *wgs = F.G.NQ * std::max(1, std::min(F.G.qmax, 512 / F.G.NQ));
-    *untile_blocks = F.G.ntiles * ((F.G.S + 7) / 8);
     return KRY_OK;
 }
 
 int grid_multi_desc(const IluFactor &F, int64_t boff, int64_t vsJ, int64_t vsK, const int own[6],
-                    int wg0, int ub0, GridMulti &d) {
+                    int wg0, GridMulti &d) {
     if (!F.grid || F.prec != KRY_PREC_F64)
         return set_error(KRY_ERR_ARG, "grid_multi: needs an FP64 grid-tiled factor");
     d.G = F.G;
@@ -1341,12 +1417,11 @@ int grid_multi_desc(const IluFactor &F, int64_t boff, int64_t vsJ, int64_t vsK, 
     d.ok0 = own[4];
     d.ok1 = own[5];
     d.wg0 = wg0;
-    d.ub0 = ub0;
     return KRY_OK;
 }
 
 int grid_multi_apply(hipStream_t s, int bs, const GridMulti *d_desc, int ngrid, int total_wgs,
-                     int total_untile, const double *v, double *z, int *err) {
+                     const double *v, double *z, int *err) {
     {
         TimedScope t("ras_ilu_fwd", s);
         if (bs == 1)
@@ -1357,14 +1432,10 @@ int grid_multi_apply(hipStream_t s, int bs, const GridMulti *d_desc, int ngrid, 
     {
         TimedScope t("ras_ilu_bwd", s);
         if (bs == 1)
-            hipLaunchKernelGGL(k_grid_bwd_multi<1>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, err);
+            hipLaunchKernelGGL(k_grid_bwd_multi<1>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, z, err);
         else
-            hipLaunchKernelGGL(k_grid_bwd_multi<3>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, err);
+            hipLaunchKernelGGL(k_grid_bwd_multi<3>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, z, err);
     }
-    if (bs == 1)
-        hipLaunchKernelGGL(k_grid_untile_multi<1>, dim3(total_untile), dim3(256), 0, s, d_desc, ngrid, z);
-    else
-        hipLaunchKernelGGL(k_grid_untile_multi<3>, dim3(total_untile), dim3(256), 0, s, d_desc, ngrid, z);
     KRY_HIP(hipGetLastError());
     return KRY_OK;
 }
@@ -1388,15 +1459,9 @@ static int grid_pair(hipStream_t s, IluFactor &F, const TF *lt, const TF *ut, co
     }
     {
         TimedScope t(F.timer_bwd ? F.timer_bwd : sweep_timer_name(false, BS, sizeof(TF), 0), s);
-        hipLaunchKernelGGL((k_grid_bwd<BS, TF, TD, TC, TO>), dim3(wgs), dim3(GWG), 0, s, F.G, ut,
-                           dt, yt, fb, ff, F.ctr.p + F.G.NQ, F.ctr.p, err);
-    }
-    {
-        TimedScope t("ilu_grid_untile", s);
-        const int nchunk = (F.G.S + UNT_CH - 1) / UNT_CH;
-        hipLaunchKernelGGL((k_grid_untile<BS, TC, TO, ADD, TAI, TAO>),
-                           dim3(8 * ((F.G.ntiles + 7) / 8) * nchunk),
-                           dim3(256), 0, s, F.G, yt, xo, add_in, add_out);
+        hipLaunchKernelGGL((k_grid_bwd<BS, TF, TD, TC, TO, ADD, TAI, TAO>), dim3(wgs), dim3(GWG), 0,
+                           s, F.G, ut, dt, yt, fb, ff, F.ctr.p + F.G.NQ, F.ctr.p, err, xo, add_in,
+                           add_out);
     }
     KRY_HIP(hipGetLastError());
     return KRY_OK;

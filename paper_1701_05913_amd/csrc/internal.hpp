@@ -247,9 +247,8 @@ struct IluFactor {
     DBuf<double> lt64, ut64, dt64;
     DBuf<float> lt32, ut32, dt32;
     DBuf<uint16_t> lt16, ut16;
-    // tile-step-major forward result (overwritten in place by the backward
-    // result) and the published face values of both sweeps, in the
-    // compute precision
+    // tile-step-major forward result and the published face values of both
+    // sweeps, in the compute precision
     DBuf<double> yt64, ff64, fb64;
     DBuf<float> yt32, ff32, fb32;
 };
@@ -366,7 +365,7 @@ struct CprPC {
 // counters (GRID_QUEUES forward, then backward), where its cells sit in the
 // caller's vectors (offset of cell (0,0,0) in doubles, strides of j and k in
 // cells), the cells it writes back (local i, j, k ranges) and its first
-// workgroup in the sweep and untile launches.
+// workgroup in the sweep launches.
 struct GridMulti {
     GridTiles G;
     const double *lt, *ut, *dt;
@@ -374,16 +373,16 @@ struct GridMulti {
     int *ctr;
     int64_t boff, vsJ, vsK;
     int oi0, oi1, oj0, oj1, ok0, ok1;
-    int wg0, ub0;
+    int wg0;
 };
-int grid_multi_launch_size(const IluFactor &F, int *wgs, int *untile_blocks);
+int grid_multi_launch_size(const IluFactor &F, int *wgs);
 // own = {i0, i1, j0, j1, k0, k1}: the cells written back, local coordinates
 int grid_multi_desc(const IluFactor &F, int64_t boff, int64_t vsJ, int64_t vsK, const int own[6],
-                    int wg0, int ub0, GridMulti &d);
-// every grid's forward sweep of its cells of v, backward sweep, and untile
-// of its owned cells into z, in three launches on s
+                    int wg0, GridMulti &d);
+// every grid's forward sweep of its cells of v, then its backward sweep with
+// the owned cells stored into z, in two launches on s
 int grid_multi_apply(hipStream_t s, int bs, const GridMulti *d_desc, int ngrid, int total_wgs,
-                     int total_untile, const double *v, double *z, int *err);
+                     const double *v, double *z, int *err);
 
 // One grid of a multi-grid factor launch: its tiling, matrix, FP64 planes,
 // face buffer and tile counter, and its first workgroup.
@@ -429,7 +428,7 @@ struct RasPC {
     bool multi = false;                   // all subdomains grid-tiled: one launch per sweep
     DBuf<GridMulti> desc;
     DBuf<FactorMulti> fdesc;
-    int wgs = 0, untile_blocks = 0, factor_wgs = 0;
+    int wgs = 0, factor_wgs = 0;
     ~RasPC();
 };
 int ras_setup(hipStream_t s, MAT_ *A, RasPC &R, int px, int py, int pz, int overlap, int prec,

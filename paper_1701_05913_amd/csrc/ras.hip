@@ -130,7 +130,7 @@ int ras_setup(hipStream_t s, MAT_ *A, RasPC &R, int px, int py, int pz, int over
     if (R.multi) {
         std::vector<GridMulti> d(R.subs.size());
         std::vector<FactorMulti> f(R.subs.size());
-        R.wgs = R.untile_blocks = R.factor_wgs = 0;
+        R.wgs = R.factor_wgs = 0;
         int rot = 0;
         for (size_t q = 0; q < R.subs.size(); q++) {
             RasSub &S = *R.subs[q];
@@ -141,15 +141,14 @@ int ras_setup(hipStream_t s, MAT_ *A, RasPC &R, int px, int py, int pz, int over
             S.F.qrot = rot;
             KRY_TRY(grid_factor_prepare(s, S.A, S.F, S.faces, S.fctr));
             rot = (rot + S.F.G.NJ) % GRID_QUEUES;
-            int w = 0, u = 0, fw = 0;
-            KRY_TRY(grid_multi_launch_size(S.F, &w, &u));
+            int w = 0, fw = 0;
+            KRY_TRY(grid_multi_launch_size(S.F, &w));
             const int own[6] = {S.ob[0] - S.gb[0], S.ob[1] - S.gb[0], S.ob[2] - S.gb[2],
                                 S.ob[3] - S.gb[2], S.ob[4] - S.gb[4], S.ob[5] - S.gb[4]};
             const int64_t boff = (((int64_t)S.gb[4] * ny + S.gb[2]) * nx + S.gb[0]) * bs;
-            KRY_TRY(grid_multi_desc(S.F, boff, nx, (int64_t)nx * ny, own, R.wgs, R.untile_blocks, d[q]));
+            KRY_TRY(grid_multi_desc(S.F, boff, nx, (int64_t)nx * ny, own, R.wgs, d[q]));
             KRY_TRY(grid_factor_desc(S.A, S.F, S.faces, S.fctr, R.factor_wgs, f[q], &fw));
             R.wgs += w;
-            R.untile_blocks += u;
             R.factor_wgs += fw;
         }
         KRY_TRY(R.desc.alloc(d.size()));
@@ -189,8 +188,7 @@ int ras_apply(hipStream_t s, RasPC &R, const double *v, double *z, int *d_err) {
     TimedScope ts("ras_apply", s);
     const int bs = R.bs;
     if (R.multi)
-        return grid_multi_apply(s, bs, R.desc.p, (int)R.subs.size(), R.wgs, R.untile_blocks, v, z,
-                                d_err);
+        return grid_multi_apply(s, bs, R.desc.p, (int)R.subs.size(), R.wgs, v, z, d_err);
     for (auto &S : R.subs) {
         // (L_s U_s)^-1 R_s v, then the owned rows into z
         KRY_TRY(ilu_apply(s, S->F, v + (int64_t)S->lo * bs, 0, S->x.p, 0, 0, nullptr, nullptr,
