@@ -19,18 +19,16 @@
 //
 // Layouts (all step-major per tile in 64-lane planes, so every wavefront
 // access of the sweeps is one contiguous row):
-//   factors  forward block b (0: k-1, 1: j-1, 2: i-1) entry e of lane l at
-//            step t of tile T at Lt[(((T * S + t) * 3 + b) * bs^2 + e) * 64 + l];
-//            backward blocks (0: i+1, 1: j+1, 2: k+1) likewise in Ut,
-//            indexed by the backward step, diagonal-block inverses in Dt;
-//   result   yt[((T * S + t) * bs + r) * 64 + l]: the forward result of
-//            the cell of lane l at forward step t; the backward sweep
-//            reads it and overwrites it with the backward result of the
-//            same cell (its step S - 1 - t), and a last kernel copies it
-//            to the caller's vector in natural order;
-//   faces    face entry f of step t of tile T at ((T * S + t) * NF + f) * bs:
-//            f < TK the j-face cell of lane kk = f, f = TK + q the k-face
-//            cell of lane jj = q.
+//   factors  the 3 bs^2 values of a cell's forward blocks (0: k-1, 1: j-1,
+//            2: i-1) at step t of tile T are step T S + t of Lt, in the
+//            pieces of StepPlanes; backward blocks (0: i+1, 1: j+1, 2: k+1)
+//            likewise in Ut, indexed by the backward step, diagonal-block
+//            inverses in Dt;
+//   result   yt: the forward result of the cell of lane l at forward step t,
+//            read by the backward sweep at its step S - 1 - t;
+//   faces    a record of FaceRec per step of a tile: the TK j-face cells
+//            (lane kk), then the TJ k-face cells (lane jj), each part padded
+//            to whole 16-byte pieces.
 // Missing neighbours, idle lanes and steps outside the line hold zero
 // factors and zero right-hand sides.  Such lanes only ever see zeros, so
 // they compute exact zeros, and a real cell multiplies a zero block only
@@ -44,8 +42,48 @@
 namespace kry {
 
 constexpr int NLOAD = 2;       // DMA loader wavefronts per workgroup
-constexpr int GWG = 64 * 7;    // wavefronts of a sweep workgroup (roles below)
+constexpr int GWG = 64 * 8;    // wavefronts of a sweep workgroup (roles below)
 constexpr int NFACE = 40;      // >= TJ + TK for every tiling used
+
+// The N values of T that each of the 64 lanes holds in one step, as pieces of
+// up to 16 bytes per lane (piece by piece: 64 lanes of W consecutive values),
+// so that a lane reads them from LDS in 16-byte instructions: these run at
+// 128 bytes a clock against 64 for two 8-byte planes at once (14 KB: 112
+// against 228 clocks).  BF16 values are padded to whole 8-byte pieces.
+template <typename T, int N>
+struct StepPlanes {
+    static constexpr int V = 16 / (int)sizeof(T);
+    static constexpr int NP = sizeof(T) == 2 ? (N + 3) / 4 * 4 : N;
+    static constexpr int SIZE = NP * 64;                    // values per step
+    static constexpr int BYTES = SIZE * (int)sizeof(T);
+    static_assert(BYTES % 256 == 0, "whole DMA pieces");
+    // width of the piece that starts at value b: V while that many are left,
+    // then the binary parts of the rest, largest first
+    static __host__ __device__ constexpr int width(int b) {
+        const int left = NP - b;
+        return left >= V ? V : left >= 4 ? 4 : left >= 2 ? 2 : 1;
+    }
+    // place of value e of a lane within the step (no loops: folds for a
+    // constant e)
+    static __host__ __device__ constexpr int at(int e, int lane) {
+        int b = e / V * V;
+        if (width(b) < V) {
+            if (e >= b + width(b)) b += width(b);
+            if (e >= b + width(b)) b += width(b);
+        }
+        return b * 64 + lane * width(b) + (e - b);
+    }
+    template <typename TC, int B = 0>
+    static __device__ __forceinline__ void read(const char *p, int lane, TC *v);
+};
+
+// values of one step's face record: the j-face part, then the k-face part
+template <typename TC, int BS>
+struct FaceRec {
+    static constexpr int V = 16 / (int)sizeof(TC);
+    static __host__ __device__ constexpr int part(int cells) { return (cells * BS + V - 1) / V * V; }
+    static __host__ __device__ constexpr int size(int TJ, int TK) { return part(TK) + part(TJ); }
+};
 
 // a cell of zeros: the right-hand side of lanes and steps with no cell
 static __device__ __align__(16) const double zero_cell[4] = {0.0, 0.0, 0.0, 0.0};
@@ -72,14 +110,16 @@ __global__ void k_grid_pack(GridTiles G, const int *__restrict__ rowptr,
     const bool lane_ok = lane < G.TJ * G.TK && j < G.ny && k < G.nz;
     const int64_t sJ = G.nx, sK = (int64_t)G.nx * G.ny;
     const int64_t step = (int64_t)T * G.S + t;
-    double *lf = Lt + step * 3 * B2 * 64 + lane;
-    double *ub = Ut + step * 3 * B2 * 64 + lane;
-    double *db = Dt + step * B2 * 64 + lane;
+    using PF = StepPlanes<double, 3 * B2>;
+    using PD = StepPlanes<double, B2>;
+    double *lf = Lt + step * PF::SIZE;
+    double *ub = Ut + step * PF::SIZE;
+    double *db = Dt + step * PD::SIZE;
     for (int e = 0; e < 3 * B2; e++) {
-        lf[e * 64] = 0.0;
-        ub[e * 64] = 0.0;
+        lf[PF::at(e, lane)] = 0.0;
+        ub[PF::at(e, lane)] = 0.0;
     }
-    for (int e = 0; e < B2; e++) db[e * 64] = 0.0;
+    for (int e = 0; e < B2; e++) db[PD::at(e, lane)] = 0.0;
     // forward cell of this step
     const int i = t - jj - kk;
     if (lane_ok && i >= 0 && i < G.nx) {
@@ -87,7 +127,7 @@ __global__ void k_grid_pack(GridTiles G, const int *__restrict__ rowptr,
         for (int p = rowptr[c]; p < diag[c]; p++) {
             const int64_t cc = col[p];
             const int b = cc == c - sK ? 0 : (cc == c - sJ ? 1 : 2);
-            for (int e = 0; e < B2; e++) lf[(b * B2 + e) * 64] = lu[(int64_t)p * B2 + e];
+            for (int e = 0; e < B2; e++) lf[PF::at(b * B2 + e, lane)] = lu[(int64_t)p * B2 + e];
         }
     }
     // backward cell of this step
@@ -97,22 +137,37 @@ __global__ void k_grid_pack(GridTiles G, const int *__restrict__ rowptr,
         for (int p = diag[c] + 1; p < rowptr[c + 1]; p++) {
             const int64_t cc = col[p];
             const int b = cc == c + 1 ? 0 : (cc == c + sJ ? 1 : 2);
-            for (int e = 0; e < B2; e++) ub[(b * B2 + e) * 64] = lu[(int64_t)p * B2 + e];
+            for (int e = 0; e < B2; e++) ub[PF::at(b * B2 + e, lane)] = lu[(int64_t)p * B2 + e];
         }
-        for (int e = 0; e < B2; e++) db[e * 64] = uinv[c * B2 + e];
+        for (int e = 0; e < B2; e++) db[PD::at(e, lane)] = uinv[c * B2 + e];
     }
 }
 
-__global__ void k_grid_round_f32(int64_t n, const double *__restrict__ x, float *__restrict__ y) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = static_cast<float>(x[i]);
+// FP64 planes of `steps` steps rounded to FP32 or BF16 planes
+template <typename T, int N>
+__global__ __launch_bounds__(256) void k_grid_round(int64_t steps, const double *__restrict__ x,
+                                                    T *__restrict__ y) {
+    using PS = StepPlanes<double, N>;
+    using PD = StepPlanes<T, N>;
+    const int lane = threadIdx.x & 63;
+    for (int64_t s = blockIdx.x * 4 + (threadIdx.x >> 6); s < steps; s += (int64_t)gridDim.x * 4) {
+        const double *xs = x + s * PS::SIZE;
+        T *ys = y + s * PD::SIZE;
+#pragma unroll
+        for (int e = 0; e < PD::NP; e++) {
+            const float f = e < N ? static_cast<float>(xs[PS::at(e, lane)]) : 0.0f;
+            if constexpr (sizeof(T) == 2) ys[PD::at(e, lane)] = f32_to_bf16_rne(f);
+            else ys[PD::at(e, lane)] = f;
+        }
+    }
 }
-
-__global__ void k_grid_round_bf16(int64_t n, const double *__restrict__ x, uint16_t *__restrict__ y) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = f32_to_bf16_rne(static_cast<float>(x[i]));
+template <typename T>
+static void launch_round(hipStream_t s, int bs, bool diag, int64_t steps, const double *x, T *y) {
+    const dim3 g(2048), b(256);
+    if (bs == 1 && diag) hipLaunchKernelGGL((k_grid_round<T, 1>), g, b, 0, s, steps, x, y);
+    else if (bs == 1) hipLaunchKernelGGL((k_grid_round<T, 3>), g, b, 0, s, steps, x, y);
+    else if (diag) hipLaunchKernelGGL((k_grid_round<T, 9>), g, b, 0, s, steps, x, y);
+    else hipLaunchKernelGGL((k_grid_round<T, 27>), g, b, 0, s, steps, x, y);
 }
 
 template <typename T>
@@ -144,6 +199,8 @@ __device__ __forceinline__ void grid_factor_body(const GridTiles &G, const int *
                                                  double *__restrict__ Dt, double *faces, int *ctr,
                                                  int *err) {
     constexpr int B2 = BS * BS;
+    using PF = StepPlanes<double, 3 * B2>;
+    using PD = StepPlanes<double, B2>;
     const int lane = threadIdx.x;
     const int TJ = G.TJ, TK = G.TK, NF = G.NF, nx = G.nx, ny = G.ny, nz = G.nz, S = G.S;
     const int64_t sJ = nx, sK = (int64_t)nx * ny;
@@ -244,26 +301,26 @@ __device__ __forceinline__ void grid_factor_body(const GridTiles &G, const int *
                 }
                 // upper blocks (unchanged) and the inverse, at the backward step
                 const int tb = (nx - 1 - i) + (TJ - 1 - jj) + (TK - 1 - kk);
-                double *ub = Ut + (int64_t)T * S * 3 * B2 * 64 + lane;
-                double *db = Dt + (int64_t)T * S * B2 * 64 + lane;
+                double *ub = Ut + ((int64_t)T * S + tb) * PF::SIZE;
+                double *db = Dt + ((int64_t)T * S + tb) * PD::SIZE;
                 int pu = p + 1;
 #pragma unroll
                 for (int b = 0; b < 3; b++) {
                     if (!has[3 + b]) continue;
 #pragma unroll
                     for (int e = 0; e < B2; e++)
-                        ub[(((int64_t)tb * 3 + b) * B2 + e) * 64] = val[(int64_t)pu * B2 + e];
+                        ub[PF::at(b * B2 + e, lane)] = val[(int64_t)pu * B2 + e];
                     pu++;
                 }
 #pragma unroll
-                for (int e = 0; e < B2; e++) db[((int64_t)tb * B2 + e) * 64] = R[e];
+                for (int e = 0; e < B2; e++) db[PD::at(e, lane)] = R[e];
             }
             // forward blocks of this step (zeros for idle lanes and steps)
-            double *lf = Lt + (int64_t)T * S * 3 * B2 * 64 + lane;
+            double *lf = Lt + ((int64_t)T * S + t) * PF::SIZE;
 #pragma unroll
             for (int b = 0; b < 3; b++)
 #pragma unroll
-                for (int e = 0; e < B2; e++) lf[(((int64_t)t * 3 + b) * B2 + e) * 64] = L[b][e];
+                for (int e = 0; e < B2; e++) lf[PF::at(b * B2 + e, lane)] = L[b][e];
             if (fj >= 0)
 #pragma unroll
                 for (int e = 0; e < B2; e++) publish<double>(frow + ((int64_t)t * NF + fj) * B2 + e, R[e]);
@@ -335,15 +392,17 @@ static int grid_tiling(const MAT_ *A, IluFactor &F) {
     for (int q = 0; q < G.NQ; q++) G.qmax = std::max(G.qmax, qo[q + 1] - qo[q]);
     KRY_TRY(F.order.alloc(G.ntiles));
     KRY_TRY(F.tidx.alloc(G.ntiles));
-    KRY_TRY(F.qtiles.alloc(G.ntiles));
+    KRY_TRY(F.qtiles.alloc(2 * (size_t)G.ntiles));
     KRY_TRY(F.qoff.alloc(G.NQ + 1));
     KRY_HIP(hipMemcpy(F.order.p, ord.data(), sizeof(int) * G.ntiles, hipMemcpyHostToDevice));
     KRY_HIP(hipMemcpy(F.tidx.p, tid.data(), sizeof(int) * G.ntiles, hipMemcpyHostToDevice));
-    KRY_HIP(hipMemcpy(F.qtiles.p, qt.data(), sizeof(int) * G.ntiles, hipMemcpyHostToDevice));
+    for (int e = 0; e < G.ntiles; e++) qt.push_back(ord[qt[e]]);
+    KRY_HIP(hipMemcpy(F.qtiles.p, qt.data(), sizeof(int) * 2 * G.ntiles, hipMemcpyHostToDevice));
     KRY_HIP(hipMemcpy(F.qoff.p, qo.data(), sizeof(int) * (G.NQ + 1), hipMemcpyHostToDevice));
     G.order = F.order.p;
     G.tidx = F.tidx.p;
     G.qtiles = F.qtiles.p;
+    G.qjk = F.qtiles.p + G.ntiles;
     G.qoff = F.qoff.p;
     const int b2 = A->bs * A->bs;
     const int64_t steps = (int64_t)G.ntiles * G.S;
@@ -359,23 +418,28 @@ static int grid_finish(hipStream_t s, const MAT_ *A, IluFactor &F) {
     const int bs = A->bs, b2 = bs * bs;
     const int64_t steps = (int64_t)G.ntiles * G.S;
     const int64_t nlu = steps * 3 * b2 * 64, nd = steps * b2 * 64;
-    const int64_t nyt = steps * bs * 64, nf = steps * G.NF * bs;
+    const int64_t nyt = steps * bs * 64;
+    const bool f64 = F.prec == KRY_PREC_F64;
+    const int64_t nf = steps * (f64 ? (bs == 1 ? FaceRec<double, 1>::size(G.TJ, G.TK)
+                                               : FaceRec<double, 3>::size(G.TJ, G.TK))
+                                    : (bs == 1 ? FaceRec<float, 1>::size(G.TJ, G.TK)
+                                               : FaceRec<float, 3>::size(G.TJ, G.TK)));
     const dim3 blk(256);
     if (F.prec != KRY_PREC_F64) {
         KRY_TRY(F.dt32.alloc(nd));
-        hipLaunchKernelGGL(k_grid_round_f32, dim3(2048), blk, 0, s, nd, F.dt64.p, F.dt32.p);
+        launch_round(s, bs, true, steps, F.dt64.p, F.dt32.p);
         if (F.prec == KRY_PREC_F32) {
             KRY_TRY(F.lt32.alloc(nlu));
             KRY_TRY(F.ut32.alloc(nlu));
-            hipLaunchKernelGGL(k_grid_round_f32, dim3(2048), blk, 0, s, nlu, F.lt64.p, F.lt32.p);
-            hipLaunchKernelGGL(k_grid_round_f32, dim3(2048), blk, 0, s, nlu, F.ut64.p, F.ut32.p);
+            launch_round(s, bs, false, steps, F.lt64.p, F.lt32.p);
+            launch_round(s, bs, false, steps, F.ut64.p, F.ut32.p);
         } else {
-            // 128 elements of slack: the sweeps' DMA of a step's planes
-            // rounds up to 256 bytes
-            KRY_TRY(F.lt16.alloc(nlu + 128));
-            KRY_TRY(F.ut16.alloc(nlu + 128));
-            hipLaunchKernelGGL(k_grid_round_bf16, dim3(2048), blk, 0, s, nlu, F.lt64.p, F.lt16.p);
-            hipLaunchKernelGGL(k_grid_round_bf16, dim3(2048), blk, 0, s, nlu, F.ut64.p, F.ut16.p);
+            const int64_t n16 = steps * (bs == 1 ? StepPlanes<uint16_t, 3>::SIZE
+                                                 : StepPlanes<uint16_t, 27>::SIZE);
+            KRY_TRY(F.lt16.alloc(n16));
+            KRY_TRY(F.ut16.alloc(n16));
+            launch_round(s, bs, false, steps, F.lt64.p, F.lt16.p);
+            launch_round(s, bs, false, steps, F.ut64.p, F.ut16.p);
         }
         KRY_HIP(hipGetLastError());
         KRY_HIP(hipStreamSynchronize(s));
@@ -515,8 +579,8 @@ int ilu_grid_factor_setup(hipStream_t s, const MAT_ *A, const double *d_val, Ilu
 //   wave 0            compute: consumes one hyperplane step at a time from
 //                     LDS and leaves its result in LDS; it touches no global
 //                     memory and waits for nothing but its operands
-//   wave 1            boundary: polls the face buffers of the two upstream
-//                     tiles and stages the values in LDS
+//   waves 1, 7        boundary: poll the face buffers of the two upstream
+//                     tiles and stage the values in LDS, steps in turn
 //   waves 2, 3        loaders: copy each step's factor planes (and the
 //                     forward's right-hand side, the backward's diagonal
 //                     inverses and forward result) straight from global
@@ -530,9 +594,10 @@ int ilu_grid_factor_setup(hipStream_t s, const MAT_ *A, const double *d_val, Ilu
 //   wave 5            publisher: takes each step's result from LDS and
 //                     publishes the face cells; in the forward sweep it
 //                     also stores the tile-step rows the backward sweep reads
-//   wave 6            backward only, writer: takes the results of a few
-//                     steps at a time from LDS and stores them to the
-//                     caller's vector in natural order, with its epilogue
+//   wave 6            forward: copies the right-hand side into its LDS ring;
+//                     backward: writer, takes the results of a few steps at
+//                     a time from LDS and stores them to the caller's vector
+//                     in natural order, with its epilogue
 //
 // Result ring.  Slot t of YRing holds what step t reads: the tile's results
 // of step t - 1 in the interior of a (TK + 1) x (TJ + 1) array of cells, and
@@ -551,10 +616,10 @@ int ilu_grid_factor_setup(hipStream_t s, const MAT_ *A, const double *d_val, Ilu
 // execute in order, so a progress word written after the reads (or writes)
 // it stands for needs no wait in between.
 // ---------------------------------------------------------------------------
-// ring slots for steps of SB bytes (120 KiB of ring, 2 to 8 slots)
-template <int SB>
+// ring slots for steps of SB bytes in ROOM bytes of LDS (2 to 8)
+template <int SB, int ROOM>
 constexpr int ring_slots() {
-    return (122880 / SB) > 8 ? 8 : (122880 / SB) < 2 ? 2 : (122880 / SB);
+    return (ROOM / SB) > 8 ? 8 : (ROOM / SB) < 2 ? 2 : (ROOM / SB);
 }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -565,13 +630,13 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // src + o + w l to dst + o + w l (w its width; the LDS address of a lane is
 // the wave-uniform base plus w l).  Every instruction runs on the whole
 // wavefront: the LDS base of an instruction must be wave-uniform, so none
-// sits under a lane-dependent branch.  A block of BF16 planes with an odd
-// plane count ends 128 bytes short of a multiple of 256: its DMA rounds up
-// (pad256), reading 128 bytes past the block (the planes are allocated with
-// that much slack) into a ring region sized for the rounded length.
-constexpr int pad256(int bytes) { return (bytes + 255) / 256 * 256; }
+// sits under a lane-dependent branch.  NT: non-temporal loads, for factors
+// that stream through once per sweep (a full-chip read of 2 GB runs at 7.3
+// TB/s with them, 5.9 without); the scalar factors of CPR's pressure stage,
+// swept several times in a row and a ninth of the size, are better left in
+// the caches (64^3, FP64: 68 us a sweep against 76 with non-temporal loads).
 constexpr int dma_count(int bytes) { return bytes / 1024 + (bytes % 1024) / 256; }
-template <int BYTES>
+template <int BYTES, bool NT>
 __device__ __forceinline__ void dma_block(const void *src, char *dst, int lane) {
     static_assert(BYTES % 256 == 0, "256-byte pieces");
     const char *g = static_cast<const char *>(src);
@@ -579,11 +644,11 @@ __device__ __forceinline__ void dma_block(const void *src, char *dst, int lane) 
 #pragma unroll
     for (int q = 0; q < N16; q++)
         __builtin_amdgcn_global_load_lds(g + q * 1024 + lane * 16, (lds_void_t *)(dst + q * 1024),
-                                         16, 0, 0);
+                                         16, 0, NT ? 2 : 0);
 #pragma unroll
     for (int q = 0; q < N4; q++) {
         const int o = N16 * 1024 + q * 256;
-        __builtin_amdgcn_global_load_lds(g + o + lane * 4, (lds_void_t *)(dst + o), 4, 0, 0);
+        __builtin_amdgcn_global_load_lds(g + o + lane * 4, (lds_void_t *)(dst + o), 4, 0, NT ? 2 : 0);
     }
 }
 // W bytes per lane (4 or 12) from each lane's own address into dst + S l,
@@ -611,46 +676,81 @@ __device__ __forceinline__ TC cvt(TF v) { return static_cast<TC>(v); }
 template <>
 __device__ __forceinline__ float cvt<float, uint16_t>(uint16_t v) { return bf16_to_f32(v); }
 
-// A cell's right-hand side (BS values of TIN, CB bytes) gathered by DMA in
-// pieces of W bytes per lane: piece p of lane l at p 64 LS + l LS (LS the
-// lane stride of the piece).  Component r of lane `lane` from those pieces.
-template <typename TIN, int BS>
-struct RhsStage {
-    static constexpr int CB = BS * (int)sizeof(TIN);
-    static constexpr int W = CB % 12 == 0 ? 12 : 4;
-    static constexpr int LS = W == 12 ? 16 : 4;
-    static constexpr int NP = CB / W;            // DMA instructions per step
-    static constexpr int BYTES = NP * 64 * LS;
-    // the lane's BS values
-    template <typename TC>
-    static __device__ __forceinline__ void read(const char *rb, int lane, TC *v) {
-        uint32_t d[CB / 4 + 2];
+template <typename T, int N>
+template <typename TC, int B>
+__device__ __forceinline__ void StepPlanes<T, N>::read(const char *p, int lane, TC *v) {
+    if constexpr (B < NP) {
+        constexpr int W = width(B);
+        const T *q = reinterpret_cast<const T *>(p) + B * 64 + lane * W;
+        if constexpr (W == 1) {
+            v[B] = cvt<TC, T>(*q);
+        } else {
+            typedef T vec_t __attribute__((ext_vector_type(W)));
+            const vec_t u = *reinterpret_cast<const vec_t *>(q);
 #pragma unroll
-        for (int q = 0; q < NP; q++) {
-            const char *p = rb + q * 64 * LS + lane * LS;
-            if constexpr (W == 12) {   // the fourth dword of a piece is never written
-                const uint4 u = *reinterpret_cast<const uint4 *>(p);
-                d[3 * q] = u.x;
-                d[3 * q + 1] = u.y;
-                d[3 * q + 2] = u.z;
-            } else {
-                d[q] = *reinterpret_cast<const uint32_t *>(p);
-            }
+            for (int i = 0; i < W; i++)
+                if (B + i < N) v[B + i] = cvt<TC, T>(u[i]);
         }
-#pragma unroll
-        for (int r = 0; r < BS; r++) {
-            if constexpr (sizeof(TIN) == 8) {
-                const uint64_t u = (static_cast<uint64_t>(d[2 * r + 1]) << 32) | d[2 * r];
-                v[r] = static_cast<TC>(__longlong_as_double(static_cast<long long>(u)));
-            } else {
-                v[r] = static_cast<TC>(__uint_as_float(d[r]));
-            }
+        read<TC, B + W>(p, lane, v);
+    }
+}
+
+// The right-hand side of the forward sweep: a ring of RS_STEPS steps in LDS,
+// filled RS_CH steps at a time by a wavefront of its own.  At a step the 64
+// lanes read 64 cells of 64 lines far apart in memory; taking RS_CH steps at
+// once lets one DMA instruction copy runs of RS_CH consecutive cells of a few
+// lines instead of one cell of each line (FP64 blocks: 8 lines of 96 bytes;
+// the gather of single cells cost as many memory requests as the factor
+// planes, 12% of the sweep at 64^3 and 9% at 256 x 256 x 128).
+// A cell is UH units of UB bytes in LDS: 3 doubles two 12-byte pieces (the
+// DMA keeps 16 bytes per lane for those), 3 floats one; a double of BS = 1
+// two dwords side by side, a float one dword.  Block q of a chunk (one DMA
+// instruction, UPI units) holds the lines q LPB .. q LPB + LPB - 1, UL units
+// of each in turn (neighbouring lanes copy neighbouring memory; with a
+// line's units spread over the block no requests merge and the ring fills
+// too slowly).  A line's units are permuted by XOR with `twist`, which puts
+// the units that a wavefront reads together (one of every line) on distinct
+// banks.  Cells outside the line are copied from a cell of zeros.
+constexpr int RS_CH = 4, RS_STEPS = 16;
+template <typename TIN, int BS>
+struct RhsRing {
+    static constexpr int CB = BS * (int)sizeof(TIN);        // bytes of a cell
+    static constexpr int UH = CB == 24 ? 2 : 1;
+    static constexpr int UB = CB % 12 == 0 ? 16 : CB;       // bytes of a unit in LDS
+    static constexpr int LPU = UB == 8 ? 2 : 1;             // DMA lanes per unit
+    static constexpr int UPI = 64 / LPU;
+    static constexpr int LPB = UPI / (RS_CH * UH);
+    static constexpr int UL = RS_CH * UH;                   // units of a line
+    static constexpr int NI = 64 / LPB;                     // DMA instructions per chunk
+    static constexpr int IB = UPI * UB, CHB = NI * IB, BYTES = (RS_STEPS / RS_CH) * CHB;
+    static __device__ __forceinline__ int twist(int q, int r) {   // line r of block q
+        return (UB == 16 ? (UL == 8 ? r : r >> 2) : q) & (UL - 1);
+    }
+    static __device__ __forceinline__ int unit(int lane, int s, int h) {
+        const int q = lane / LPB, r = lane % LPB;
+        return q * IB + (r * UL + ((s * UH + h) ^ twist(q, r))) * UB;
+    }
+    // the lane's cell of step t, s = t % RS_CH
+    template <typename TC>
+    static __device__ __forceinline__ void read(const char *ring, int t, int s, int lane, TC *v) {
+        const char *c = ring + ((t / RS_CH) & (RS_STEPS / RS_CH - 1)) * CHB;
+        if constexpr (CB == 24) {   // the fourth dword of a piece is never written
+            const uint4 a = *reinterpret_cast<const uint4 *>(c + unit(lane, s, 0));
+            const uint4 b = *reinterpret_cast<const uint4 *>(c + unit(lane, s, 1));
+            v[0] = static_cast<TC>(join(a.x, a.y));
+            v[1] = static_cast<TC>(join(a.z, b.x));
+            v[2] = static_cast<TC>(join(b.y, b.z));
+        } else if constexpr (CB == 12) {
+            const uint4 a = *reinterpret_cast<const uint4 *>(c + unit(lane, s, 0));
+            v[0] = static_cast<TC>(__uint_as_float(a.x));
+            v[1] = static_cast<TC>(__uint_as_float(a.y));
+            v[2] = static_cast<TC>(__uint_as_float(a.z));
+        } else {
+            v[0] = static_cast<TC>(*reinterpret_cast<const TIN *>(c + unit(lane, s, 0)));
         }
     }
-    static __device__ __forceinline__ void load(const TIN *cell, char *dst) {
-#pragma unroll
-        for (int q = 0; q < NP; q++)
-            dma_piece<W>(reinterpret_cast<const char *>(cell) + q * W, dst + q * 64 * LS);
+    static __device__ __forceinline__ double join(uint32_t lo, uint32_t hi) {
+        return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
     }
 };
 
@@ -686,6 +786,7 @@ __device__ __forceinline__ int progress_get(const Progress &p) {
 // wait until the progress word reaches v (it is kept by a wavefront of this
 // workgroup that waits only on earlier steps)
 __device__ __forceinline__ void progress_wait(const Progress &p, int v, int &seen, int *err) {
+#pragma clang loop unroll(disable)
     for (uint32_t it = 0; seen < v; ++it) {
         seen = progress_get(p);
         if (it > 4 * SPIN_LIMIT) {
@@ -710,6 +811,12 @@ struct YRing {
     static constexpr int WB = BS == 3 && sizeof(TC) == 8 ? 8 : 0;
     static constexpr int BYTES = DY * CELLS * (WA + WB);
     static __device__ __forceinline__ int slot(int t) { return t & (DY - 1); }
+    // byte offset of value r of a cell in slot 0, and the slots' stride
+    static __device__ __forceinline__ void place(int cell, int r, int &off, int &stride) {
+        const bool second = WB != 0 && r == 2;
+        off = second ? DY * CELLS * WA + cell * WB : cell * WA + r * (int)sizeof(TC);
+        stride = second ? CELLS * WB : CELLS * WA;
+    }
     static __device__ __forceinline__ void load(const char *ring, int s, int cell, TC (&v)[BS]) {
         const char *p = ring + s * (CELLS * WA) + cell * WA;
         if constexpr (BS == 1) {
@@ -754,12 +861,14 @@ __device__ __forceinline__ unsigned long long step_flag_get(const StepFlag &f) {
 __device__ __forceinline__ void step_wait(unsigned long long pre, const StepFlag &f, int st, int *err) {
     const unsigned long long want =
         (static_cast<unsigned long long>(static_cast<unsigned>(st + 1)) << 32) | static_cast<unsigned>(st);
-    if (__builtin_amdgcn_ballot_w64(pre != want) != 0)
+    if (__builtin_amdgcn_ballot_w64(pre != want) != 0) {
+#pragma clang loop unroll(disable)
         for (uint32_t it = 0; __builtin_amdgcn_ballot_w64(step_flag_get(f) != want) != 0; ++it)
             if (it > 4 * SPIN_LIMIT) {
                 __hip_atomic_store(err, ERR_STALL_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
             }
+    }
     asm volatile("" : : : "memory");
 }
 
@@ -770,14 +879,17 @@ __device__ __forceinline__ void step_wait(unsigned long long pre, const StepFlag
 // planes are read during the step before, those of step 0 before step 0).
 // The wait counts assume no other vector memory operation of the wavefront
 // is outstanding when the loop starts.
+// A step is stamped only when `rhs_p` (where given) shows its right-hand side
+// staged too.
 template <int D, int P, int K, int DY, typename F>
 __device__ __forceinline__ void loader_loop(int w, int S, int base, const Progress &done_p,
-                                            StepFlag (&fl)[DY], int lane, int *err, F &&issue) {
+                                            const Progress *rhs_p, StepFlag (&fl)[DY], int lane,
+                                            int *err, F &&issue) {
     // the wave's vector memory counter holds at most 63 outstanding
     // instructions: every DMA of the K steps in flight must fit in it
     static_assert(K >= 1 && K <= 4 && K * P <= 63, "in-flight DMA within the vmcnt range");
     static_assert(D < DY, "the stamps of the steps in the ring are distinct slots");
-    int next = w, done = w;
+    int next = w, done = w, rhs = base;
     uint32_t idle = 0;
     wait_vm<0>();
     while (done < S) {
@@ -803,6 +915,15 @@ __device__ __forceinline__ void loader_loop(int w, int S, int base, const Progre
         if constexpr (K >= 3) { if (inflight == 3) wait_vm<(K >= 3 ? 2 * P : 0)>(); }
         if constexpr (K >= 2) { if (inflight == 2) wait_vm<(K >= 2 ? P : 0)>(); }
         if (inflight == 1) wait_vm<0>();
+        if (rhs_p)
+#pragma clang loop unroll(disable)
+            for (uint32_t it = 0; rhs <= base + done; ++it) {
+                rhs = __builtin_amdgcn_readfirstlane(lds_flag_get(rhs_p->w));
+                if (it > 4 * SPIN_LIMIT) {
+                    __hip_atomic_store(err, ERR_STALL_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+            }
         if (lane == 0) lds_flag_put(&fl[(done + DY - 1) & (DY - 1)].h[1], base + done);
         done += NLOAD;
     }
@@ -820,93 +941,165 @@ __device__ __forceinline__ void block_sub(TC (&acc)[BS], const TC (&v)[NV], int 
         for (int c = 0; c < BS; c++) acc[r] -= v[b * BS * BS + r * BS + c] * y[c];
 }
 
-// Boundary role.  Lane f of the NF face lanes serves face entry f; `src`
-// points at that entry of the upstream tile at the step that produces the
-// value for this tile's step 0 (nullptr when the upstream tile or the
-// lane's line does not exist), consecutive steps are NF * BS values apart.
-// The face cell of step t lies at offset t - lag along the lane's line.
-//
-// The wave is cut into G = 64 / NF groups of NF lanes; group g stages
-// steps g, g + G, g + 2G, ... .  Every round probes each group's current
-// step: its first lane (a j-face entry, from the J - 1 tile) and its last
-// lane (a k-face entry, from the K - 1 tile) read the last word of their
-// entry.  Only a group whose probes both show published values reads its
-// NF entries in full; a group whose NF cells are all published (and whose
-// ring slot has been consumed) stages them and moves on, the others probe
-// again.  A waiting round thus costs two words per group instead of the
-// NF * BS values of a full read: these agent-scope loads bypass the L2,
-// and with every tile's boundary wavefront polling, full reads cost 11 to
-// 14% of the sweep time at 256 x 256 x 128.
-// `cell` is the lane's halo cell of a ring slot; step t may be staged once
-// `prog` (and `prog2` where it is given) shows that slot t's results of
-// step t - DY - 1 have been taken from the ring, which also means that the
-// compute wavefront is past step t - DY.
-template <typename TC, int BS>
-__device__ void boundary_role(int S, int nx, int base, int lane, int NF, const TC *src, int lag,
-                              char *yring, int cell, StepFlag (&fl)[YRing<TC, BS>::DY],
-                              const Progress &prog, const Progress *prog2, int *err) {
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes that see other workgroups' published values (device scope), the
+// load waited for in the same statement
+__device__ __forceinline__ u32x4 load_published(const void *a) {
+    u32x4 r;
+    asm volatile("global_load_dwordx4 %0, %1, off sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(r)
+                 : "v"(a)
+                 : "memory");
+    return r;
+}
+__device__ __forceinline__ void store_published(void *a, u32x4 v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(a), "v"(v) : "memory");
+}
+
+// What the publisher's lane u holds of a step's face record: 16 bytes of it
+// (lanes past the record hold none), gathered from the result ring's cells.
+// One store instruction publishes both faces, whole lines at a time: stores
+// of single values by the lanes that own the cells touched every line three
+// times while the neighbours were polling it.
+template <typename TC, int BS, bool REV>
+struct FacePublisher {
     using U = typename Bits<TC>::U;
     using YR = YRing<TC, BS>;
-    const U *q = reinterpret_cast<const U *>(src);
-    const int G = (64 / NF) < YR::DY ? (64 / NF) : YR::DY;
-    const int f = lane % NF, g = lane / NF;
-    const bool lane_ok = g < G;
-    const uint64_t gmask = (NF >= 64 ? ~0ull : ((1ull << NF) - 1ull)) << (lane_ok ? g * NF : 0);
-    const int64_t stride = (int64_t)NF * BS;
-    int ts = g;
+    using FR = FaceRec<TC, BS>;
+    int off[FR::V], stride[FR::V];
+    bool mine;
+    __device__ __forceinline__ FacePublisher(int TJ, int TK, int lane) {
+        const int PJ = FR::part(TK);
+        mine = lane * FR::V < FR::size(TJ, TK);
+        const bool isj = lane * FR::V < PJ;
+        const int e0 = isj ? lane * FR::V : lane * FR::V - PJ;
+#pragma unroll
+        for (int i = 0; i < FR::V; i++) {
+            const int c = (e0 + i) / BS, r = e0 + i - c * BS;
+            int cell = YR::CELLS - 1;   // padding: any value will do
+            if (mine && isj && c < TK) cell = (REV ? TK - c : c + 1) * (TJ + 1) + TJ;
+            if (mine && !isj && c < TJ) cell = TK * (TJ + 1) + (REV ? TJ - c : c + 1);
+            YR::place(cell, r, off[i], stride[i]);
+        }
+    }
+    // this lane's piece of the results in ring slot s
+    __device__ __forceinline__ u32x4 gather(const char *ring, int s) const {
+        U w[FR::V];
+#pragma unroll
+        for (int i = 0; i < FR::V; i++) w[i] = *reinterpret_cast<const U *>(ring + off[i] + s * stride[i]);
+#pragma unroll
+        for (int i = 0; i < FR::V; i++)
+            if (w[i] == Bits<TC>::sentinel) w[i] = Bits<TC>::qnan;
+        u32x4 v;
+        __builtin_memcpy(&v, w, 16);
+        return v;
+    }
+};
+
+// Boundary role, on two wavefronts (`part` 0 and 1).  A step's halo is a
+// record part of the j-upstream tile and one of the k-upstream tile, read as
+// 16-byte pieces, one per lane: n lanes hold a step, a wavefront GL = 64 / n
+// steps (FP64 blocks on 8 x 8 tiles: 24 lanes, 2 steps), and the wavefronts
+// take GL steps in turn.  The values validate themselves (sentinel =
+// unwritten); a group of n lanes whose pieces are all written, and whose ring
+// slot has been taken, stages its step and moves on.
+//   A round is one memory round trip (0.6 us) and under 100 instructions, so
+// a halo arrives one trip after its publication, and the wavefronts' rounds
+// overlap.  A tile runs at its producers' pace and keeps whatever it once
+// fell behind, so the rounds must keep up with the compute wavefront from the
+// first step on: one wavefront with twice the loads and more bookkeeping
+// took 1.35 us for four steps, and 4 us a tile hop.  Two steps a round also
+// for the smaller records of FP32 and of BS = 1: with five or eight the
+// missing ones are asked for too often (64^3 FP32 forward 86 against 77 us,
+// BS = 1 66 against 56).
+// `prog` (and `prog2` where it is given) show that slot t's results of step
+// t - DY - 1 have been taken from the ring, which also means that the
+// compute wavefront is past step t - DY.
+template <typename TC, int BS, bool REV>
+__device__ __forceinline__ void boundary_role(const GridTiles &G, int JK, int base, int lane, int part,
+                                              const TC *faces, char *yring,
+                                              StepFlag (&fl)[YRing<TC, BS>::DY], const Progress &prog,
+                                              const Progress *prog2, int *err) {
+    using U = typename Bits<TC>::U;
+    using YR = YRing<TC, BS>;
+    using FR = FaceRec<TC, BS>;
+    constexpr int V = FR::V;
+    const int TJ = G.TJ, TK = G.TK, S = G.S;
+    const int PJ = FR::part(TK), FV = FR::size(TJ, TK);
+    const int n = FV / V;                                   // lanes per step, at most 51
+    const int GL = min(64 / n, 2);                 // steps per round
+    const int g = lane / n, u = lane - g * n;
+    const bool lane_ok = g < GL;
+    const bool isj = u * V < PJ;
+    const int e0 = isj ? u * V : u * V - PJ;                // first value within the part
+    const int J = (JK & 0xffff) + (isj ? (REV ? 1 : -1) : 0);
+    const int K = (JK >> 16) + (isj ? 0 : (REV ? 1 : -1));
+    const int sh = isj ? TJ - 1 : TK - 1;                   // producer step - this tile's step
+    const bool have = lane_ok && J >= 0 && J < G.NJ && K >= 0 && K < G.NK;
+    // where the lane's values go in a ring slot: value i at off[i] + slot
+    // stride[i]; padding goes to a cell that nobody reads
+    int off[V], stride[V];
+    bool real[V];
+#pragma unroll
+    for (int i = 0; i < V; i++) {
+        const int e = e0 + i, c = e / BS, r = e - c * BS;
+        real[i] = c < (isj ? TK : TJ);
+        const int cell = !real[i] ? YR::CELLS - 1
+                         : isj    ? (REV ? TK - c : c + 1) * (TJ + 1)
+                                  : (REV ? TJ - c : c + 1);
+        YR::place(cell, r, off[i], stride[i]);
+    }
+    const uint64_t gmask = lane_ok ? ((1ull << n) - 1ull) << (g * n) : ~0ull;
+    // this lane's next step; steps from `lim` on have no producer step (their
+    // halo is zero)
+    int ts = lane_ok ? part * GL + g : S;
+    int lim = have ? S - sh : 0;
+    const TC *sp = have ? faces + ((int64_t)G.tidx[J * G.NK + K] * S + sh + ts) * FV + u * V : faces;
+    const int64_t hop = have ? (int64_t)2 * GL * FV : 0;
+    U fill = 0;
     bool failed = false;
     uint32_t idle = 0;
-    for (;;) {
-        const bool active = lane_ok && ts < S;
-        if (__ballot(active) == 0) break;
-        bool ready = active;
-        TC vals[BS];
+    while (__ballot(ts < S) != 0) {
+        const int taken = min(progress_get(prog), prog2 ? progress_get(*prog2) : INT32_MAX);
+        const bool act = ts < S;
+        U w[V];
 #pragma unroll
-        for (int r = 0; r < BS; r++) vals[r] = TC(0);
-        bool pr = true;
-        if (active && (f == 0 || f == NF - 1) && !failed) {
-            const int off = ts - lag;
-            if (q != nullptr && off >= 0 && off < nx)
-                pr = __hip_atomic_load(const_cast<U *>(q) + ts * stride + (BS - 1),
-                                       __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT) != Bits<TC>::sentinel;
+        for (int i = 0; i < V; i++) w[i] = fill;
+        if (act && ts < lim) {
+            const u32x4 raw = load_published(sp);
+            __builtin_memcpy(w, &raw, 16);
         }
-        const uint64_t pb = __ballot(pr);
-        const bool probed = lane_ok && ((pb >> (g * NF)) & 1ull) && ((pb >> (g * NF + NF - 1)) & 1ull);
-        if (active && !probed) ready = false;
-        if (active && probed) {
-            const int off = ts - lag;
-            if (q != nullptr && off >= 0 && off < nx) {
+        bool ready = act && taken >= base + ts - YR::DY + 1;
 #pragma unroll
-                for (int r = 0; r < BS; r++) {
-                    const U u = failed ? Bits<TC>::qnan
-                                       : __hip_atomic_load(const_cast<U *>(q) + ts * stride + r,
-                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    vals[r] = Bits<TC>::from(u);
-                    ready = ready && u != Bits<TC>::sentinel;
-                }
+        for (int i = 0; i < V; i++) ready = ready && !(real[i] && w[i] == Bits<TC>::sentinel);
+        const bool go = (__ballot(ready) & gmask) == gmask;
+        if (go) {
+            const int s = YR::slot(ts);
+#pragma unroll
+            for (int i = 0; i < V; i++)
+                *reinterpret_cast<U *>(yring + off[i] + s * stride[i]) = w[i];
+            // LDS operations execute in order: the stamp follows the values
+            asm volatile("" : : : "memory");
+            if (u == 0) {
+                const unsigned a = (unsigned)(size_t)((__attribute__((address_space(3))) int *)&fl[s].h[0]);
+                asm volatile("ds_write_b32 %0, %1" : : "v"(a), "v"(base + ts) : "memory");
             }
-            const int need = base + ts - YR::DY + 1;
-            ready = ready && lds_get(const_cast<int *>(prog.w)) >= need &&
-                    (!prog2 || lds_get(const_cast<int *>(prog2->w)) >= need);
+            ts += 2 * GL;
+            sp += hop;
         }
-        const bool go = active && (__ballot(ready) & gmask) == gmask;
-        lds_acquire();
-        if (go) YR::store(yring, YR::slot(ts), cell, vals);
-        lds_release();
-        if (go && f == 0) lds_put(&fl[YR::slot(ts)].h[0], base + ts);
-        if (go) ts += G;
         if (__ballot(go) != 0) {
             idle = 0;
             continue;
         }
-        // no group could stage this round
         if ((++idle & 63u) == 0u && !failed) {
             const int e = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (e != 0 || idle > SPIN_LIMIT) {
                 if (e == 0 && lane == 0)
                     __hip_atomic_store(err, ERR_STALL_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 failed = true;   // stage NaNs from now on so the compute wave drains
+                fill = Bits<TC>::qnan;
+                lim = 0;
             }
         }
         __builtin_amdgcn_s_sleep(1);
@@ -920,14 +1113,18 @@ __device__ void boundary_role(int S, int nx, int base, int lane, int NF, const T
 // backward sweep, last to first; -1 when the queue is empty.  Within a
 // queue the tiles come in dependency order and every queue is served by at
 // least one workgroup, so every taken tile's producers are running.
-__device__ __forceinline__ int next_tile(const GridTiles &G, int *ctr, int *tile, bool rev,
-                                         int blk) {
+struct Tile {
+    int T, JK;   // tile, J | K << 16
+};
+__device__ __forceinline__ Tile next_tile(const GridTiles &G, int *ctr, Tile *tile, bool rev,
+                                          int blk) {
     __syncthreads();
     if (threadIdx.x == 0) {
         const int q = blk % G.NQ;
         const int i = atomicAdd(ctr + q, 1);
-        const int len = G.qoff[q + 1] - G.qoff[q];
-        *tile = i < len ? G.qtiles[G.qoff[q] + (rev ? len - 1 - i : i)] : -1;
+        const int q0 = G.qoff[q], len = G.qoff[q + 1] - q0;
+        const int e = q0 + (rev ? len - 1 - i : i);
+        *tile = i < len ? Tile{G.qtiles[e], G.qjk[e]} : Tile{-1, 0};
     }
     __syncthreads();
     return *tile;
@@ -943,41 +1140,43 @@ __device__ __forceinline__ void grid_fwd_body(const GridTiles &G, const TF *__re
                                               const TIN *__restrict__ b, TC *yt, TC *ff, TC *fb,
                                               int *ctr, int *other_ctr, int *err, int blk,
                                               int64_t vsJ, int64_t vsK) {
-    constexpr int B2 = BS * BS, NM = 3 * B2, NV = NM + BS;
-    // ring step: NM factor planes of TF, then the step's right-hand-side
-    // cells as gathered by the DMA pieces of RhsStage
-    using RS = RhsStage<TIN, BS>;
+    constexpr int NM = 3 * BS * BS, NV = NM + BS;
+    using PL = StepPlanes<TF, NM>;
+    using RR = RhsRing<TIN, BS>;
     using YR = YRing<TC, BS>;
+    using FR = FaceRec<TC, BS>;
     constexpr int DY = YR::DY;
-    constexpr int PB = pad256(NM * 64 * (int)sizeof(TF));
-    constexpr int SB = (PB + RS::BYTES + 15) / 16 * 16;
-    constexpr int D = ring_slots<SB>();
-    constexpr int P = dma_count(PB) + RS::NP;                  // DMA instructions per step
-    constexpr int K = (D / NLOAD) < (63 / P) ? (D / NLOAD) : (63 / P);
+    constexpr int SB = PL::BYTES;
+    constexpr int D = ring_slots<SB, 120000 - RR::BYTES>();
+    constexpr int P = dma_count(SB);                           // DMA instructions per step
+    constexpr int KM = (D / NLOAD) < (63 / P) ? (D / NLOAD) : (63 / P), K = KM < 4 ? KM : 4;
     __shared__ __attribute__((aligned(16))) char ringb[D * SB];
     __shared__ __attribute__((aligned(16))) char yring[YR::BYTES];
+    __shared__ __attribute__((aligned(16))) char rring[RR::BYTES];
     __shared__ StepFlag fl[DY];
-    __shared__ Progress done_p, pub_p;   // steps computed, steps taken by the publisher
-    __shared__ int tile;
+    // steps computed, taken by the publisher, with a staged right-hand side
+    __shared__ Progress done_p, pub_p, rhs_p;
+    __shared__ Tile tile;
     // wave-uniform role index (an SGPR), so the roles are real branches
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (blk == 0 && (int)threadIdx.x < G.NQ) other_ctr[threadIdx.x] = 0;
     if (threadIdx.x < DY) fl[threadIdx.x].h[0] = fl[threadIdx.x].h[1] = -1;
-    if (threadIdx.x < 64) done_p.w[threadIdx.x] = pub_p.w[threadIdx.x] = 0;
-    const int TJ = G.TJ, TK = G.TK, NF = G.NF, nx = G.nx, S = G.S;
+    if (threadIdx.x < 64)
+        done_p.w[threadIdx.x] = pub_p.w[threadIdx.x] = rhs_p.w[threadIdx.x] = 0;
+    const int TJ = G.TJ, TK = G.TK, nx = G.nx, S = G.S;
     const int jj = lane % TJ, kk = lane / TJ;
     const int own = (kk + 1) * (TJ + 1) + jj + 1;   // this lane's cell of a ring slot
     if (wave == 0) {
         // ---- compute ----
-        auto read_step = [&](const char *sl, TC (&v)[NV]) {
-            const TF *pl = reinterpret_cast<const TF *>(sl);
-#pragma unroll
-            for (int e = 0; e < NM; e++) v[e] = cvt<TC, TF>(pl[e * 64 + lane]);
-            RS::template read<TC>(sl + PB, lane, v + NM);
+        // planes and right-hand side of step t, s = t % RS_CH
+        auto read_step = [&](const char *sl, int t, int s, TC (&v)[NV]) {
+            PL::template read<TC>(sl, lane, v);
+            RR::template read<TC>(rring, t, s, lane, v + NM);
         };
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, false, blk);
+            const Tile tl = next_tile(G, ctr, &tile, false, blk);
+            const int T = tl.T;
             if (T < 0) break;
             TC yp[BS];
 #pragma unroll
@@ -987,14 +1186,15 @@ __device__ __forceinline__ void grid_fwd_body(const GridTiles &G, const TF *__re
             unsigned long long pre = ~0ull;   // flag of the next step, read one step early
             int slot = D > 1 ? SB : 0;        // byte offset of step t + 1's planes
             // step t computes with the planes in vc and reads the planes of
-            // step t + 1 into vn; the two arrays swap roles every step
-            auto step = [&](int t, const TC (&vc)[NV], TC (&vn)[NV]) {
+            // step t + 1 into vn; the two arrays swap roles every step.
+            // s1 = (t + 1) % RS_CH (the steps are unrolled by RS_CH)
+            auto step = [&](int t, int s1, const TC (&vc)[NV], TC (&vn)[NV]) {
                 const int st = base + t;
                 step_wait(pre, fl[YR::slot(t)], st, err);
                 TC yj[BS], yk[BS];
                 YR::load(yring, YR::slot(t), own - (TJ + 1), yk);
                 YR::load(yring, YR::slot(t), own - 1, yj);
-                read_step(ringb + slot, vn);
+                read_step(ringb + slot, t + 1, s1, vn);
                 slot = slot == (D - 1) * SB ? 0 : slot + SB;
                 pre = step_flag_get(fl[YR::slot(t + 1)]);
                 TC acc[BS];
@@ -1010,88 +1210,137 @@ __device__ __forceinline__ void grid_fwd_body(const GridTiles &G, const TF *__re
             };
             TC va[NV], vb[NV];
             lds_wait_eq(&fl[DY - 1].h[1], base, err);
-            read_step(ringb, va);
+            read_step(ringb, 0, 0, va);
+            static_assert(RS_CH == 4, "the step loop is unrolled by RS_CH");
             int t = 0;
-            for (; t + 1 < S; t += 2) {
-                step(t, va, vb);
-                step(t + 1, vb, va);
+            for (; t + 3 < S; t += 4) {
+                step(t, 1, va, vb);
+                step(t + 1, 2, vb, va);
+                step(t + 2, 3, va, vb);
+                step(t + 3, 0, vb, va);
             }
-            if (t < S) step(t, va, vb);
+            if (t < S) step(t, 1, va, vb);
+            if (t + 1 < S) step(t + 1, 2, vb, va);
+            if (t + 2 < S) step(t + 2, 3, va, vb);
         }
-    } else if (wave == 1) {
+    } else if (wave == 1 || wave == 7) {
         // ---- boundary: faces of tiles (J-1, K) and (J, K-1) ----
-        const int f = lane % NF;
-        const int cell = f < TK ? (f + 1) * (TJ + 1) : f - TK + 1;
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, false, blk);
+            const Tile tl = next_tile(G, ctr, &tile, false, blk);
+            const int T = tl.T;
             if (T < 0) break;
-            const int JK = G.order[T];
-            const int J = JK & 0xffff, K = JK >> 16;
-            const TC *src = nullptr;
-            int lag = 0;
-            if (f < TK) {                  // j-face of lane kk = f: lane (TJ-1, f) of (J-1, K)
-                if (J > 0 && K * TK + f < G.nz)
-                    src = ff + (((int64_t)G.tidx[(J - 1) * G.NK + K] * S + (TJ - 1)) * NF + f) * BS;
-                lag = f;
-            } else {                       // k-face of lane jj = q: lane (q, TK-1) of (J, K-1)
-                const int q = f - TK;
-                if (K > 0 && J * TJ + q < G.ny)
-                    src = ff + (((int64_t)G.tidx[J * G.NK + K - 1] * S + (TK - 1)) * NF + f) * BS;
-                lag = q;
-            }
-            boundary_role<TC, BS>(S, nx, base, lane, NF, src, lag, yring, cell, fl, pub_p, nullptr, err);
+            boundary_role<TC, BS, false>(G, tl.JK, base, lane, wave == 1 ? 0 : 1, ff, yring, fl, pub_p, nullptr, err);
         }
     } else if (wave < 2 + NLOAD) {
         // ---- loaders: DMA of steps w, w + NLOAD, ... ----
         const int w = wave - 2;
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, false, blk);
+            const Tile tl = next_tile(G, ctr, &tile, false, blk);
+            const int T = tl.T;
             if (T < 0) break;
-            const int JK = G.order[T];
-            const int j = (JK & 0xffff) * TJ + jj, k = (JK >> 16) * TK + kk;
-            const bool lane_ok = lane < TJ * TK && j < G.ny && k < G.nz;
-            const int64_t cl = lane_ok ? vsJ * j + vsK * k : 0;
-            const TF *lb = Lt + (int64_t)T * S * NM * 64;
-            // every step issues the same P instructions (the wait counts
-            // assume it): a lane with no cell loads zeros
+            const TF *lb = Lt + (int64_t)T * S * PL::SIZE;
             auto issue = [&](int t) {
-                char *sl = ringb + (t % D) * SB;
-                dma_block<PB>(lb + (int64_t)t * NM * 64, sl, lane);
-                const int i = t - jj - kk;
-                const bool ok = lane_ok && i >= 0 && i < nx;
-                RS::load(ok ? b + (cl + i) * BS : reinterpret_cast<const TIN *>(zero_cell), sl + PB);
+                dma_block<SB, BS == 3>(lb + (int64_t)t * PL::SIZE, ringb + (t % D) * SB, lane);
             };
-            loader_loop<D, P, K>(w, S, base, done_p, fl, lane, err, issue);
+            loader_loop<D, P, K>(w, S, base, done_p, &rhs_p, fl, lane, err, issue);
             // the backward sweep's face slots of this tile start unwritten
-            TC *fr = fb + (int64_t)T * S * NF * BS;
-            for (int64_t e = w * 64 + lane; e < (int64_t)S * NF * BS; e += NLOAD * 64)
-                fr[e] = sentinel_value<TC>();
+            const int64_t nf = (int64_t)S * FR::size(TJ, TK);
+            TC *fr = fb + (int64_t)T * nf;
+            for (int64_t e = w * 64 + lane; e < nf; e += NLOAD * 64) fr[e] = sentinel_value<TC>();
         }
     } else if (wave == 5) {
         // ---- publisher: high faces feed tiles J+1, K+1 ----
-        const int fj = jj == TJ - 1 && kk < TK ? kk : -1;
-        const int fk = kk == TK - 1 ? TK + jj : -1;
+        const int FV = FR::size(TJ, TK);
+        const FacePublisher<TC, BS, false> fp(TJ, TK, lane);
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, false, blk);
+            const Tile tl = next_tile(G, ctr, &tile, false, blk);
+            const int T = tl.T;
             if (T < 0) break;
-            TC *yrow = yt + (int64_t)T * S * BS * 64 + lane;
-            TC *frow = ff + (int64_t)T * S * NF * BS;
+            using PY = StepPlanes<TC, BS>;
+            TC *yrow = yt + (int64_t)T * S * PY::SIZE;
+            TC *frow = ff + (int64_t)T * S * FV;
             int seen = base;
             for (int t = 0; t < S; t++) {
                 progress_wait(done_p, base + t + 1, seen, err);
-                TC y[BS], pub[BS];
+                const u32x4 rec = fp.gather(yring, YR::slot(t + 1));
+                TC y[BS];
                 YR::load(yring, YR::slot(t + 1), own, y);
                 progress_put(pub_p, lane, base + t + 1);
-                unsentinel<TC, BS>(y, pub);
-                TC *ft = frow + (int64_t)t * NF * BS;
-                if (fj >= 0) publish_checked<TC, BS>(ft + fj * BS, pub);
-                if (fk >= 0) publish_checked<TC, BS>(ft + fk * BS, pub);
+                if (fp.mine) store_published(frow + (int64_t)t * FV + lane * FR::V, rec);
 #pragma unroll
-                for (int r = 0; r < BS; r++) yrow[(t * BS + r) * 64] = y[r];
+                for (int r = 0; r < BS; r++) yrow[(int64_t)t * PY::SIZE + PY::at(r, lane)] = y[r];
+            }
+        }
+    } else if (wave == 6) {
+        // ---- right-hand side: runs of RS_CH cells of every line ----
+        for (int base = 0;; base += S + 1) {
+            const Tile tl = next_tile(G, ctr, &tile, false, blk);
+            const int T = tl.T;
+            if (T < 0) break;
+            const int JK = tl.JK;
+            // this lane's cell of instruction q: line l, step s of the chunk
+            const TIN *src[RR::NI];
+            int x[RR::NI];
+            const int un = lane / RR::LPU;
+            const int rTJ = 65536 / TJ + 1;   // l / TJ = (l rTJ) >> 16 for l < 64, TJ <= 8
+#pragma unroll
+            for (int q = 0; q < RR::NI; q++) {
+                const int r = un / RR::UL, sh = (un % RR::UL) ^ RR::twist(q, r);
+                const int l = q * RR::LPB + r;
+                const int lkk = (l * rTJ) >> 16, ljj = l - lkk * TJ;
+                const int j = (JK & 0xffff) * TJ + ljj, k = (JK >> 16) * TK + lkk;
+                const bool ok = l < TJ * TK && j < G.ny && k < G.nz;
+                x[q] = ok ? sh / RR::UH - ljj - lkk : INT32_MIN / 2;   // x of the chunk at step 0
+                // 12-byte halves of a cell, or the dwords of a double
+                const int part = RR::UH == 2 ? (sh % RR::UH) * 12 : (lane % RR::LPU) * 4;
+                src[q] = reinterpret_cast<const TIN *>(
+                    reinterpret_cast<const char *>(b + ((ok ? vsJ * j + vsK * k : 0) + x[q]) * BS) + part);
+            }
+            // chunk c overwrites the steps RS_STEPS before its own; up to
+            // NCH chunks in flight
+            constexpr int NCH = RS_STEPS / RS_CH;
+            static_assert(NCH == 4 && NCH * RR::NI <= 63, "in-flight DMA within the vmcnt range");
+            const int nchunk = (S + RS_CH - 1) / RS_CH;
+            int next = 0, done = 0;
+            uint32_t idle = 0;
+            wait_vm<0>();
+            while (done < nchunk) {
+                while (next < nchunk && next - done < NCH &&
+                       (next < NCH || __builtin_amdgcn_readfirstlane(lds_flag_get(done_p.w)) >=
+                                          base + (next - NCH + 1) * RS_CH)) {
+                    char *dst = rring + (next & (NCH - 1)) * RR::CHB;
+                    const int t0 = next * RS_CH;
+#pragma unroll
+                    for (int q = 0; q < RR::NI; q++) {
+                        const int xi = x[q] + t0;
+                        const bool ok = xi >= 0 && xi < nx;
+                        dma_piece<RR::UB == 16 ? 12 : 4>(
+                            ok ? static_cast<const void *>(src[q] + (int64_t)t0 * BS)
+                               : static_cast<const void *>(zero_cell),
+                            dst + q * RR::IB);
+                    }
+                    next++;
+                }
+                const int inflight = next - done;
+                if (inflight == 0) {
+                    if (++idle > 4 * SPIN_LIMIT) {
+                        __hip_atomic_store(err, ERR_STALL_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                    continue;
+                }
+                idle = 0;
+                if (inflight == 4) wait_vm<3 * RR::NI>();
+                if (inflight == 3) wait_vm<2 * RR::NI>();
+                if (inflight == 2) wait_vm<RR::NI>();
+                if (inflight == 1) wait_vm<0>();
+                done++;
+                progress_put(rhs_p, lane, base + min(done * RS_CH, S));
             }
         }
     } else {
-        while (next_tile(G, ctr, &tile, false, blk) >= 0) {
+        while (next_tile(G, ctr, &tile, false, blk).T >= 0) {
         }
     }
 }
@@ -1112,7 +1361,7 @@ struct OutBox {
 // add_in + x; 2 add_out = (add_in[cell], 0, 0) + x.  Their operands are
 // loaded before the wait for the steps, off everyone's critical path.
 template <int BS, typename TC, typename TO, int ADD, typename TAI, typename TAO>
-__device__ __forceinline__ void writer_role(const GridTiles &G, int T, int base, int lane,
+__device__ __forceinline__ void writer_role(const GridTiles &G, int JK, int base, int lane,
                                             const char *yring, const Progress &done_p, Progress &wr_p,
                                             const OutBox &box, TO *__restrict__ xo,
                                             const TAI *__restrict__ add_in,
@@ -1120,7 +1369,6 @@ __device__ __forceinline__ void writer_role(const GridTiles &G, int T, int base,
     using YR = YRing<TC, BS>;
     constexpr int CK = YR::DY / 4, LPI = 64 / CK, NA = ADD == 1 ? BS : 1;
     const int TJ = G.TJ, TK = G.TK, S = G.S;
-    const int JK = G.order[T];
     const int j0 = (JK & 0xffff) * TJ, k0 = (JK >> 16) * TK;
     const int rTJ = 65536 / TJ + 1;   // l / TJ = (l rTJ) >> 16 for l < 64, TJ <= 8
     int seen = base;
@@ -1174,27 +1422,29 @@ __device__ __forceinline__ void grid_bwd_body(const GridTiles &G, const TF *__re
                                               const TAI *__restrict__ add_in,
                                               TAO *__restrict__ add_out) {
     constexpr int B2 = BS * BS, NM = 3 * B2, NV = NM + B2 + BS;
-    // ring step: NM factor planes of TF, B2 diagonal-inverse planes of TD,
-    // BS forward-result planes of TC
+    // ring step: the factor planes, the diagonal inverses, the forward result
+    using PL = StepPlanes<TF, NM>;
+    using PD = StepPlanes<TD, B2>;
+    using PY = StepPlanes<TC, BS>;
     using YR = YRing<TC, BS>;
+    using FR = FaceRec<TC, BS>;
     constexpr int DY = YR::DY;
-    constexpr int PB = pad256(NM * 64 * (int)sizeof(TF)), DBY = B2 * 64 * (int)sizeof(TD);
-    constexpr int YB = BS * 64 * (int)sizeof(TC);
+    constexpr int PB = PL::BYTES, DBY = PD::BYTES, YB = PY::BYTES;
     constexpr int SB = PB + DBY + YB;
-    constexpr int D = ring_slots<SB>();
+    constexpr int D = ring_slots<SB, 120000>();
     constexpr int P = dma_count(PB) + dma_count(DBY) + dma_count(YB);
-    constexpr int K = (D / NLOAD) < (63 / P) ? (D / NLOAD) : (63 / P);
+    constexpr int KM = (D / NLOAD) < (63 / P) ? (D / NLOAD) : (63 / P), K = KM < 4 ? KM : 4;
     __shared__ __attribute__((aligned(16))) char ringb[D * SB];
     __shared__ __attribute__((aligned(16))) char yring[YR::BYTES];
     __shared__ StepFlag fl[DY];
     __shared__ Progress done_p, pub_p, wr_p;   // computed, published, written
-    __shared__ int tile;
+    __shared__ Tile tile;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (blk == 0 && (int)threadIdx.x < G.NQ) other_ctr[threadIdx.x] = 0;
     if (threadIdx.x < DY) fl[threadIdx.x].h[0] = fl[threadIdx.x].h[1] = -1;
     if (threadIdx.x < 64) done_p.w[threadIdx.x] = pub_p.w[threadIdx.x] = wr_p.w[threadIdx.x] = 0;
-    const int TJ = G.TJ, TK = G.TK, NF = G.NF, nx = G.nx, S = G.S;
+    const int TJ = G.TJ, TK = G.TK, S = G.S;
     const int jj = lane % TJ, kk = lane / TJ;
     // the ring slots hold the tile mirrored in j and k, so the +1 neighbours
     // sit where the forward sweep has its -1 neighbours
@@ -1202,18 +1452,12 @@ __device__ __forceinline__ void grid_bwd_body(const GridTiles &G, const TF *__re
     if (wave == 0) {
         // ---- compute ----
         auto read_step = [&](const char *sl, TC (&v)[NV]) {
-            const TF *pu = reinterpret_cast<const TF *>(sl);
-            const TD *pd = reinterpret_cast<const TD *>(sl + PB);
-            const TC *py = reinterpret_cast<const TC *>(sl + PB + DBY);
-#pragma unroll
-            for (int e = 0; e < NM; e++) v[e] = cvt<TC, TF>(pu[e * 64 + lane]);
-#pragma unroll
-            for (int e = 0; e < B2; e++) v[NM + e] = static_cast<TC>(pd[e * 64 + lane]);
-#pragma unroll
-            for (int r = 0; r < BS; r++) v[NM + B2 + r] = py[r * 64 + lane];
+            PL::template read<TC>(sl, lane, v);
+            PD::template read<TC>(sl + PB, lane, v + NM);
+            PY::template read<TC>(sl + PB + DBY, lane, v + NM + B2);
         };
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, true, blk);   // reverse tile order
+            const int T = next_tile(G, ctr, &tile, true, blk).T;   // reverse tile order
             if (T < 0) break;
             TC xp[BS];
 #pragma unroll
@@ -1258,81 +1502,65 @@ __device__ __forceinline__ void grid_bwd_body(const GridTiles &G, const TF *__re
             }
             if (t < S) step(t, va, vb);
         }
-    } else if (wave == 1) {
+    } else if (wave == 1 || wave == 7) {
         // ---- boundary: faces of tiles (J+1, K) and (J, K+1) ----
-        const int f = lane % NF;
-        const int cell = f < TK ? (TK - f) * (TJ + 1) : TJ - (f - TK);
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, true, blk);
+            const Tile tl = next_tile(G, ctr, &tile, true, blk);
+            const int T = tl.T;
             if (T < 0) break;
-            const int JK = G.order[T];
-            const int J = JK & 0xffff, K = JK >> 16;
-            const TC *src = nullptr;
-            int lag = 0;
-            if (f < TK) {                  // j-face of lane (TJ-1, f): lane (0, f) of (J+1, K)
-                if (J + 1 < G.NJ && K * TK + f < G.nz)
-                    src = fb + (((int64_t)G.tidx[(J + 1) * G.NK + K] * S + (TJ - 1)) * NF + f) * BS;
-                lag = TK - 1 - f;
-            } else {                       // k-face of lane (q, TK-1): lane (q, 0) of (J, K+1)
-                const int q = f - TK;
-                if (K + 1 < G.NK && J * TJ + q < G.ny)
-                    src = fb + (((int64_t)G.tidx[J * G.NK + K + 1] * S + (TK - 1)) * NF + f) * BS;
-                lag = TJ - 1 - q;
-            }
-            boundary_role<TC, BS>(S, nx, base, lane, NF, src, lag, yring, cell, fl, pub_p, &wr_p, err);
+            boundary_role<TC, BS, true>(G, tl.JK, base, lane, wave == 1 ? 0 : 1, fb, yring, fl, pub_p, &wr_p, err);
         }
     } else if (wave < 2 + NLOAD) {
         // ---- loaders: DMA of U blocks, diagonal inverses, forward result ----
         const int w = wave - 2;
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, true, blk);
+            const Tile tl = next_tile(G, ctr, &tile, true, blk);
+            const int T = tl.T;
             if (T < 0) break;
-            const TF *ub = Ut + (int64_t)T * S * NM * 64;
-            const TD *db = Dt + (int64_t)T * S * B2 * 64;
-            const TC *yb = yt + (int64_t)T * S * BS * 64;
+            const TF *ub = Ut + (int64_t)T * S * PL::SIZE;
+            const TD *db = Dt + (int64_t)T * S * PD::SIZE;
+            const TC *yb = yt + (int64_t)T * S * PY::SIZE;
             auto issue = [&](int t) {
                 char *sl = ringb + (t % D) * SB;
-                dma_block<PB>(ub + (int64_t)t * NM * 64, sl, lane);
-                dma_block<DBY>(db + (int64_t)t * B2 * 64, sl + PB, lane);
+                dma_block<PB, BS == 3>(ub + (int64_t)t * PL::SIZE, sl, lane);
+                dma_block<DBY, BS == 3>(db + (int64_t)t * PD::SIZE, sl + PB, lane);
                 // the forward result of the same cells: forward step S - 1 - t
-                dma_block<YB>(yb + (int64_t)(S - 1 - t) * BS * 64, sl + PB + DBY, lane);
+                dma_block<YB, BS == 3>(yb + (int64_t)(S - 1 - t) * PY::SIZE, sl + PB + DBY, lane);
             };
-            loader_loop<D, P, K>(w, S, base, done_p, fl, lane, err, issue);
+            loader_loop<D, P, K>(w, S, base, done_p, nullptr, fl, lane, err, issue);
             // the forward sweep's face slots of this tile start unwritten
-            TC *fr = ff + (int64_t)T * S * NF * BS;
-            for (int64_t e = w * 64 + lane; e < (int64_t)S * NF * BS; e += NLOAD * 64)
-                fr[e] = sentinel_value<TC>();
+            const int64_t nf = (int64_t)S * FR::size(TJ, TK);
+            TC *fr = ff + (int64_t)T * nf;
+            for (int64_t e = w * 64 + lane; e < nf; e += NLOAD * 64) fr[e] = sentinel_value<TC>();
         }
     } else if (wave == 5) {
         // ---- publisher: low faces feed tiles J-1, K-1 ----
-        const int fj = jj == 0 && kk < TK ? kk : -1;
-        const int fk = kk == 0 ? TK + jj : -1;
+        const int FV = FR::size(TJ, TK);
+        const FacePublisher<TC, BS, true> fp(TJ, TK, lane);
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, true, blk);
+            const Tile tl = next_tile(G, ctr, &tile, true, blk);
+            const int T = tl.T;
             if (T < 0) break;
-            TC *frow = fb + (int64_t)T * S * NF * BS;
+            TC *frow = fb + (int64_t)T * S * FV;
             int seen = base;
             for (int t = 0; t < S; t++) {
                 progress_wait(done_p, base + t + 1, seen, err);
-                TC x[BS], pub[BS];
-                YR::load(yring, YR::slot(t + 1), own, x);
+                const u32x4 rec = fp.gather(yring, YR::slot(t + 1));
                 progress_put(pub_p, lane, base + t + 1);
-                unsentinel<TC, BS>(x, pub);
-                TC *ft = frow + (int64_t)t * NF * BS;
-                if (fj >= 0) publish_checked<TC, BS>(ft + fj * BS, pub);
-                if (fk >= 0) publish_checked<TC, BS>(ft + fk * BS, pub);
+                if (fp.mine) store_published(frow + (int64_t)t * FV + lane * FR::V, rec);
             }
         }
     } else if (wave == 6) {
         // ---- writer ----
         for (int base = 0;; base += S + 1) {
-            const int T = next_tile(G, ctr, &tile, true, blk);
+            const Tile tl = next_tile(G, ctr, &tile, true, blk);
+            const int T = tl.T;
             if (T < 0) break;
-            writer_role<BS, TC, TO, ADD, TAI, TAO>(G, T, base, lane, yring, done_p, wr_p, box, xo,
+            writer_role<BS, TC, TO, ADD, TAI, TAO>(G, tl.JK, base, lane, yring, done_p, wr_p, box, xo,
                                                    add_in, add_out, err);
         }
     } else {
-        while (next_tile(G, ctr, &tile, true, blk) >= 0) {
+        while (next_tile(G, ctr, &tile, true, blk).T >= 0) {
         }
     }
 }
@@ -1362,6 +1590,21 @@ __global__ __launch_bounds__(GWG) void k_grid_bwd(GridTiles G, const TF *__restr
 // owns the workgroups [wg0, wg0 + wgs) of each kernel (multiples of
 // GRID_QUEUES, so a workgroup's queue, and XCD, keep their mapping)
 // ---------------------------------------------------------------------------
+// A pointer read from a descriptor, as an offset from `origin`, a kernel
+// argument that is null: derived from a kernel argument, its accesses are
+// global instructions; those of a pointer read from memory are flat ones,
+// which also wait on the LDS counter.
+template <typename T>
+__device__ __forceinline__ T *as_global(char *origin, T *p) {
+    return reinterpret_cast<T *>(origin + reinterpret_cast<uintptr_t>(p));
+}
+__device__ __forceinline__ void globalize(char *origin, GridTiles &G) {
+    G.order = as_global(origin, const_cast<int *>(G.order));
+    G.tidx = as_global(origin, const_cast<int *>(G.tidx));
+    G.qtiles = as_global(origin, const_cast<int *>(G.qtiles));
+    G.qjk = as_global(origin, const_cast<int *>(G.qjk));
+    G.qoff = as_global(origin, const_cast<int *>(G.qoff));
+}
 __device__ __forceinline__ int find_grid(const GridMulti *__restrict__ d, int ngrid, int blk) {
     int g = 0;
     while (g + 1 < ngrid && blk >= d[g + 1].wg0) g++;
@@ -1370,23 +1613,28 @@ __device__ __forceinline__ int find_grid(const GridMulti *__restrict__ d, int ng
 
 template <int BS>
 __global__ __launch_bounds__(GWG) void k_grid_fwd_multi(const GridMulti *__restrict__ d, int ngrid,
-                                                        const double *__restrict__ v, int *err) {
+                                                        const double *__restrict__ v, int *err,
+                                                        char *origin) {
     const int g = find_grid(d, ngrid, blockIdx.x);
-    const GridMulti D = d[g];
-    grid_fwd_body<BS, double, double, double>(D.G, D.lt, v + D.boff, D.yt, D.ff, D.fb, D.ctr,
-                                              D.ctr + D.G.NQ, err, blockIdx.x - D.wg0, D.vsJ,
-                                              D.vsK);
+    GridMulti D = d[g];
+    globalize(origin, D.G);
+    grid_fwd_body<BS, double, double, double>(
+        D.G, as_global(origin, D.lt), v + D.boff, as_global(origin, D.yt), as_global(origin, D.ff), as_global(origin, D.fb),
+        as_global(origin, D.ctr), as_global(origin, D.ctr) + D.G.NQ, err, blockIdx.x - D.wg0, D.vsJ, D.vsK);
 }
 
 template <int BS>
 __global__ __launch_bounds__(GWG) void k_grid_bwd_multi(const GridMulti *__restrict__ d, int ngrid,
-                                                        double *__restrict__ z, int *err) {
+                                                        double *__restrict__ z, int *err,
+                                                        char *origin) {
     const int g = find_grid(d, ngrid, blockIdx.x);
-    const GridMulti D = d[g];
+    GridMulti D = d[g];
+    globalize(origin, D.G);
     const OutBox box{D.oi0, D.oi1, D.oj0, D.oj1, D.ok0, D.ok1, D.vsJ, D.vsK};
     grid_bwd_body<BS, double, double, double, double, 0, double, double>(
-        D.G, D.ut, D.dt, D.yt, D.fb, D.ff, D.ctr + D.G.NQ, D.ctr, err, blockIdx.x - D.wg0, box,
-        z + D.boff, nullptr, nullptr);
+        D.G, as_global(origin, D.ut), as_global(origin, D.dt), as_global(origin, D.yt), as_global(origin, D.fb), as_global(origin, D.ff),
+        as_global(origin, D.ctr) + D.G.NQ, as_global(origin, D.ctr), err, blockIdx.x - D.wg0, box, z + D.boff,
+        nullptr, nullptr);
 }
 
 int grid_multi_launch_size(const IluFactor &F, int *wgs) {
@@ -1425,16 +1673,20 @@ int grid_multi_apply(hipStream_t s, int bs, const GridMulti *d_desc, int ngrid, 
     {
         TimedScope t("ras_ilu_fwd", s);
         if (bs == 1)
-            hipLaunchKernelGGL(k_grid_fwd_multi<1>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, v, err);
+            hipLaunchKernelGGL(k_grid_fwd_multi<1>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, v, err,
+                               static_cast<char *>(nullptr));
         else
-            hipLaunchKernelGGL(k_grid_fwd_multi<3>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, v, err);
+            hipLaunchKernelGGL(k_grid_fwd_multi<3>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, v, err,
+                               static_cast<char *>(nullptr));
     }
     {
         TimedScope t("ras_ilu_bwd", s);
         if (bs == 1)
-            hipLaunchKernelGGL(k_grid_bwd_multi<1>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, z, err);
+            hipLaunchKernelGGL(k_grid_bwd_multi<1>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, z, err,
+                               static_cast<char *>(nullptr));
         else
-            hipLaunchKernelGGL(k_grid_bwd_multi<3>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, z, err);
+            hipLaunchKernelGGL(k_grid_bwd_multi<3>, dim3(total_wgs), dim3(GWG), 0, s, d_desc, ngrid, z, err,
+                               static_cast<char *>(nullptr));
     }
     KRY_HIP(hipGetLastError());
     return KRY_OK;

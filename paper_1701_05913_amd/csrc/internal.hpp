@@ -217,6 +217,7 @@ struct GridTiles {
     // which the dispatcher places on XCD b % 8
     int NQ = 0, qmax = 0;            // queue count, longest queue
     const int *qtiles = nullptr;
+    const int *qjk = nullptr;        // J | K << 16 of the same entries
     const int *qoff = nullptr;
 };
 
