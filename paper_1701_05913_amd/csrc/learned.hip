@@ -14,8 +14,8 @@
 // load.  The input gradient of a layer is the same kernel run with the
 // weights flipped in space and transposed in channels; the weight gradient
 // is a second MFMA kernel that contracts over cells (K = 32 cells), with
-// channel-major LDS copies of the brick shifted along x so every 8-cell
-// operand is an aligned 16-byte load.  Partial sums are reduced in a fixed
+// channel-major LDS copies of the brick (the output gradient's shifted along
+// x) so every 8-cell operand is an aligned 16-byte load.  Partial sums are reduced in a fixed
 // order (bitwise reproducible).
 //
 // Parameter layout (FP32 master copy): for each layer l, W_l[co][ci][tap]
@@ -40,7 +40,6 @@ constexpr int HX = BX + 2, HY = BY + 2, HZ = BZ + 2;
 constexpr int HCELLS = HX * HY * HZ;
 constexpr int CSTRIDE32 = 40;                                // bf16 per halo cell (32 + pad)
 constexpr int DWX = 16, DWY = 4, DWZ = 2;                    // weight-gradient brick
-constexpr int DWROWX = 24;                                   // padded x extent of its halo rows
 constexpr int DW_WG = 256;                                   // persistent weight-gradient workgroups
 
 // FP32 -> BF16 round to nearest even in one instruction (v_cvt_pk_bf16_f32
@@ -455,126 +454,216 @@ __global__ __launch_bounds__(256) void k_conv32(int nx, int ny, int nz, int cout
 
 // ---------------------------------------------------------------------------
 // weight gradient: part[wg][m][n] = sum over the bricks of workgroup wg of
-// dz[cell][m] * h[cell + tap][c], n = tap * CINP + c (M = MT*16 output
-// channels, N = 27*CINP columns in tiles of 16).  K runs over 32 cells at a
-// time: lane group q of a K block covers 8 consecutive x cells.
+// dz[cell - dx][m] * h[cell + (dy, dz)][c], n = tap * CINP + c: a contraction
+// over cells (K), 32 at a time: lane group q of a K block covers 8 cells of
+// one x row.
+//   The matrix cores want 8 consecutive cells of one channel per lane, the
+// arrays are channels-last.  Each thread loads 8 cells x 8 channels (16 bytes
+// a cell) of its part of the brick into registers, pairs neighbouring cells
+// with byte permutes and writes 8 cells of a channel as one 16-byte piece.
+// The x shift of a tap sits on dz, whose three shifted copies come from the
+// same registers (10 cells), so one fragment of h serves the three dx of a
+// (dz, dy) pair: 11 LDS fragment reads per 30 MFMAs of a wavefront.  The next
+// brick's loads are in flight during the MFMAs.
+//   Bound by the MFMAs and, at 64^3, by having 8 bricks per workgroup.  64^3,
+// 32 -> 32 channels (14.5 GFLOP): 35 us (2-byte loads, one per element and
+// shifted copy, and three copies of h in LDS: 287 us).
 // ---------------------------------------------------------------------------
+constexpr int DW_ROWS = (DWY + 2) * (DWZ + 2);               // h rows of a brick
+constexpr int DW_HST = DW_ROWS * DWX + 8;                    // channel strides in LDS: 4 words
+constexpr int DW_DST = DWX * DWY * DWZ + 8;                  // modulo 64, no bank conflicts
+
+// dword of the values of two neighbouring cells (a before b) of channel
+// half `hi` of their words
+template <int HI>
+__device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_perm(b, a, HI ? 0x07060302u : 0x05040100u);
+}
+
 template <int CINP, int MT, int DZC>
 __global__ __launch_bounds__(256) void k_conv_wgrad(int nx, int ny, int nz,
                                                     const uint16_t *__restrict__ dz,
                                                     const uint16_t *__restrict__ h,
                                                     float *__restrict__ part) {
-    constexpr int NNT = (27 * CINP + 15) / 16;               // column tiles
-    constexpr int TPW = (NNT + 3) / 4;                       // column tiles per wave
     constexpr int M = MT * 16;
-    constexpr int HYd = DWY + 2, HZd = DWZ + 2;
-    constexpr int ROWS = HYd * HZd;                          // halo rows per channel
-    constexpr int CH = CINP;
-    // channel-major brick of h with halo, three copies shifted along x by
-    // 0, 1, 2 cells so that the 8-cell operand of every tap is aligned
-    __shared__ __attribute__((aligned(16))) uint16_t sh_h[3][CH * ROWS * DWROWX];
-    __shared__ __attribute__((aligned(16))) uint16_t sh_dz[M][DWX * DWY * DWZ];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int CTH = CINP < 8 ? CINP : 8, CTD = DZC < 8 ? DZC : 8;   // channels per task
+    constexpr int ND = DWY * DWZ * 2 * (DZC / CTD), NH = DW_ROWS * 2 * (CINP / CTH);
+    static_assert(DWX == 16 && ND + NH <= 256, "one staging task per thread");
+    constexpr int NU = CINP == 32 ? 18 : 3;                  // fragments of h per K block
+    constexpr int UPW = (NU + 3) / 4;
+    __shared__ __attribute__((aligned(16))) uint16_t sh_h[CINP * DW_HST];
+    __shared__ __attribute__((aligned(16))) uint16_t sh_dz[3][M * DW_DST];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nbx = (nx + DWX - 1) / DWX, nby = (ny + DWY - 1) / DWY, nbz = (nz + DWZ - 1) / DWZ;
     const int nbricks = nbx * nby * nbz;
     const int64_t sy = nx, sz = (int64_t)nx * ny;
     const int xl = lane & 15, q = lane >> 4;
-    f32x4 acc[TPW][MT];
-#pragma unroll
-    for (int j = 0; j < TPW; j++)
-#pragma unroll
-        for (int m = 0; m < MT; m++) acc[j][m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    for (int br = blockIdx.x; br < nbricks; br += gridDim.x) {
-        const int x0 = (br % nbx) * DWX, y0 = ((br / nbx) % nby) * DWY, z0 = (br / (nbx * nby)) * DWZ;
-        __syncthreads();
-        // stage h: copy s holds x index hx at position hx - s
-        for (int e = tid; e < CH * ROWS * DWROWX; e += 256) {
-            const int px = e % DWROWX, row = (e / DWROWX) % ROWS, c = e / (DWROWX * ROWS);
-            const int hy = row % HYd, hz = row / HYd;
-            const int gy = y0 + hy - 1, gz = z0 + hz - 1;
+    // this thread's staging task: channels cg.., 8 cells from 8 xg of a row
+    const bool isdz = tid < ND;
+    const int task = isdz ? tid : tid - ND;
+    const bool busy = isdz || task < NH;
+    const int ncg = isdz ? DZC / CTD : CINP / CTH;
+    const int cg = task % ncg, xg = (task / ncg) & 1, row = task / (2 * ncg);
+    const int ry = isdz ? row % DWY : row % (DWY + 2) - 1, rz = isdz ? row / DWY : row / (DWY + 2) - 1;
+    uint32_t pre[10][4];
+    auto load = [&](int br) {
+        const int x0 = (br % nbx) * DWX + 8 * xg, y = ((br / nbx) % nby) * DWY + ry,
+                  z = (br / (nbx * nby)) * DWZ + rz;
+        const bool ok = busy && y >= 0 && y < ny && z >= 0 && z < nz;
+        const int64_t cell = x0 + y * sy + z * sz;
 #pragma unroll
-            for (int s = 0; s < 3; s++) {
-                const int gx = x0 + px + s - 1;
-                uint16_t v = 0;
-                if (px + s < DWX + 2 && gx >= 0 && gx < nx && gy >= 0 && gy < ny && gz >= 0 && gz < nz)
-                    v = h[(gx + gy * sy + gz * sz) * CINP + c];
-                sh_h[s][e] = v;
+        for (int i = 0; i < 10; i++) {
+#pragma unroll
+            for (int w = 0; w < 4; w++) pre[i][w] = 0;
+            if (isdz) {                                      // cells x0 - 1 .. x0 + 8
+                if (ok && x0 + i - 1 >= 0 && x0 + i - 1 < nx)
+                    __builtin_memcpy(pre[i], __builtin_assume_aligned(dz + (cell + i - 1) * DZC + cg * CTD, 2 * CTD), 2 * CTD);
+            } else if (i < 8) {                              // cells x0 .. x0 + 7
+                if (ok && x0 + i < nx)
+                    __builtin_memcpy(pre[i], __builtin_assume_aligned(h + (cell + i) * CINP + cg * CTH, 2 * CTH), 2 * CTH);
             }
         }
-        // stage dz transposed: sh_dz[m][cell of brick]
-        for (int e = tid; e < M * DWX * DWY * DWZ; e += 256) {
-            const int cb = e % (DWX * DWY * DWZ), m = e / (DWX * DWY * DWZ);
-            const int bx = cb % DWX, by = (cb / DWX) % DWY, bz = cb / (DWX * DWY);
-            const int gx = x0 + bx, gy = y0 + by, gz = z0 + bz;
-            uint16_t v = 0;
-            if (m < DZC && gx < nx && gy < ny && gz < nz) v = dz[(gx + gy * sy + gz * sz) * DZC + m];
-            sh_dz[m][cb] = v;
+    };
+    // 8 cells of channel c of the task, from pre[i0] on
+    auto piece = [&](int c, int i0) {
+        uint4 v;
+        const int w = c >> 1;
+        if (c & 1)
+            v = make_uint4(pair16<1>(pre[i0][w], pre[i0 + 1][w]), pair16<1>(pre[i0 + 2][w], pre[i0 + 3][w]),
+                           pair16<1>(pre[i0 + 4][w], pre[i0 + 5][w]), pair16<1>(pre[i0 + 6][w], pre[i0 + 7][w]));
+        else
+            v = make_uint4(pair16<0>(pre[i0][w], pre[i0 + 1][w]), pair16<0>(pre[i0 + 2][w], pre[i0 + 3][w]),
+                           pair16<0>(pre[i0 + 4][w], pre[i0 + 5][w]), pair16<0>(pre[i0 + 6][w], pre[i0 + 7][w]));
+        return v;
+    };
+    auto stage = [&]() {
+        if (isdz) {
+#pragma unroll
+            for (int c = 0; c < CTD; c++)
+#pragma unroll
+                for (int s = 0; s < 3; s++)                  // dx = s - 1: cell x - dx
+                    *reinterpret_cast<uint4 *>(&sh_dz[s][(cg * CTD + c) * DW_DST + row * DWX + 8 * xg]) =
+                        piece(c, 2 - s);
+        } else if (busy) {
+#pragma unroll
+            for (int c = 0; c < CTH; c++)
+                *reinterpret_cast<uint4 *>(&sh_h[(cg * CTH + c) * DW_HST + row * DWX + 8 * xg]) = piece(c, 0);
         }
+    };
+
+    f32x4 acc[UPW][3][MT];
+#pragma unroll
+    for (int u = 0; u < UPW; u++)
+#pragma unroll
+        for (int s = 0; s < 3; s++)
+#pragma unroll
+            for (int m = 0; m < MT; m++) acc[u][s][m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // this lane's column of unit wave + 4 u: channel and (dz, dy) pair p
+    // (CINP = 4: four pairs a unit, those past the ninth give zeros)
+    int hofs[UPW];
+    bool real[UPW];
+#pragma unroll
+    for (int u = 0; u < UPW; u++) {
+        const int un = wave + 4 * u;
+        const int p = CINP == 32 ? un >> 1 : (un * 16 + xl) >> 2;
+        const int c = CINP == 32 ? (un & 1) * 16 + xl : xl & 3;
+        real[u] = un < NU && p < 9;
+        const int pp = real[u] ? p : 0;
+        hofs[u] = c * DW_HST + ((pp / 3) * (DWY + 2) + pp % 3) * DWX;
+    }
+    if (DZC < M)   // rows past the channels stay zero
+        for (int e = tid; e < 3 * M * DW_DST; e += 256) (&sh_dz[0][0])[e] = 0;
+
+    int br = blockIdx.x;
+    if (br < nbricks) load(br);
+    for (; br < nbricks; br += gridDim.x) {
+        __syncthreads();   // the previous brick's fragments have been read
+        stage();
         __syncthreads();
-        // K blocks: 32 cells = rows (2 kb, 2 kb + 1) of 16 x cells; lane group
-        // q covers row 2 kb + q/2, x = 8 (q%2) .. + 8
+        if (br + (int)gridDim.x < nbricks) load(br + gridDim.x);
+#pragma unroll
         for (int kb = 0; kb < DWY * DWZ / 2; kb++) {
-            const int row = 2 * kb + (q >> 1), xs = 8 * (q & 1);
-            const int by = row % DWY, bz = row / DWY;
-            bf16x8 afr[MT];
+            const int r = 2 * kb + (q >> 1), xs = 8 * (q & 1);
+            const int by = r % DWY, bz = r / DWY;
+            bf16x8 afr[3][MT];
 #pragma unroll
-            for (int m = 0; m < MT; m++)
-                afr[m] = *reinterpret_cast<const bf16x8 *>(&sh_dz[m * 16 + xl][row * DWX + xs]);
+            for (int s = 0; s < 3; s++)
 #pragma unroll
-            for (int j = 0; j < TPW; j++) {
-                const int nt = wave + 4 * j;
-                if (nt < NNT) {
-                    const int n = nt * 16 + xl;
-                    const int tap = n / CINP < 27 ? n / CINP : 26, c = n % CINP;
-                    const int dzz = tap / 9 - 1, dyy = (tap / 3) % 3 - 1, dxx = tap % 3 - 1;
-                    // halo x of the first cell = xs + 1 + dxx, taken from copy
-                    // s = 1 + dxx at position xs (aligned to 8 elements)
-                    const int hrow = (bz + 1 + dzz) * HYd + (by + 1 + dyy);
-                    const uint16_t *src = &sh_h[1 + dxx][(c * ROWS + hrow) * DWROWX + xs];
-                    bf16x8 b = *reinterpret_cast<const bf16x8 *>(src);
-                    if (n >= 27 * CINP) b = bf16x8{};
+                for (int m = 0; m < MT; m++)
+                    afr[s][m] = *reinterpret_cast<const bf16x8 *>(&sh_dz[s][(m * 16 + xl) * DW_DST + r * DWX + xs]);
+#pragma unroll
+            for (int u = 0; u < UPW; u++) {
+                if (wave + 4 * u >= NU) continue;            // wave-uniform
+                bf16x8 b = *reinterpret_cast<const bf16x8 *>(&sh_h[hofs[u] + (bz * (DWY + 2) + by) * DWX + xs]);
+                if (CINP == 4 && !real[u]) b = bf16x8{};
+#pragma unroll
+                for (int s = 0; s < 3; s++)
 #pragma unroll
                     for (int m = 0; m < MT; m++)
-                        acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[m], b, acc[j][m], 0, 0, 0);
-                }
+                        acc[u][s][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[s][m], b, acc[u][s][m], 0, 0, 0);
             }
         }
     }
-    // D[m][n]: lane holds n = nt*16 + lane%16, m = mt*16 + 4 (lane/16) + i
-    float *pw = part + (size_t)blockIdx.x * M * (NNT * 16);
+    // D[m][n]: lane holds column xl of its unit, m = mt*16 + 4 q + i
+    constexpr int NN = 27 * CINP;
+    float *pw = part + (size_t)blockIdx.x * M * NN;
 #pragma unroll
-    for (int j = 0; j < TPW; j++) {
-        const int nt = wave + 4 * j;
-        if (nt < NNT)
+    for (int u = 0; u < UPW; u++) {
+        const int un = wave + 4 * u;
+        if (!real[u]) continue;
+        const int p = CINP == 32 ? un >> 1 : (un * 16 + xl) >> 2;
+        const int c = CINP == 32 ? (un & 1) * 16 + xl : xl & 3;
+#pragma unroll
+        for (int s = 0; s < 3; s++)
 #pragma unroll
             for (int m = 0; m < MT; m++)
 #pragma unroll
                 for (int i = 0; i < 4; i++)
-                    pw[(size_t)(m * 16 + 4 * q + i) * (NNT * 16) + nt * 16 + xl] = acc[j][m][i];
+                    pw[(size_t)(m * 16 + 4 * q + i) * NN + (p * 3 + s) * CINP + c] = acc[u][s][m][i];
     }
 }
 
-// grad W[co][ci][tap] = sum over workgroups (fixed order) of part[wg][co][tap*CINP + ci]
-__global__ void k_wgrad_reduce(const float *__restrict__ part, int nwg, int M, int NN, int cinp,
-                               int cin, int cout, float *__restrict__ gW) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= cout * cin * 27) return;
-    const int tap = q % 27, ci = (q / 27) % cin, co = q / (27 * cin);
-    const int n = tap * cinp + ci;
+// grad W[co][ci][tap] = sum over workgroups (fixed order) of
+// part[wg][co][tap * cinp + ci], NN = 27 cinp: blockIdx.y = co, a wavefront
+// reads 64 consecutive columns, the four wavefronts take the workgroups in
+// turn (64^3, 256 partials of 110 KB: 6 us; one thread per weight in
+// the output's order, whose loads are cinp apart, took 75 us)
+__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *__restrict__ part, int nwg, int M,
+                                                      int cinp, int cin, float *__restrict__ gW) {
+    __shared__ float sh[4][64];
+    const int NN = 27 * cinp, lane = threadIdx.x & 63, w4 = threadIdx.x >> 6;
+    const int n = blockIdx.x * 64 + lane, co = blockIdx.y;
     float s = 0.0f;
-    for (int w = 0; w < nwg; w++) s += part[((size_t)w * M + co) * NN + n];
-    gW[q] = s;
+    if (n < NN) {
+        const float *p = part + (size_t)co * NN + n;
+#pragma unroll 8
+        for (int w = w4; w < nwg; w += 4) s += p[(size_t)w * M * NN];
+    }
+    sh[w4][lane] = s;
+    __syncthreads();
+    if (w4 != 0 || n >= NN) return;
+    const int tap = n / cinp, ci = n - tap * cinp;
+    if (ci < cin) gW[((size_t)co * cin + ci) * 27 + tap] = sh[0][lane] + sh[1][lane] + sh[2][lane] + sh[3][lane];
 }
 
-// bias gradient from block partials (fixed order)
-__global__ void k_bgrad_reduce(const float *__restrict__ part, int nblk, int stride, int cout,
-                               float *__restrict__ gb) {
-    const int co = threadIdx.x;
-    if (co >= cout) return;
+// bias gradient from block partials of 32 columns (fixed order): 32 groups of
+// threads take the blocks in turn
+__global__ __launch_bounds__(1024) void k_bgrad_reduce(const float *__restrict__ part, int nblk,
+                                                       float *__restrict__ gb) {
+    __shared__ float sh[32][32];
+    const int co = threadIdx.x & 31, g = threadIdx.x >> 5;
     float s = 0.0f;
-    for (int b = 0; b < nblk; b++) s += part[(size_t)b * stride + co];
-    gb[co] = s;
+#pragma unroll 4
+    for (int b = g; b < nblk; b += 32) s += part[(size_t)b * 32 + co];
+    sh[g][co] = s;
+    __syncthreads();
+    if (threadIdx.x >= 32) return;
+    s = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 32; k++) s += sh[k][threadIdx.x];
+    gb[threadIdx.x] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -657,12 +746,22 @@ __global__ void k_il_to_cm(int64_t cells, const double *__restrict__ x, float *_
     for (int k = 0; k < 3; k++) y[k * cells + c] = static_cast<float>(x[c * 3 + k]);
 }
 
-__global__ void k_loss_final(const float *__restrict__ part, int nblk, int64_t cells,
-                             float *__restrict__ loss, float *__restrict__ gb4) {
+// sums of the loss partials (loss, three bias gradients) in FP64, in a fixed
+// order: thread t takes value t % 4 of the blocks t / 4 (mod 64)
+__global__ __launch_bounds__(256) void k_loss_final(const float *__restrict__ part, int nblk,
+                                                    int64_t cells, float *__restrict__ loss,
+                                                    float *__restrict__ gb4) {
+    __shared__ double sh[256];
+    double s = 0.0;
+#pragma unroll 4
+    for (int64_t e = threadIdx.x; e < (int64_t)nblk * 4; e += 256) s += part[e];
+    sh[threadIdx.x] = s;
+    __syncthreads();
     const int k = threadIdx.x;
     if (k >= 4) return;
-    double s = 0.0;
-    for (int b = 0; b < nblk; b++) s += part[(size_t)b * 4 + k];
+    s = 0.0;
+#pragma unroll 16
+    for (int g = 0; g < 64; g++) s += sh[g * 4 + k];
     if (k == 0) *loss = static_cast<float>(s / (3.0 * (double)cells));
     else gb4[k - 1] = static_cast<float>(s);
 }
@@ -796,7 +895,7 @@ static int net_alloc(ConvNet &N, int nx, int ny, int nz, bool training) {
         KRY_TRY(N.dz4.alloc(N.cells * 4));
         KRY_TRY(N.dza.alloc(N.cells * 32));
         KRY_TRY(N.dzb.alloc(N.cells * 32));
-        const size_t pw = (size_t)wgrad_blocks(N) * 32 * ((27 * 32 + 15) / 16 * 16);
+        const size_t pw = (size_t)wgrad_blocks(N) * 32 * 27 * 32;
         const size_t pl = (size_t)((N.cells + 255) / 256) * 4;
         const size_t pb = (size_t)conv_blocks(N) * 32;
         KRY_TRY(N.part.alloc(std::max(pw, std::max(pl, pb))));
@@ -855,7 +954,7 @@ static int net_backward_from_dz4(hipStream_t s, ConvNet &N);
 static int net_backward(hipStream_t s, ConvNet &N, const float *target) {
     const int nlb = static_cast<int>((N.cells + 255) / 256);
     hipLaunchKernelGGL(k_loss, dim3(nlb), dim3(256), 0, s, N.cells, N.out.p, target, N.dz4.p, N.part.p);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, s, N.part.p, nlb, N.cells, N.loss.p,
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(256), 0, s, N.part.p, nlb, N.cells, N.loss.p,
                        N.grad.p + NET_OFF[3] + 3 * 32 * 27);
     return net_backward_from_dz4(s, N);
 }
@@ -864,7 +963,7 @@ static int net_backward(hipStream_t s, ConvNet &N, const float *target) {
 static int net_backward_dout(hipStream_t s, ConvNet &N, const float *dout) {
     const int nlb = static_cast<int>((N.cells + 255) / 256);
     hipLaunchKernelGGL(k_outgrad, dim3(nlb), dim3(256), 0, s, N.cells, dout, N.dz4.p, N.part.p);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, s, N.part.p, nlb, N.cells, N.loss.p,
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(256), 0, s, N.part.p, nlb, N.cells, N.loss.p,
                        N.grad.p + NET_OFF[3] + 3 * 32 * 27);
     return net_backward_from_dz4(s, N);
 }
@@ -874,21 +973,20 @@ static int net_backward_dout(hipStream_t s, ConvNet &N, const float *dout) {
 static int net_backward_from_dz4(hipStream_t s, ConvNet &N) {
     const dim3 g(conv_blocks(N)), b(256);
     const int nwg = wgrad_blocks(N);
-    constexpr int NN32 = (27 * 32 + 15) / 16 * 16, NN4 = (27 * 4 + 15) / 16 * 16;
     // layer 4: weight gradient from dz4 (3 channels) and h[2]
     {
         TimedScope t("conv_wgrad", s);
         hipLaunchKernelGGL((k_conv_wgrad<32, 1, 4>), dim3(nwg), b, 0, s, N.nx, N.ny, N.nz, N.dz4.p,
                            N.h[2].p, N.part.p);
-        hipLaunchKernelGGL(k_wgrad_reduce, dim3((3 * 32 * 27 + 255) / 256), dim3(256), 0, s, N.part.p,
-                           nwg, 16, NN32, 32, 32, 3, N.grad.p + NET_OFF[3]);
+        hipLaunchKernelGGL(k_wgrad_reduce, dim3((27 * 32 + 63) / 64, 3), dim3(256), 0, s, N.part.p,
+                           nwg, 16, 32, 32, N.grad.p + NET_OFF[3]);
     }
     // dz3 = conv^T(dz4) * GELU'(z3)
     {
         TimedScope t("conv_dgrad", s);
         hipLaunchKernelGGL((k_conv<4, 2, 2>), g, b, 0, s, N.nx, N.ny, N.nz, 32, N.dz4.p, N.wt[3].p,
                            nullptr, N.dza.p, nullptr, N.z[2].p, N.part.p);
-        hipLaunchKernelGGL(k_bgrad_reduce, dim3(1), dim3(64), 0, s, N.part.p, (int)g.x, 32, 32,
+        hipLaunchKernelGGL(k_bgrad_reduce, dim3(1), dim3(1024), 0, s, N.part.p, (int)g.x,
                            N.grad.p + NET_OFF[2] + 32 * 32 * 27);
     }
     // layers 3 and 2: weight gradient, then the input gradient of the layer below
@@ -898,15 +996,15 @@ static int net_backward_from_dz4(hipStream_t s, ConvNet &N) {
             TimedScope t("conv_wgrad", s);
             hipLaunchKernelGGL((k_conv_wgrad<32, 2, 32>), dim3(nwg), b, 0, s, N.nx, N.ny, N.nz, dcur,
                                N.h[l - 1].p, N.part.p);
-            hipLaunchKernelGGL(k_wgrad_reduce, dim3((32 * 32 * 27 + 255) / 256), dim3(256), 0, s,
-                               N.part.p, nwg, 32, NN32, 32, 32, 32, N.grad.p + NET_OFF[l]);
+            hipLaunchKernelGGL(k_wgrad_reduce, dim3((27 * 32 + 63) / 64, 32), dim3(256), 0, s,
+                               N.part.p, nwg, 32, 32, 32, N.grad.p + NET_OFF[l]);
         }
         {
             TimedScope t("conv_dgrad", s);
             const dim3 gp(conv_persist_blocks(N));
             hipLaunchKernelGGL((k_conv32<2, 2>), gp, b, 0, s, N.nx, N.ny, N.nz, 32, dcur, N.wt[l].p,
                                nullptr, dnext, nullptr, N.z[l - 1].p, N.part.p);
-            hipLaunchKernelGGL(k_bgrad_reduce, dim3(1), dim3(64), 0, s, N.part.p, (int)gp.x, 32, 32,
+            hipLaunchKernelGGL(k_bgrad_reduce, dim3(1), dim3(1024), 0, s, N.part.p, (int)gp.x,
                                N.grad.p + NET_OFF[l - 1] + (l - 1 == 0 ? 32 * 4 * 27 : 32 * 32 * 27));
         }
         std::swap(dcur, dnext);
@@ -916,8 +1014,8 @@ static int net_backward_from_dz4(hipStream_t s, ConvNet &N) {
         TimedScope t("conv_wgrad", s);
         hipLaunchKernelGGL((k_conv_wgrad<4, 2, 32>), dim3(nwg), b, 0, s, N.nx, N.ny, N.nz, dcur, N.h0.p,
                            N.part.p);
-        hipLaunchKernelGGL(k_wgrad_reduce, dim3((32 * 4 * 27 + 255) / 256), dim3(256), 0, s, N.part.p,
-                           nwg, 32, NN4, 4, 4, 32, N.grad.p + NET_OFF[0]);
+        hipLaunchKernelGGL(k_wgrad_reduce, dim3((27 * 4 + 63) / 64, 32), dim3(256), 0, s, N.part.p,
+                           nwg, 32, 4, 4, N.grad.p + NET_OFF[0]);
     }
     KRY_HIP(hipGetLastError());
     return KRY_OK;
