@@ -221,6 +221,17 @@ struct GridTiles {
     const int *qoff = nullptr;
 };
 
+// what a row block of a sweep (ilu.hip) reads of other blocks
+struct RowImports {
+    int ncells = 0;          // LDS cells of a block: its rows, its imports and a zero
+    int imports = 0;
+    // the cells and the list of the elements to import
+    size_t lds_bytes(int bs, size_t value) const {
+        return (size_t)ncells * bs * value + (size_t)imports * bs * sizeof(int);
+    }
+    DBuf<int> off, words;    // blocks + 1 offsets; vector elements by first use
+};
+
 struct IluFactor {
     int bs = 1, nb = 0;
     // timer names of this factor's sweeps: nullptr = the per-kind names of
@@ -234,11 +245,13 @@ struct IluFactor {
     int nlev_f = 0, nlev_b = 0;
     Sell L;                 // forward order, strictly lower blocks
     Sell U;                 // backward order, strictly upper blocks
+    bool rows = false;      // L, U hold row blocks (col: LDS cells), not levels
+    RowImports Limp, Uimp;
     DBuf<double> dinv;      // U_ii^-1 in U slice layout
     DBuf<float> dinvf;
     DBuf<double> y64;       // forward result (sentinel between sweeps)
     DBuf<float> y32;
-    DBuf<int> ctr;          // level sweeps: [0] forward, [1] backward slice counters;
+    DBuf<int> ctr;          // level sweeps: [0] forward, [1] backward slice (block) counters;
                             // grid sweeps: GRID_QUEUES forward, then backward tile counters
     int grid_waves = 0;     // waves launched per sweep
     // grid-tiled sweeps (7-point stencils in natural order)
