@@ -460,37 +460,89 @@ __device__ __forceinline__ double team_sum(double v) {
 template <int CH>
 constexpr int lower_slots() { return CH * (CH + 1) / 2; }
 
-// sums over the entries that read the old iterate: s[t] for the CH rows.
-// Every slot k < K of the group exists (padding holds column -1, value 0),
-// so the loads are unconditional and overlap; a padded slot gathers x[0]
-// and its product is dropped.
-template <int CH, int T>
-__device__ __forceinline__ void rest_sums(int K, int64_t base, int lt, const int *len,
-                                          const int *__restrict__ ecol,
-                                          const double *__restrict__ eval,
-                                          const double *__restrict__ x, double (&s)[CH]) {
+// One smoothing sweep reads a level once (64^3's finest: 22 MB, 4 us), and
+// the coarse levels are small: what bounds all of them is the chain of
+// dependent loads (a group's place, columns, values of x) that each
+// wavefront goes through, about 1 us a link.  Hence the columns and values of
+// KB slots of all CH rows are loaded at once, what the chunk's own solve
+// needs is loaded before them, and a level with few wavefronts gets more
+// lanes per row (team_size).
+// Measured, V-cycle of a 64x64x64 system, chunks of 4: a sweep of the finest
+// level 10 -> 6.8 us, of the coarse ones 9-15 -> 5-9 us (131 072 and 60 504
+// rows of 22 and 36 entries: 12.5 us, 3.5 TB/s of padded rows); the whole
+// cycle 465 -> 310 us, at 24x24x24 250 -> 170 us, at 128x96x64 840 -> 655 us.
+//
+// KB slots, the first one k0, of the sums over the entries that read the old
+// iterate.  Padding holds column -1; it gathers x[0] and drops the product.
+template <int KB, int CH, int T>
+__device__ __forceinline__ void rest_batch(int K, int k0, int64_t base, const int *__restrict__ ecol,
+                                           const double *__restrict__ eval,
+                                           const double *__restrict__ x, double (&s)[CH]) {
+    int j[KB][CH];
+    double a[KB][CH], xv[KB][CH];
 #pragma unroll
-    for (int t = 0; t < CH; t++) s[t] = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < K; k++) {
+    for (int k = 0; k < KB; k++)
 #pragma unroll
         for (int t = 0; t < CH; t++) {
-            const int64_t p = base + ((int64_t)(t * K + k) << 6);
-            const int j = ecol[p];
-            const double a = eval[p];
-            const double xv = x[j < 0 ? 0 : j];
-            s[t] += k * T + lt < len[t] ? a * xv : 0.0;
+            const int64_t p = base + ((int64_t)(t * K + k0 + k) << 6);
+            j[k][t] = ecol[p];
+            a[k][t] = eval[p];
         }
-    }
+#pragma unroll
+    for (int k = 0; k < KB; k++)
+#pragma unroll
+        for (int t = 0; t < CH; t++) xv[k][t] = x[j[k][t] < 0 ? 0 : j[k][t]];
+#pragma unroll
+    for (int k = 0; k < KB; k++)
+#pragma unroll
+        for (int t = 0; t < CH; t++) s[t] += j[k][t] < 0 ? 0.0 : a[k][t] * xv[k][t];
+}
+
+// the sums over all K slots of the group, in slot order
+template <int CH, int T>
+__device__ __forceinline__ void rest_sums(int K, int64_t base, const int *__restrict__ ecol,
+                                          const double *__restrict__ eval,
+                                          const double *__restrict__ x, double (&s)[CH]) {
+    constexpr int KB = CH <= 4 ? 4 : CH == 8 ? 2 : 1;   // at most 16 entries a lane in flight
+#pragma unroll
+    for (int t = 0; t < CH; t++) s[t] = 0.0;
+    int k = 0;
+    for (; k + KB <= K; k += KB) rest_batch<KB, CH, T>(K, k, base, ecol, eval, x, s);
+    if (KB == 4 && K - k == 3) rest_batch<KB == 4 ? 3 : 1, CH, T>(K, k, base, ecol, eval, x, s);
+    else if (KB == 4 && K - k == 2) rest_batch<KB == 4 ? 2 : 1, CH, T>(K, k, base, ecol, eval, x, s);
+    else if (K - k == 1) rest_batch<1, CH, T>(K, k, base, ecol, eval, x, s);
 #pragma unroll
     for (int t = 0; t < CH; t++) s[t] = team_sum<T>(s[t]);
+}
+
+// a chunk's diagonal and lower block, entry e at lw[e * stride]
+template <int CH>
+__device__ __forceinline__ void load_lower(const double *__restrict__ lw, int stride, double (&l)[lower_slots<CH>()]) {
+#pragma unroll
+    for (int e = 0; e < lower_slots<CH>(); e++) l[e] = lw[(int64_t)e * stride];
+}
+
+// the chunk's rows r0 + t < n solved in order for the right-hand side v
+template <int CH>
+__device__ __forceinline__ void solve_chunk(int n, int r0, const double (&l)[lower_slots<CH>()],
+                                            const double (&v)[CH], double *__restrict__ xn) {
+    double xl[CH];
+#pragma unroll
+    for (int t = 0; t < CH; t++) {
+        xl[t] = 0.0;
+        if (r0 + t >= n) continue;
+        double w = v[t];
+#pragma unroll
+        for (int u = 0; u < t; u++) w -= l[t * (t + 1) / 2 + u] * xl[u];
+        xl[t] = w / l[t * (t + 1) / 2 + t];
+        xn[r0 + t] = xl[t];
+    }
 }
 
 // one hybrid Gauss-Seidel sweep: xn from xo (xo == nullptr: from zero)
 template <int CH, int T>
 __global__ __launch_bounds__(256) void k_amg_smooth(int n, int nch, const int64_t *__restrict__ goff,
                                                     const int *__restrict__ gk,
-                                                    const int *__restrict__ rlen,
                                                     const int *__restrict__ ecol,
                                                     const double *__restrict__ eval,
                                                     const double *__restrict__ low,
@@ -499,44 +551,34 @@ __global__ __launch_bounds__(256) void k_amg_smooth(int n, int nch, const int64_
                                                     double *__restrict__ xn) {
     constexpr int CPW = 64 / T, NL = lower_slots<CH>();
     const int gl = blockIdx.x * blockDim.x + threadIdx.x;
-    const int grp = gl >> 6, lane = gl & 63;
+    const int grp = __builtin_amdgcn_readfirstlane(gl >> 6), lane = gl & 63;
     const int c = lane / T, lt = lane % T;
     const int q = grp * CPW + c;                      // this team's chunk
     if (grp * CPW >= nch) return;                     // whole wavefront idle
-    const bool live = q < nch;
+    const bool lead = q < nch && lt == 0;
     const int r0 = q * CH;
-    int len[CH];
+    double l[NL], v[CH], s[CH];
+    if (lead) {
+        load_lower<CH>(low + (int64_t)grp * NL * CPW + c, CPW, l);
 #pragma unroll
-    for (int t = 0; t < CH; t++)
-        len[t] = live && r0 + t < n ? rlen[((int64_t)grp * CH + t) * CPW + c] : 0;
-    double s[CH];
+        for (int t = 0; t < CH; t++) v[t] = r0 + t < n ? b[r0 + t] : 0.0;
+    }
     if (xo) {
-        rest_sums<CH, T>(gk[grp], goff[grp] + lane, lt, len, ecol, eval, xo, s);
+        rest_sums<CH, T>(gk[grp], goff[grp] + lane, ecol, eval, xo, s);
     } else {
 #pragma unroll
         for (int t = 0; t < CH; t++) s[t] = 0.0;
     }
-    if (!live || lt != 0) return;
-    const double *lw = low + (int64_t)grp * NL * CPW + c;
-    double xl[CH];
+    if (!lead) return;
 #pragma unroll
-    for (int t = 0; t < CH; t++) {
-        const int r = r0 + t;
-        xl[t] = 0.0;
-        if (r >= n) continue;
-        double v = b[r] - s[t];
-#pragma unroll
-        for (int u = 0; u < t; u++) v -= lw[(t * (t + 1) / 2 + u) * CPW] * xl[u];
-        xl[t] = v / lw[(t * (t + 1) / 2 + t) * CPW];
-        xn[r] = xl[t];
-    }
+    for (int t = 0; t < CH; t++) v[t] -= s[t];
+    solve_chunk<CH>(n, r0, l, v, xn);
 }
 
 // r = b - A x in the same layout
 template <int CH, int T>
 __global__ __launch_bounds__(256) void k_amg_resid(int n, int nch, const int64_t *__restrict__ goff,
                                                    const int *__restrict__ gk,
-                                                   const int *__restrict__ rlen,
                                                    const int *__restrict__ ecol,
                                                    const double *__restrict__ eval,
                                                    const double *__restrict__ low,
@@ -545,53 +587,130 @@ __global__ __launch_bounds__(256) void k_amg_resid(int n, int nch, const int64_t
                                                    double *__restrict__ r) {
     constexpr int CPW = 64 / T, NL = lower_slots<CH>();
     const int gl = blockIdx.x * blockDim.x + threadIdx.x;
-    const int grp = gl >> 6, lane = gl & 63;
+    const int grp = __builtin_amdgcn_readfirstlane(gl >> 6), lane = gl & 63;
     const int c = lane / T, lt = lane % T;
     const int q = grp * CPW + c;
     if (grp * CPW >= nch) return;
-    const bool live = q < nch;
+    const bool lead = q < nch && lt == 0;
     const int r0 = q * CH;
-    int len[CH];
+    double l[NL], v[CH], xl[CH], s[CH];
+    if (lead) {
+        load_lower<CH>(low + (int64_t)grp * NL * CPW + c, CPW, l);
 #pragma unroll
-    for (int t = 0; t < CH; t++)
-        len[t] = live && r0 + t < n ? rlen[((int64_t)grp * CH + t) * CPW + c] : 0;
-    double s[CH];
-    rest_sums<CH, T>(gk[grp], goff[grp] + lane, lt, len, ecol, eval, x, s);
-    if (!live || lt != 0) return;
-    const double *lw = low + (int64_t)grp * NL * CPW + c;
+        for (int t = 0; t < CH; t++) {
+            v[t] = r0 + t < n ? b[r0 + t] : 0.0;
+            xl[t] = r0 + t < n ? x[r0 + t] : 0.0;
+        }
+    }
+    rest_sums<CH, T>(gk[grp], goff[grp] + lane, ecol, eval, x, s);
+    if (!lead) return;
 #pragma unroll
     for (int t = 0; t < CH; t++) {
-        const int row = r0 + t;
-        if (row >= n) continue;
-        double v = s[t];
+        if (r0 + t >= n) continue;
+        double w = s[t];
 #pragma unroll
-        for (int u = 0; u <= t; u++) v += lw[(t * (t + 1) / 2 + u) * CPW] * x[r0 + u];
-        r[row] = b[row] - v;
+        for (int u = 0; u <= t; u++) w += l[t * (t + 1) / 2 + u] * xl[u];
+        r[r0 + t] = v[t] - w;
     }
 }
 
-// y = M x (add = 0) or y += M x (add = 1), one row per thread
-__global__ __launch_bounds__(256) void k_amg_csr(int rows, const int *__restrict__ rp,
-                                                 const int *__restrict__ ci,
-                                                 const double *__restrict__ v,
-                                                 const double *__restrict__ x,
-                                                 double *__restrict__ y, int add) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= rows) return;
-    double s = 0.0;
-    for (int q = rp[i]; q < rp[i + 1]; q++) s += v[q] * x[ci[q]];
-    y[i] = add ? y[i] + s : s;
+// b = R r on the next level (rows, nch: its rows and chunks) and, low !=
+// nullptr, that level's first smoothing sweep: from zero it reads only the
+// chunk's own b, so the team that has summed a chunk's rows solves them too.
+// The lower blocks lie cpw chunks to a group.
+template <int CH, int T>
+__global__ __launch_bounds__(256) void k_amg_restrict(int rows, int nch, const int *__restrict__ rp,
+                                                      const int *__restrict__ ci,
+                                                      const double *__restrict__ pv,
+                                                      const double *__restrict__ r,
+                                                      double *__restrict__ b, int cpw,
+                                                      const double *__restrict__ low,
+                                                      double *__restrict__ xn) {
+    constexpr int NL = lower_slots<CH>();
+    const int gl = blockIdx.x * blockDim.x + threadIdx.x;
+    const int q = gl / T, lt = gl % T, r0 = q * CH;
+    if (q >= nch) return;                             // whole teams only
+    int at[CH], end[CH];
+    double s[CH], l[NL];
+#pragma unroll
+    for (int t = 0; t < CH; t++) {
+        const int row = r0 + t < rows ? r0 + t : rows;
+        at[t] = rp[row] + lt;
+        end[t] = r0 + t < rows ? rp[row + 1] : 0;
+    }
+    if (low && lt == 0) load_lower<CH>(low + (int64_t)(q / cpw) * NL * cpw + q % cpw, cpw, l);
+    {   // the first entry of every row at once
+        int j[CH];
+        double a[CH];
+#pragma unroll
+        for (int t = 0; t < CH; t++) {
+            const bool have = at[t] < end[t];
+            j[t] = have ? ci[at[t]] : -1;
+            a[t] = have ? pv[at[t]] : 0.0;
+        }
+#pragma unroll
+        for (int t = 0; t < CH; t++) s[t] = j[t] >= 0 ? a[t] * r[j[t]] : 0.0;
+    }
+#pragma unroll
+    for (int t = 0; t < CH; t++)
+        for (int p = at[t] + T; p < end[t]; p += T) s[t] += pv[p] * r[ci[p]];
+#pragma unroll
+    for (int t = 0; t < CH; t++) s[t] = team_sum<T>(s[t]);
+    if (lt != 0) return;
+#pragma unroll
+    for (int t = 0; t < CH; t++)
+        if (r0 + t < rows) b[r0 + t] = s[t];
+    if (low) solve_chunk<CH>(rows, r0, l, s, xn);
 }
 
-// x = Minv b, one wavefront per row of the dense inverse
+// x += P xc, one row per thread, PB entries at once (most rows have no more)
+__global__ __launch_bounds__(256) void k_amg_prolong(int rows, const int *__restrict__ rp,
+                                                     const int *__restrict__ ci,
+                                                     const double *__restrict__ pv,
+                                                     const double *__restrict__ xc,
+                                                     double *__restrict__ x) {
+    constexpr int PB = 4;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= rows) return;
+    const int end = rp[i + 1];
+    const double xi = x[i];
+    double s = 0.0;
+    for (int q = rp[i]; q < end; q += PB) {
+        int j[PB];
+        double a[PB];
+#pragma unroll
+        for (int e = 0; e < PB; e++) {
+            j[e] = q + e < end ? ci[q + e] : -1;
+            a[e] = q + e < end ? pv[q + e] : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < PB; e++)
+            if (j[e] >= 0) s += a[e] * xc[j[e]];
+    }
+    x[i] = xi + s;
+}
+
+// x = Minv b, one wavefront per row of the dense inverse, eight of its 64
+// columns at once
 __global__ __launch_bounds__(256) void k_amg_dense(int n, const double *__restrict__ Minv,
                                                    const double *__restrict__ b,
                                                    double *__restrict__ x) {
+    constexpr int DB = 8;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= n) return;
     const double *m = Minv + (int64_t)row * n;
     double s = 0.0;
-    for (int j = lane; j < n; j += 64) s += m[j] * b[j];
+    for (int j = lane; j < n; j += 64 * DB) {
+        double a[DB], v[DB];
+#pragma unroll
+        for (int e = 0; e < DB; e++) {
+            const bool in = j + 64 * e < n;
+            a[e] = in ? m[j + 64 * e] : 0.0;
+            v[e] = in ? b[j + 64 * e] : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < DB; e++) s += a[e] * v[e];
+    }
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
     if (lane == 0) x[row] = s;
 }
@@ -681,11 +800,17 @@ constexpr int AMG_DENSE_MAX = 8192;
 
 }  // namespace
 
-// team size for a level: about 4 entries of a row per lane
-static int team_size(const AmgCsr &A) {
-    const double mean = A.n ? (double)A.ci.size() / A.n : 0.0;
+// Team size for the rows of M, ch of them to a chunk: about 4 entries of a
+// row per lane, which pads short rows least; more lanes, down to one entry
+// per lane, while there are fewer than 2048 wavefronts, eight to a CU (at
+// 64x64x64: an apply 342 us, with 8192 wavefronts 387 us, the finest levels
+// then reading more padding; without more lanes 409 us).
+static int team_size(const AmgCsr &M, int ch) {
+    const double mean = M.n ? (double)M.ci.size() / M.n : 0.0;
+    const int64_t nch = (M.n + ch - 1) / ch;
     int T = 1;
     while (T < 32 && mean > 4.0 * T) T *= 2;
+    while (T < 32 && mean > T && nch * T / 64 < 2048) T *= 2;
     return T;
 }
 
@@ -696,11 +821,11 @@ struct EllHost {
     int n = 0, nch = 0, team = 1, ngrp = 0;
     std::vector<int64_t> goff;
     std::vector<int> gk;
-    HVec<int> rlen, ecol;
+    HVec<int> ecol;
     HVec<double> eval, low;
 };
 static void build_ell(const AmgCsr &A, int ch, EllHost &E) {
-    const int n = A.n, T = team_size(A), cpw = 64 / T, nl = ch * (ch + 1) / 2;
+    const int n = A.n, T = team_size(A, ch), cpw = 64 / T, nl = ch * (ch + 1) / 2;
     const int nch = (n + ch - 1) / ch, ngrp = (nch + cpw - 1) / cpw;
     const int gr = cpw * ch;   // rows per group
     // an entry (r, j) is "lower" when j lies in r's chunk at or before r
@@ -725,7 +850,6 @@ static void build_ell(const AmgCsr &A, int ch, EllHost &E) {
     }, 64);
     for (int g = 0; g < ngrp; g++) E.goff[g + 1] = E.goff[g] + (int64_t)ch * E.gk[g] * 64;
     const size_t ne = std::max<int64_t>(E.goff[ngrp], 1);
-    E.rlen.resize((size_t)ngrp * ch * cpw);
     E.ecol.resize(ne);
     E.eval.resize(ne);
     E.low.resize((size_t)ngrp * nl * cpw);
@@ -736,7 +860,6 @@ static void build_ell(const AmgCsr &A, int ch, EllHost &E) {
     for_ranges(ngrp, nw, [&](int glo, int ghi, int) {
         std::fill(E.ecol.begin() + E.goff[glo], E.ecol.begin() + E.goff[ghi], -1);
         std::fill(E.eval.begin() + E.goff[glo], E.eval.begin() + E.goff[ghi], 0.0);
-        std::fill(E.rlen.begin() + (size_t)glo * ch * cpw, E.rlen.begin() + (size_t)ghi * ch * cpw, 0);
         std::fill(E.low.begin() + (size_t)glo * nl * cpw, E.low.begin() + (size_t)ghi * nl * cpw, 0.0);
         for (int r = glo * gr; r < std::min(n, ghi * gr); r++) {
             const int q = r / ch, t = r % ch, g = q / cpw, c = q % cpw;
@@ -752,7 +875,6 @@ static void build_ell(const AmgCsr &A, int ch, EllHost &E) {
                 E.eval[p] = A.v[k];
                 e++;
             }
-            E.rlen[((size_t)g * ch + t) * cpw + c] = e;
         }
     }, 64);
 }
@@ -766,14 +888,12 @@ static int upload_level(hipStream_t s, const AmgCsr &A, int ch, AmgLevel &L) {
     L.team = E.team;
     KRY_TRY(L.goff.alloc(ngrp));
     KRY_TRY(L.gk.alloc(ngrp));
-    KRY_TRY(L.rlen.alloc(E.rlen.size()));
     KRY_TRY(L.ecol.alloc(E.ecol.size()));
     KRY_TRY(L.eval.alloc(E.eval.size()));
     KRY_TRY(L.low.alloc(E.low.size()));
     KRY_HIP(hipMemcpyAsync(L.low.p, E.low.data(), sizeof(double) * E.low.size(), hipMemcpyHostToDevice, s));
     KRY_HIP(hipMemcpyAsync(L.goff.p, E.goff.data(), sizeof(int64_t) * ngrp, hipMemcpyHostToDevice, s));
     KRY_HIP(hipMemcpyAsync(L.gk.p, E.gk.data(), sizeof(int) * ngrp, hipMemcpyHostToDevice, s));
-    KRY_HIP(hipMemcpyAsync(L.rlen.p, E.rlen.data(), sizeof(int) * E.rlen.size(), hipMemcpyHostToDevice, s));
     KRY_HIP(hipMemcpyAsync(L.ecol.p, E.ecol.data(), sizeof(int) * E.ecol.size(), hipMemcpyHostToDevice, s));
     KRY_HIP(hipMemcpyAsync(L.eval.p, E.eval.data(), sizeof(double) * E.eval.size(), hipMemcpyHostToDevice, s));
     L.ell_bytes = (int64_t)E.ecol.size() * (sizeof(int) + sizeof(double));
@@ -853,7 +973,9 @@ int amg_setup(hipStream_t s, int n, const int *h_rowptr, const int *h_col, const
         KRY_TRY(upload_level(s, H.A, ch, L));
         L.nc = H.P.m;
         KRY_TRY(upload_csr(s, H.P, L.prp, L.pci, L.pv));
-        KRY_TRY(upload_csr(s, transpose_csr(H.P), L.rrp, L.rci, L.rv));
+        const AmgCsr R = transpose_csr(H.P);
+        KRY_TRY(upload_csr(s, R, L.rrp, L.rci, L.rv));
+        L.rteam = team_size(R, ch);
     }
     // dense inverse of the coarsest matrix
     {
@@ -888,46 +1010,57 @@ int amg_setup(hipStream_t s, int n, const int *h_rowptr, const int *h_col, const
     return KRY_OK;
 }
 
-// lanes of a level's smoother and residual launches
-static dim3 amg_grid(const AmgLevel &L) {
-    const int cpw = 64 / L.team;
-    const int64_t waves = (L.nch + cpw - 1) / cpw;
+// workgroups for nch chunks with a team of T lanes each
+static dim3 team_grid(int nch, int T) {
+    const int64_t waves = ((int64_t)nch + 64 / T - 1) / (64 / T);
     return dim3((unsigned)((waves + 3) / 4));
 }
 
+enum class LevelOp { smooth, resid, restrict_ };
+
+// smoothing sweep (xin -> out) or residual (of xin, -> out) on level L;
+// restrict_: xin = L's residual to the right-hand side b of the next level N
+// and, N smoothed at all, N's first sweep from zero to out
+struct LevelArgs {
+    const AmgLevel *L, *N;
+    const double *b, *xin;
+    double *bout, *out;
+};
+
 template <int CH, int T>
-static void launch_pair(hipStream_t s, bool sm, const AmgLevel &L, const double *b,
-                        const double *xin, double *out) {
-    if (sm)
-        hipLaunchKernelGGL((k_amg_smooth<CH, T>), amg_grid(L), dim3(256), 0, s, L.n, L.nch, L.goff.p,
-                           L.gk.p, L.rlen.p, L.ecol.p, L.eval.p, L.low.p, b, xin, out);
+static void launch_level(hipStream_t s, LevelOp op, const LevelArgs &a) {
+    const AmgLevel &L = *a.L;
+    if (op == LevelOp::smooth)
+        hipLaunchKernelGGL((k_amg_smooth<CH, T>), team_grid(L.nch, T), dim3(256), 0, s, L.n, L.nch,
+                           L.goff.p, L.gk.p, L.ecol.p, L.eval.p, L.low.p, a.b, a.xin, a.out);
+    else if (op == LevelOp::resid)
+        hipLaunchKernelGGL((k_amg_resid<CH, T>), team_grid(L.nch, T), dim3(256), 0, s, L.n, L.nch,
+                           L.goff.p, L.gk.p, L.ecol.p, L.eval.p, L.low.p, a.b, a.xin, a.out);
     else
-        hipLaunchKernelGGL((k_amg_resid<CH, T>), amg_grid(L), dim3(256), 0, s, L.n, L.nch, L.goff.p,
-                           L.gk.p, L.rlen.p, L.ecol.p, L.eval.p, L.low.p, b, xin, out);
+        hipLaunchKernelGGL((k_amg_restrict<CH, T>), team_grid((L.nc + CH - 1) / CH, T), dim3(256), 0, s,
+                           L.nc, (L.nc + CH - 1) / CH, L.rrp.p, L.rci.p, L.rv.p, a.xin, a.bout,
+                           64 / a.N->team, a.out ? a.N->low.p : nullptr, a.out);
 }
 
 template <int CH>
-static void launch_team(hipStream_t s, bool sm, const AmgLevel &L, const double *b,
-                        const double *xin, double *out) {
-    switch (L.team) {
-    case 1: launch_pair<CH, 1>(s, sm, L, b, xin, out); break;
-    case 2: launch_pair<CH, 2>(s, sm, L, b, xin, out); break;
-    case 4: launch_pair<CH, 4>(s, sm, L, b, xin, out); break;
-    case 8: launch_pair<CH, 8>(s, sm, L, b, xin, out); break;
-    case 16: launch_pair<CH, 16>(s, sm, L, b, xin, out); break;
-    default: launch_pair<CH, 32>(s, sm, L, b, xin, out); break;
+static void launch_team(hipStream_t s, LevelOp op, const LevelArgs &a) {
+    switch (op == LevelOp::restrict_ ? a.L->rteam : a.L->team) {
+    case 1: launch_level<CH, 1>(s, op, a); break;
+    case 2: launch_level<CH, 2>(s, op, a); break;
+    case 4: launch_level<CH, 4>(s, op, a); break;
+    case 8: launch_level<CH, 8>(s, op, a); break;
+    case 16: launch_level<CH, 16>(s, op, a); break;
+    default: launch_level<CH, 32>(s, op, a); break;
     }
 }
 
-// smoothing sweep (sm) or residual on level L
-static void level_op(hipStream_t s, int ch, bool sm, const AmgLevel &L, const double *b,
-                     const double *xin, double *out) {
+static void level_op(hipStream_t s, int ch, LevelOp op, const LevelArgs &a) {
     switch (ch) {
-    case 1: launch_team<1>(s, sm, L, b, xin, out); break;
-    case 2: launch_team<2>(s, sm, L, b, xin, out); break;
-    case 4: launch_team<4>(s, sm, L, b, xin, out); break;
-    case 8: launch_team<8>(s, sm, L, b, xin, out); break;
-    default: launch_team<16>(s, sm, L, b, xin, out); break;
+    case 1: launch_team<1>(s, op, a); break;
+    case 2: launch_team<2>(s, op, a); break;
+    case 4: launch_team<4>(s, op, a); break;
+    case 8: launch_team<8>(s, op, a); break;
+    default: launch_team<16>(s, op, a); break;
     }
 }
 
@@ -946,18 +1079,22 @@ int amg_apply(hipStream_t s, AmgPC &M, const double *b, double *x, int *d_err) {
     }
     // level 0 works in x itself: 2 ns sweeps (an even number of swaps) end there
     cur[0] = x;
-    auto sweeps = [&](int l, bool from_zero) {
-        for (int k = 0; k < ns; k++) {
-            level_op(s, ch, true, *M.lev[l], bl[l], from_zero && k == 0 ? nullptr : cur[l], alt[l]);
+    // sweeps k0 .. ns - 1; sweep 0 of the way down starts from zero
+    auto sweeps = [&](int l, int k0, bool from_zero) {
+        for (int k = k0; k < ns; k++) {
+            level_op(s, ch, LevelOp::smooth,
+                     {M.lev[l].get(), nullptr, bl[l], from_zero && k == 0 ? nullptr : cur[l], nullptr, alt[l]});
             std::swap(cur[l], alt[l]);
         }
     };
     for (int l = 0; l < nlev - 1; l++) {
-        AmgLevel &L = *M.lev[l];
-        sweeps(l, true);
-        level_op(s, ch, false, L, bl[l], cur[l], L.r.p);
-        hipLaunchKernelGGL(k_amg_csr, dim3((L.nc + 255) / 256), blk, 0, s, L.nc, L.rrp.p, L.rci.p,
-                           L.rv.p, L.r.p, M.lev[l + 1]->b.p, 0);
+        AmgLevel &L = *M.lev[l], &N = *M.lev[l + 1];
+        sweeps(l, l == 0 ? 0 : 1, true);
+        level_op(s, ch, LevelOp::resid, {&L, nullptr, bl[l], cur[l], nullptr, L.r.p});
+        const bool smoothed = l + 1 < nlev - 1;
+        level_op(s, ch, LevelOp::restrict_,
+                 {&L, &N, nullptr, L.r.p, N.b.p, smoothed ? alt[l + 1] : nullptr});
+        if (smoothed) std::swap(cur[l + 1], alt[l + 1]);
     }
     {
         AmgLevel &C = *M.lev[nlev - 1];
@@ -966,9 +1103,9 @@ int amg_apply(hipStream_t s, AmgPC &M, const double *b, double *x, int *d_err) {
     }
     for (int l = nlev - 2; l >= 0; l--) {
         AmgLevel &L = *M.lev[l];
-        hipLaunchKernelGGL(k_amg_csr, dim3((L.n + 255) / 256), blk, 0, s, L.n, L.prp.p, L.pci.p,
-                           L.pv.p, cur[l + 1], cur[l], 1);
-        sweeps(l, false);
+        hipLaunchKernelGGL(k_amg_prolong, dim3((L.n + 255) / 256), blk, 0, s, L.n, L.prp.p, L.pci.p,
+                           L.pv.p, cur[l + 1], cur[l]);
+        sweeps(l, 0, false);
     }
     if (cur[0] != x)
         KRY_HIP(hipMemcpyAsync(x, cur[0], sizeof(double) * M.lev[0]->n, hipMemcpyDeviceToDevice, s));

@@ -338,10 +338,11 @@ struct AmgLevelHost {           // A_l, its C/F splitting and P_l (not on the co
     AmgCsr P;
 };
 struct AmgLevel {
-    int n = 0, nc = 0, nch = 0, team = 1;
+    int n = 0, nc = 0, nch = 0;
+    int team = 1, rteam = 1;     // lanes per chunk: smoother and residual, restriction
     int64_t ell_bytes = 0;
     DBuf<int64_t> goff;         // chunk-interleaved rows of A_l, per wavefront group
-    DBuf<int> gk, rlen, ecol;
+    DBuf<int> gk, ecol;
     DBuf<double> eval, low;     // low: each chunk's diagonal and lower block
     DBuf<int> prp, pci, rrp, rci;   // P_l and R_l = P_l^T
     DBuf<double> pv, rv;
