@@ -49,7 +49,7 @@ enum {
 // coefficients of its second pass (sa, dv) and the sums of its first (ab)
 struct SmallLayout {
     int m;
-    size_t H, cs, sn, g, y, h1, h2, sc, Hu, hp, sa, dv, ab, total;
+    size_t H, cs, sn, g, y, h1, h2, sc, Hu, hp, sa, dv, total;
     explicit SmallLayout(int m_) : m(m_) {
         H = 0;
         cs = H + (size_t)(m + 1) * m;
@@ -63,8 +63,7 @@ struct SmallLayout {
         hp = Hu + (size_t)(m + 1) * m;
         sa = hp + MAXCOL + 1;
         dv = sa + MAXCOL;
-        ab = dv + MAXCOL + 1;
-        total = ab + 2 * MAXCOL;
+        total = dv + MAXCOL + 1;
     }
 };
 
@@ -327,34 +326,44 @@ __global__ __launch_bounds__(256) void k_cgs_update_scale(int n, const double *_
 // Hessenberg column j from col[0..j] = h1 + h2 and h_{j+1,j} = hn: apply the
 // previous Givens rotations, form rotation j, update g and the residual
 // estimate |g_{j+1}| (one thread; cs, sn = the previous rotations, staged
-// in LDS by the caller)
-__device__ void arnoldi_column(double *small, const SmallLayout &L, int j, int m, double *col,
-                               const double *cs, const double *sn, double hn) {
+// in LDS by the caller); host, if not null, is where the host reads
+// h_{j+1,j} and the estimate (pinned memory, written from here: a copy of 24
+// bytes on the stream took 15 us of every step)
+constexpr int HOST_HN = 0, HOST_EST = 1;
+__device__ void arnoldi_column(double *__restrict__ small, const SmallLayout &L, int j, int m,
+                               const double *col, const double *cs, const double *sn, double hn,
+                               double *host) {
     double *H = small + L.H + (size_t)j * (m + 1), *g = small + L.g, *sc = small + L.sc;
-    col[j + 1] = hn;
+    const double gj = g[j];
     sc[SC_HN] = hn;
     sc[SC_INVHN] = hn != 0.0 ? 1.0 / hn : 0.0;
     sc[SC_BREAK] = hn == 0.0 ? 1.0 : 0.0;
+    double head = col[0];
+#pragma unroll 4
     for (int k = 0; k < j; k++) {
-        const double t = cs[k] * col[k] + sn[k] * col[k + 1];
-        col[k + 1] = -sn[k] * col[k] + cs[k] * col[k + 1];
-        col[k] = t;
+        const double next = col[k + 1];
+        H[k] = cs[k] * head + sn[k] * next;
+        head = -sn[k] * head + cs[k] * next;
     }
-    const double r = hypot(col[j], col[j + 1]);
+    const double r = hypot(head, hn);
     double c = 1.0, sv = 0.0;
     if (r != 0.0) {
-        c = col[j] / r;
-        sv = col[j + 1] / r;
+        c = head / r;
+        sv = hn / r;
     }
     small[L.cs + j] = c;
     small[L.sn + j] = sv;
-    col[j] = r;
-    col[j + 1] = 0.0;
-    for (int k = 0; k <= j + 1; k++) H[k] = col[k];
-    const double gj = g[j];
+    H[j] = r;
+    H[j + 1] = 0.0;
     g[j + 1] = -sv * gj;
     g[j] = c * gj;
-    sc[SC_EST] = fabs(sv * gj);
+    const double est = fabs(sv * gj);
+    sc[SC_EST] = est;
+    if (host) {
+        __hip_atomic_store(host + HOST_HN, hn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(host + HOST_EST, est, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): there before the kernel ends
+    }
 }
 
 // After pass 3 of a step that asked for an explicit norm: every block sums
@@ -367,7 +376,8 @@ __device__ void arnoldi_column(double *small, const SmallLayout &L, int j, int m
 // breakdown: w lies in span V).  Exits at once on the usual path.
 __global__ __launch_bounds__(256) void k_cgs_renorm(int n, const double *__restrict__ partial,
                                                     int nblocks, double *__restrict__ w, int j,
-                                                    int m, double *small, SmallLayout L) {
+                                                    int m, double *small, SmallLayout L,
+                                                    double *host) {
     __shared__ double red[4];
     __shared__ double hsh;
     __shared__ double col[MAXCOL + 1], cs[MAXCOL], sn[MAXCOL];
@@ -391,7 +401,7 @@ __global__ __launch_bounds__(256) void k_cgs_renorm(int n, const double *__restr
         sn[threadIdx.x] = small[L.sn + threadIdx.x];
     }
     __syncthreads();
-    if (threadIdx.x == 0) arnoldi_column(small, L, j, m, col, cs, sn, hn);
+    if (threadIdx.x == 0) arnoldi_column(small, L, j, m, col, cs, sn, hn, host);
 }
 
 // Finish Arnoldi step j in one block: h2 from pass 2's partials (columns
@@ -405,7 +415,7 @@ __global__ __launch_bounds__(256) void k_cgs_renorm(int n, const double *__restr
 template <int MAXC>
 __global__ __launch_bounds__(1024) void k_arnoldi_finish(const double *__restrict__ partial,
                                                          int nblocks, int j, int m, double *small,
-                                                         SmallLayout L) {
+                                                         SmallLayout L, double *host) {
     constexpr int NT = 1024, G = NT / MAXC;
     __shared__ double lds[NT];
     __shared__ double red[NT / 64];
@@ -439,7 +449,7 @@ __global__ __launch_bounds__(1024) void k_arnoldi_finish(const double *__restric
     for (int k = 0; k <= j; k++) h2sq += h2s[k] * h2s[k];
     if (h2sq <= 0.5 * s) {
         sc[SC_RENORM] = 0.0;
-        arnoldi_column(small, L, j, m, col, cs, sn, sqrt(s - h2sq));
+        arnoldi_column(small, L, j, m, col, cs, sn, sqrt(s - h2sq), host);
     } else {
         // ||w||^2 = ||h1||^2 + ||w - V h1||^2 for the breakdown test
         double h1sq = 0.0;
@@ -629,18 +639,64 @@ __global__ __launch_bounds__(256) void k_dcgs_update(int n, double *V, int64_t l
     if (threadIdx.x == 0) partial[(size_t)blockIdx.x * MAXCOL] = nacc;
 }
 
-// finish of step j (one wavefront) from pass A's sums ab = [a_0..a_j,
-// b_0..b_j]: column j - 1 of H made final (unrotated into Hu, rotated into
-// H, with its Givens rotation and g, replacing its provisional form), the
-// coefficients sa, cu of v_j, the provisional column j (hp) and d of u'.
-// Lane k holds the k-th entries (j <= 31 < 64); the rotations run on lane 0
-// over LDS copies.
-__global__ __launch_bounds__(64) void k_dcgs_finish(int j, int m, double *small, SmallLayout L) {
-    __shared__ double col[MAXCOL + 1], cs[MAXCOL], sn[MAXCOL], sh[MAXCOL];
-    const int k = threadIdx.x;
-    double *sc = small + L.sc, *Hu = small + L.Hu, *hp = small + L.hp;
-    const double *a = small + L.ab, *b = a + (j + 1);
+// finish of step j (one workgroup) from pass A's partials: the sums a_0..a_j,
+// b_0..b_j (thread t takes sum t % MAXS and the blocks t / MAXS (mod
+// NT / MAXS), the groups are added in order); then, in the first wavefront,
+// column j - 1 of H made final (unrotated into Hu, rotated into H, with its
+// Givens rotation and g, replacing its provisional form), the coefficients
+// sa, cu of v_j, the provisional column j (hp) and d of u'.  Lane k holds the
+// k-th entries (j <= 31 < 64); the rotations run on lane 0.
+//
+// A chain of small steps, bound by their latency: what is read of small is
+// in LDS before the sums are done.  64 x 3 x 8 partials, j = 29: 7 us, the
+// sums and the finish as launches of their own 5 + 7 us.
+template <int MAXS>
+__global__ __launch_bounds__(1024) void k_dcgs_finish(const double *__restrict__ partial, int nblocks,
+                                                      int j, int m, double *small, SmallLayout L) {
+    constexpr int NT = 1024, G = NT / MAXS, MAXJ = MAXS / 2;
+    __shared__ double lds[NT];
+    __shared__ double ab[MAXS];
+    __shared__ double Hs[MAXJ][MAXJ + 1];   // unrotated columns q < j of H
+    __shared__ double col[MAXJ + 1], cs[MAXJ], sn[MAXJ], sh[MAXJ], hps[MAXJ + 1];
+    double *sc = small + L.sc, *Hu = small + L.Hu;
     const double eta = sc[SC_ETA];
+    {
+        const int q = threadIdx.x % MAXS, g = threadIdx.x / MAXS;
+        double s = 0.0;
+        if (q < 2 * (j + 1)) {
+            int b = g;
+            for (; b + 3 * G < nblocks; b += 4 * G) {
+                const double a0 = partial[(size_t)b * MAXCOL + q];
+                const double a1 = partial[(size_t)(b + G) * MAXCOL + q];
+                const double a2 = partial[(size_t)(b + 2 * G) * MAXCOL + q];
+                const double a3 = partial[(size_t)(b + 3 * G) * MAXCOL + q];
+                s += a0;
+                s += a1;
+                s += a2;
+                s += a3;
+            }
+            for (; b < nblocks; b += G) s += partial[(size_t)b * MAXCOL + q];
+        }
+        lds[threadIdx.x] = s;
+        if ((int)threadIdx.x <= j) hps[threadIdx.x] = small[L.hp + threadIdx.x];
+        if ((int)threadIdx.x < j) {
+            cs[threadIdx.x] = small[L.cs + threadIdx.x];
+            sn[threadIdx.x] = small[L.sn + threadIdx.x];
+        }
+        for (int e = threadIdx.x; e < (j - 1) * MAXJ; e += NT)
+            if (e % MAXJ <= j) Hs[e / MAXJ][e % MAXJ] = Hu[(size_t)(e / MAXJ) * (m + 1) + e % MAXJ];
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < 2 * (j + 1)) {
+        double r = 0.0;
+#pragma unroll 8
+        for (int g = 0; g < G; g++) r += lds[g * MAXS + threadIdx.x];
+        ab[threadIdx.x] = r;
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int k = threadIdx.x;
+    const double *a = ab, *b = ab + (j + 1);
     const bool eok = eta > 0.0 && isfinite(eta);
     const double sk = eok && k < j ? a[k] / eta : 0.0;
     const double ss = wave_sum(sk * sk);
@@ -649,23 +705,18 @@ __global__ __launch_bounds__(64) void k_dcgs_finish(int j, int m, double *small,
     const bool ok = eok && isfinite(al2) && al2 > 0.5 * sig;
     const double al = ok ? sqrt(al2) : 0.0;
     const double s_k = ok ? sk : 0.0;
-    if (k < j) {
-        sh[k] = s_k;
-        cs[k] = small[L.cs + k];
-        sn[k] = small[L.sn + k];
+    if (k < j) sh[k] = s_k;
+    if (j >= 1 && k <= j) {
+        const double c = k < j ? hps[k] + (ok ? eta * s_k : 0.0) : ok ? eta * al : 0.0;
+        col[k] = Hs[j - 1][k] = c;
+        Hu[(size_t)(j - 1) * (m + 1) + k] = c;
     }
-    if (j >= 1) {
-        if (k < j) col[k] = hp[k] + (ok ? eta * s_k : 0.0);
-        if (k == j) col[j] = ok ? eta * al : 0.0;
-        __syncthreads();
-        if (k <= j) Hu[(size_t)(j - 1) * (m + 1) + k] = col[k];
-        __syncthreads();
-        if (k == 0) {
-            small[L.g + j - 1] = sc[SC_GSAVE];   // g_{j-1} before the provisional rotation
-            arnoldi_column(small, L, j - 1, m, col, cs, sn, col[j]);
-        }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (j >= 1 && k == 0) {
+        small[L.g + j - 1] = sc[SC_GSAVE];   // g_{j-1} before the provisional rotation
+        arnoldi_column(small, L, j - 1, m, col, cs, sn, col[j], nullptr);
     }
-    __syncthreads();
     if (k == 0) sc[SC_CU] = ok ? 1.0 / (eta * al) : 0.0;
     if (k < j) small[L.sa + k] = ok ? s_k / al : 0.0;
     if (!ok) {
@@ -678,7 +729,7 @@ __global__ __launch_bounds__(64) void k_dcgs_finish(int j, int m, double *small,
     double h = 0.0;
     if (k <= j) {
         double hs = 0.0;   // (H s)_k over the final columns q >= k - 1
-        for (int q = k > 0 ? k - 1 : 0; q < j; q++) hs += Hu[(size_t)q * (m + 1) + k] * sh[q];
+        for (int q = k > 0 ? k - 1 : 0; q < j; q++) hs += Hs[q][k] * sh[q];
         h = ((k < j ? b[k] : bwj) / eta - hs) / al;
         small[L.hp + k] = h;
         small[L.dv + k] = hs / al + h;
@@ -691,7 +742,8 @@ __global__ __launch_bounds__(64) void k_dcgs_finish(int j, int m, double *small,
 // provisional column j rotated into H (rotation j, g, residual estimate,
 // h_{j+1,j} and its inverse in the step's scalars), g_j saved first
 __global__ __launch_bounds__(256) void k_dcgs_norm(const double *__restrict__ partial, int nblocks,
-                                                   int j, int m, double *small, SmallLayout L) {
+                                                   int j, int m, double *small, SmallLayout L,
+                                                   double *host) {
     __shared__ double red[4];
     __shared__ double col[MAXCOL + 1], cs[MAXCOL], sn[MAXCOL];
     double s = 0.0;
@@ -708,7 +760,7 @@ __global__ __launch_bounds__(256) void k_dcgs_norm(const double *__restrict__ pa
     if (eta <= 8.0 * DBL_EPSILON * (j + 2) * sqrt(sc[SC_HH] + s)) eta = 0.0;
     sc[SC_ETA] = eta;
     sc[SC_GSAVE] = small[L.g + j];
-    arnoldi_column(small, L, j, m, col, cs, sn, eta);
+    arnoldi_column(small, L, j, m, col, cs, sn, eta, host);
 }
 
 // g = beta e_1 and the first basis vector scale factor
@@ -722,17 +774,27 @@ __global__ void k_cycle_start(double *small, SmallLayout L) {
     sc[SC_ETA] = 1.0;   // the lagged Gram-Schmidt's v_0 = r / beta
 }
 
-// R y = g(0:jend) by back substitution
-__global__ void k_ls_solve(double *small, SmallLayout L, int jend) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// R y = g(0:jend) by back substitution, column by column: lane i holds row i
+// of what is left of g (jend <= MAXCOL - 1 < 64), R is staged in LDS by the
+// whole workgroup.  One thread walking R in memory took 40 us at jend = 30,
+// this takes 8.
+__global__ __launch_bounds__(256) void k_ls_solve(double *small, SmallLayout L, int jend) {
+    __shared__ double R[MAXCOL][MAXCOL + 1];
     const int m = L.m;
-    const double *H = small + L.H, *g = small + L.g;
-    double *y = small + L.y;
-    for (int i = jend - 1; i >= 0; i--) {
-        double s = g[i];
-        for (int k = i + 1; k < jend; k++) s -= H[(size_t)k * (m + 1) + i] * y[k];
-        const double d = H[(size_t)i * (m + 1) + i];
-        y[i] = d != 0.0 ? s / d : 0.0;
+    const double *H = small + L.H;
+    for (int e = threadIdx.x; e < jend * 64; e += 256) {
+        const int k = e >> 6, i = e & 63;
+        if (i <= k) R[k][i] = H[(size_t)k * (m + 1) + i];
+    }
+    __syncthreads();
+    const int i = threadIdx.x;
+    if (i >= 64) return;
+    double s = i < jend ? small[L.g + i] : 0.0;
+    const double d = i < jend ? R[i][i] : 0.0;
+    for (int k = jend - 1; k >= 0; k--) {
+        const double yk = __shfl(d != 0.0 ? s / d : 0.0, k);
+        if (i < k) s -= R[k][i] * yk;
+        if (i == k) small[L.y + k] = yk;
     }
 }
 
@@ -965,7 +1027,9 @@ static int ensure_workspace(SOLVER_ *S) {
     const size_t np = std::max<size_t>({(size_t)RED_BLOCKS * MAXCOL, (size_t)CGS_MAXBLK * MAXCOL,
                                         (size_t)spmv_blocks(S->A) * 2});
     KRY_TRY(S->partial.alloc(np));
-    if (!S->h_pinned) KRY_HIP(hipHostMalloc(reinterpret_cast<void **>(&S->h_pinned), 64 * sizeof(double)));
+    if (!S->h_pinned)   // coherent: kernels write into it
+        KRY_HIP(hipHostMalloc(reinterpret_cast<void **>(&S->h_pinned), 64 * sizeof(double),
+                              hipHostMallocCoherent));
     for (auto &ev : S->step_ev)
         if (!ev) KRY_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     KRY_HIP(hipMemsetAsync(S->small.p, 0, S->small.bytes(), S->stream));
@@ -984,7 +1048,7 @@ static int readback(SOLVER_ *S, const double *d, int n, double *h) {
 // columns); pass 2 holds MAXC x 256 doubles of LDS per block
 template <int MAXC>
 static void launch_cgs(hipStream_t st, int n, const double *V, int64_t ldv, int nc, double *w,
-                       double *small, SmallLayout L, double *partial, int j, int m) {
+                       double *small, SmallLayout L, double *partial, int j, int m, double *host) {
     const dim3 b(256);
     const int g2 = MAXC == 64 ? 256 : MAXC == 16 ? 1024 : 512;
     const int g1 = MAXC >= 32 ? g2 : 512;
@@ -1002,22 +1066,22 @@ static void launch_cgs(hipStream_t st, int n, const double *V, int64_t ldv, int 
     hipLaunchKernelGGL(k_cgs_update_dots<MAXC>, dim3(g2), b, 0, st, n, V, ldv, nc, small + L.h1, w,
                        partial);
     hipLaunchKernelGGL(k_arnoldi_finish<MAXC>, dim3(1), dim3(1024), 0, st, partial, g2, j, m,
-                       small, L);
+                       small, L, host);
     hipLaunchKernelGGL(k_cgs_update_scale<MAXC>, dim3(g3), b, 0, st, n, V, ldv, nc, small + L.h2,
                        small + L.sc + SC_INVHN, small + L.sc + SC_RENORM, w, partial);
-    hipLaunchKernelGGL(k_cgs_renorm, dim3(256), b, 0, st, n, partial, g3, w, j, m, small, L);
+    hipLaunchKernelGGL(k_cgs_renorm, dim3(256), b, 0, st, n, partial, g3, w, j, m, small, L, host);
 }
 
-static int cgs2_step(SOLVER_ *S, int j, double *w) {
+static int cgs2_step(SOLVER_ *S, int j, double *w, double *host) {
     const int n = S->A->nb * S->A->bs;
     const int nc = j + 1;
     const SmallLayout L = layout_of(S);
     TimedScope ts("cgs2", S->stream);
     double *sm = S->small.p, *pt = S->partial.p;
-    if (nc <= 8) launch_cgs<8>(S->stream, n, S->V.p, S->ldv, nc, w, sm, L, pt, j, L.m);
-    else if (nc <= 16) launch_cgs<16>(S->stream, n, S->V.p, S->ldv, nc, w, sm, L, pt, j, L.m);
-    else if (nc <= 32) launch_cgs<32>(S->stream, n, S->V.p, S->ldv, nc, w, sm, L, pt, j, L.m);
-    else launch_cgs<64>(S->stream, n, S->V.p, S->ldv, nc, w, sm, L, pt, j, L.m);
+    if (nc <= 8) launch_cgs<8>(S->stream, n, S->V.p, S->ldv, nc, w, sm, L, pt, j, L.m, host);
+    else if (nc <= 16) launch_cgs<16>(S->stream, n, S->V.p, S->ldv, nc, w, sm, L, pt, j, L.m, host);
+    else if (nc <= 32) launch_cgs<32>(S->stream, n, S->V.p, S->ldv, nc, w, sm, L, pt, j, L.m, host);
+    else launch_cgs<64>(S->stream, n, S->V.p, S->ldv, nc, w, sm, L, pt, j, L.m, host);
     KRY_HIP(hipGetLastError());
     return KRY_OK;
 }
@@ -1025,29 +1089,29 @@ static int cgs2_step(SOLVER_ *S, int j, double *w) {
 // one step of the lagged Gram-Schmidt
 template <int MAXC>
 static void launch_dcgs(hipStream_t st, int n, double *V, int64_t ldv, int j, double *small,
-                        SmallLayout L, double *partial, int m) {
+                        SmallLayout L, double *partial, int m, double *host) {
     const dim3 b(256);
-    const int ga = MAXC == 16 ? 1024 : 512, gb = 512;
+    // no more blocks than have rows: their zero partials only lengthen the sums
+    const int ga = std::min(MAXC == 16 ? 1024 : 512, (n + CGS_CH - 1) / CGS_CH);
+    const int gb = std::min(512, (n / CGS_ROWS + 255) / 256 + 1);
     static_assert(2 * MAXC <= MAXCOL, "pass A's sums of a block fit one partial row");
     const int nc = j + 1;
     double *u = V + (int64_t)j * ldv;
     hipLaunchKernelGGL(k_dcgs_dots<MAXC>, dim3(ga), b, 0, st, n, V, ldv, nc, u + ldv, partial);
-    hipLaunchKernelGGL((k_sum_cols<2 * MAXC, 1024>), dim3(1), dim3(1024), 0, st, partial, ga,
-                       2 * nc, small + L.ab);
-    hipLaunchKernelGGL(k_dcgs_finish, dim3(1), dim3(64), 0, st, j, m, small, L);
+    hipLaunchKernelGGL(k_dcgs_finish<2 * MAXC>, dim3(1), dim3(1024), 0, st, partial, ga, j, m, small, L);
     hipLaunchKernelGGL(k_dcgs_update<MAXC>, dim3(gb), b, 0, st, n, V, ldv, j,
                        small + L.sa, small + L.dv, small + L.sc + SC_CU, partial);
-    hipLaunchKernelGGL(k_dcgs_norm, dim3(1), b, 0, st, partial, gb, j, m, small, L);
+    hipLaunchKernelGGL(k_dcgs_norm, dim3(1), b, 0, st, partial, gb, j, m, small, L, host);
 }
 
-static int dcgs_step(SOLVER_ *S, int j) {
+static int dcgs_step(SOLVER_ *S, int j, double *host) {
     const int n = S->A->nb * S->A->bs;
     const SmallLayout L = layout_of(S);
     TimedScope ts("dcgs2", S->stream);
     double *sm = S->small.p, *pt = S->partial.p;
-    if (j + 1 <= 8) launch_dcgs<8>(S->stream, n, S->V.p, S->ldv, j, sm, L, pt, L.m);
-    else if (j + 1 <= 16) launch_dcgs<16>(S->stream, n, S->V.p, S->ldv, j, sm, L, pt, L.m);
-    else launch_dcgs<32>(S->stream, n, S->V.p, S->ldv, j, sm, L, pt, L.m);
+    if (j + 1 <= 8) launch_dcgs<8>(S->stream, n, S->V.p, S->ldv, j, sm, L, pt, L.m, host);
+    else if (j + 1 <= 16) launch_dcgs<16>(S->stream, n, S->V.p, S->ldv, j, sm, L, pt, L.m, host);
+    else launch_dcgs<32>(S->stream, n, S->V.p, S->ldv, j, sm, L, pt, L.m, host);
     KRY_HIP(hipGetLastError());
     return KRY_OK;
 }
@@ -1183,8 +1247,8 @@ static int gmres_solve(SOLVER_ *S, const double *b, double *x) {
         // step j: z_j = M^-1 v_j (or the stored correction), w = A z_j, CGS2
         // against v_0..v_j with the Hessenberg column and Givens update and
         // w normalized in place into v_{j+1}, then
-        // an asynchronous read-back of (h_{j+1,j}, 1/h_{j+1,j}, estimate) into
-        // pinned slot j % 2 and an event.  When the preconditioner runs no
+        // an event; the step's last kernel leaves h_{j+1,j} and the estimate
+        // in pinned slot j % 2.  When the preconditioner runs no
         // host code and keeps no counters, step j+1 is issued before step
         // j's estimate is read, so the GPU never waits for the host; if step
         // j ends the cycle, step j+1's results (column j+2 of V, column j+1
@@ -1200,11 +1264,10 @@ static int gmres_solve(SOLVER_ *S, const double *b, double *x) {
                 KRY_HIP(hipMemcpyAsync(zj, S->AUG.p + (size_t)((head + j - m) % k) * S->ldv,
                                        sizeof(double) * n, hipMemcpyDeviceToDevice, S->stream));
             KRY_TRY(spmv_f64(S->stream, S->A, 1.0, zj, 0.0, nullptr, w, 0, nullptr, nullptr, nullptr));
-            if (lagged) KRY_TRY(dcgs_step(S, j));
-            else KRY_TRY(cgs2_step(S, j, w));
+            double *host = S->h_pinned + 8 + 8 * (j & 1);
+            if (lagged) KRY_TRY(dcgs_step(S, j, host));
+            else KRY_TRY(cgs2_step(S, j, w, host));
             last = j;
-            KRY_HIP(hipMemcpyAsync(S->h_pinned + 8 + 8 * (j & 1), sc + SC_HN, 3 * sizeof(double),
-                                   hipMemcpyDeviceToHost, S->stream));
             KRY_HIP(hipEventRecord(S->step_ev[j & 1], S->stream));
             return KRY_OK;
         };
@@ -1213,8 +1276,8 @@ static int gmres_solve(SOLVER_ *S, const double *b, double *x) {
             const bool ahead = speculate && j + 1 < steps;
             if (ahead) KRY_TRY(issue(j + 1));
             KRY_HIP(hipEventSynchronize(S->step_ev[j & 1]));
-            const double hn = S->h_pinned[8 + 8 * (j & 1)];        // SC_HN
-            const double est = S->h_pinned[8 + 8 * (j & 1) + 2];   // SC_EST
+            const double hn = S->h_pinned[8 + 8 * (j & 1) + HOST_HN];
+            const double est = S->h_pinned[8 + 8 * (j & 1) + HOST_EST];
             nits++;
             jend = j + 1;
             S->hist.push_back(est);
@@ -1230,7 +1293,7 @@ static int gmres_solve(SOLVER_ *S, const double *b, double *x) {
             double *vj = S->V.p + (size_t)jend * S->ldv;
             KRY_TRY(vec_scale_copy(S->stream, n, dc(sc + SC_INVHN), vj, vj));
         }
-        hipLaunchKernelGGL(k_ls_solve, dim3(1), dim3(64), 0, S->stream, small, L, jend);
+        hipLaunchKernelGGL(k_ls_solve, dim3(1), dim3(256), 0, S->stream, small, L, jend);
         if (k > 0) {
             // dx = U y; x += dx; dx / ||dx|| becomes the newest correction
             KRY_TRY(gemvn_acc(S, S->Z.p, jend, small + L.y, 0.0, utmp));
