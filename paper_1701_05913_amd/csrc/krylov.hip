@@ -497,7 +497,8 @@ __global__ __launch_bounds__(1024) void k_arnoldi_finish(const double *__restric
 // pass A: partials of v_k . u and v_k . w for the nc = j + 1 columns
 // k = 0..j of V (column j is u), in partial[b * MAXCOL + k] and
 // partial[b * MAXCOL + nc + k]; the LDS tiling of pass 2 with u's rows
-// staged beside w's
+// staged beside w's; non-temporal loads (25 M unknowns, 31 columns: 6.05 ->
+// 6.2 TB/s; V is next read by pass B, far beyond any cache at such sizes)
 template <int MAXC>
 __global__ __launch_bounds__(256) void k_dcgs_dots(int n, const double *__restrict__ V,
                                                    int64_t ldv, int nc,
@@ -520,7 +521,7 @@ __global__ __launch_bounds__(256) void k_dcgs_dots(int n, const double *__restri
         wpre = ok ? w[r] : 0.0;
 #pragma unroll
         for (int k = 0; k < MAXC; k++)
-            if (k < nc) pre[k] = ok ? V[k * ldv + r] : 0.0;
+            if (k < nc) pre[k] = ok ? __builtin_nontemporal_load(V + k * ldv + r) : 0.0;
     };
     int base = blockIdx.x * CGS_CH;
     if (base < n) load(base);
@@ -563,16 +564,19 @@ __global__ __launch_bounds__(256) void k_dcgs_dots(int n, const double *__restri
 
 // pass B: column j = cu u - V sa and column j + 1 = cu w - V d - v_j d_j,
 // with its partial |.|^2 in partial[b * MAXCOL]; sa over the j final
-// columns, d over j + 1 values, cu = 1 / (eta alpha)
-template <int MAXC>
+// columns, d over j + 1 values, cu = 1 / (eta alpha).  Four columns are in
+// flight at once: one after another a thread waited j times (2 880 unknowns,
+// j = 29: 7.3 -> 5 us).  Large sizes are bound by HBM (25 M unknowns: 5.2
+// TB/s with the two columns written; eight columns at once, non-temporal
+// loads or 1024 workgroups are slower).
 __global__ __launch_bounds__(256) void k_dcgs_update(int n, double *V, int64_t ldv, int j,
                                                      const double *__restrict__ sa,
                                                      const double *__restrict__ dv,
                                                      const double *__restrict__ cu_p,
                                                      double *__restrict__ partial) {
-    __shared__ double ss[MAXC], ds[MAXC];
+    __shared__ double ss[DCGS_MAXM + 1], ds[DCGS_MAXM + 1];
     __shared__ double red[4];
-    if (threadIdx.x < MAXC) {
+    if (threadIdx.x <= DCGS_MAXM) {
         ss[threadIdx.x] = (int)threadIdx.x < j ? sa[threadIdx.x] : 0.0;
         ds[threadIdx.x] = (int)threadIdx.x <= j ? dv[threadIdx.x] : 0.0;
     }
@@ -596,20 +600,34 @@ __global__ __launch_bounds__(256) void k_dcgs_update(int n, double *V, int64_t l
         t0.y *= cu;
         t1.x *= cu;
         t1.y *= cu;
+        // nb columns from k0 on, all loaded before the first is used
+        auto columns = [&](auto nb, int k0) {
+            constexpr int NB = decltype(nb)::value;
+            double2 a[NB], b[NB];
 #pragma unroll
-        for (int k = 0; k < MAXC; k++)
-            if (k < j) {
-                const double2 *col = reinterpret_cast<const double2 *>(V + k * ldv + off);
-                const double2 a = col[0], b = col[1];
-                v0.x -= a.x * ss[k];
-                v0.y -= a.y * ss[k];
-                v1.x -= b.x * ss[k];
-                v1.y -= b.y * ss[k];
-                t0.x -= a.x * ds[k];
-                t0.y -= a.y * ds[k];
-                t1.x -= b.x * ds[k];
-                t1.y -= b.y * ds[k];
+            for (int c = 0; c < NB; c++) {
+                const double *col = V + (k0 + c) * ldv + off;
+                a[c] = *reinterpret_cast<const double2 *>(col);
+                b[c] = *reinterpret_cast<const double2 *>(col + 2);
             }
+#pragma unroll
+            for (int c = 0; c < NB; c++) {
+                const double sk = ss[k0 + c], dk = ds[k0 + c];
+                v0.x -= a[c].x * sk;
+                v0.y -= a[c].y * sk;
+                v1.x -= b[c].x * sk;
+                v1.y -= b[c].y * sk;
+                t0.x -= a[c].x * dk;
+                t0.y -= a[c].y * dk;
+                t1.x -= b[c].x * dk;
+                t1.y -= b[c].y * dk;
+            }
+        };
+        int k = 0;
+        for (; k + 4 <= j; k += 4) columns(std::integral_constant<int, 4>(), k);
+        if (j - k == 3) columns(std::integral_constant<int, 3>(), k);
+        else if (j - k == 2) columns(std::integral_constant<int, 2>(), k);
+        else if (j - k == 1) columns(std::integral_constant<int, 1>(), k);
         t0.x -= v0.x * dj;
         t0.y -= v0.y * dj;
         t1.x -= v1.x * dj;
@@ -623,13 +641,12 @@ __global__ __launch_bounds__(256) void k_dcgs_update(int n, double *V, int64_t l
     if (blockIdx.x == 0 && (int)threadIdx.x < n - nq * CGS_ROWS) {
         const int r = nq * CGS_ROWS + threadIdx.x;
         double v = u[r] * cu, t = w[r] * cu;
-#pragma unroll
-        for (int k = 0; k < MAXC; k++)
-            if (k < j) {
-                const double a = V[k * ldv + r];
-                v -= a * ss[k];
-                t -= a * ds[k];
-            }
+#pragma unroll 4
+        for (int k = 0; k < j; k++) {
+            const double a = V[k * ldv + r];
+            v -= a * ss[k];
+            t -= a * ds[k];
+        }
         t -= v * dj;
         u[r] = v;
         w[r] = t;
@@ -1099,7 +1116,7 @@ static void launch_dcgs(hipStream_t st, int n, double *V, int64_t ldv, int j, do
     double *u = V + (int64_t)j * ldv;
     hipLaunchKernelGGL(k_dcgs_dots<MAXC>, dim3(ga), b, 0, st, n, V, ldv, nc, u + ldv, partial);
     hipLaunchKernelGGL(k_dcgs_finish<2 * MAXC>, dim3(1), dim3(1024), 0, st, partial, ga, j, m, small, L);
-    hipLaunchKernelGGL(k_dcgs_update<MAXC>, dim3(gb), b, 0, st, n, V, ldv, j,
+    hipLaunchKernelGGL(k_dcgs_update, dim3(gb), b, 0, st, n, V, ldv, j,
                        small + L.sa, small + L.dv, small + L.sc + SC_CU, partial);
     hipLaunchKernelGGL(k_dcgs_norm, dim3(1), b, 0, st, partial, gb, j, m, small, L, host);
 }
