@@ -64,6 +64,29 @@ struct DBuf {
     size_t bytes() const { return n * sizeof(T); }
 };
 
+// Pinned host memory that kernels write: a kernel's last store and the
+// synchronization its caller needs anyway take 12 us, a copy of 8 bytes into
+// pageable memory 23 us (into pinned memory 15 us).
+template <typename T>
+struct HostBuf {
+    T *p = nullptr;
+    HostBuf() = default;
+    HostBuf(const HostBuf &) = delete;
+    HostBuf &operator=(const HostBuf &) = delete;
+    ~HostBuf() {
+        if (p) (void)hipHostFree(p);
+    }
+    int alloc(size_t count) {   // once; later calls keep what is there
+        if (p) return KRY_OK;
+        if (hipHostMalloc(reinterpret_cast<void **>(&p), count * sizeof(T),
+                          hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess) {
+            p = nullptr;
+            return set_error(KRY_ERR_ALLOC, "hipHostMalloc of %zu bytes failed", count * sizeof(T));
+        }
+        return KRY_OK;
+    }
+};
+
 // ---------------------------------------------------------------------------
 // sliced ELLPACK with 64-row slices (one wavefront per slice) and
 // entry-major value planes: value e of slot t of lane l sits at
@@ -513,7 +536,7 @@ struct SOLVER_ {
     int64_t ldv = 0;
     kry::DBuf<double> V, Z, wrk, H, small, partial;
     kry::DBuf<double> AUG;       // LGMRES: stored corrections (aug_k columns)
-    double *h_pinned = nullptr;  // host-visible readback slots
+    kry::HostBuf<double> pinned;      // readback slots: 0.. scalars, 8 and 16 Arnoldi steps, 24 error flag
     hipEvent_t step_ev[2] = {nullptr, nullptr};   // Arnoldi steps' read-backs (slots 8, 16)
 };
 

@@ -32,6 +32,7 @@
 namespace kry {
 
 constexpr int MAXCOL = 64;   // restart length limit (columns of V)
+constexpr int PINNED_SLOTS = 32, PINNED_FLAG = 24;
 constexpr int DCGS_MAXM = 31; // longest restart of the lagged Gram-Schmidt
 static_assert(DCGS_MAXM < 64, "the lagged finish holds one column entry per lane of a wavefront");
 static_assert(2 * (DCGS_MAXM + 1) <= MAXCOL, "pass A's sums of a block fit one partial row");
@@ -1044,9 +1045,7 @@ static int ensure_workspace(SOLVER_ *S) {
     const size_t np = std::max<size_t>({(size_t)RED_BLOCKS * MAXCOL, (size_t)CGS_MAXBLK * MAXCOL,
                                         (size_t)spmv_blocks(S->A) * 2});
     KRY_TRY(S->partial.alloc(np));
-    if (!S->h_pinned)   // coherent: kernels write into it
-        KRY_HIP(hipHostMalloc(reinterpret_cast<void **>(&S->h_pinned), 64 * sizeof(double),
-                              hipHostMallocCoherent));
+    KRY_TRY(S->pinned.alloc(PINNED_SLOTS));
     for (auto &ev : S->step_ev)
         if (!ev) KRY_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     KRY_HIP(hipMemsetAsync(S->small.p, 0, S->small.bytes(), S->stream));
@@ -1055,9 +1054,9 @@ static int ensure_workspace(SOLVER_ *S) {
 
 // read n scalars from device memory (synchronizes the solver stream)
 static int readback(SOLVER_ *S, const double *d, int n, double *h) {
-    KRY_HIP(hipMemcpyAsync(S->h_pinned, d, sizeof(double) * n, hipMemcpyDeviceToHost, S->stream));
+    KRY_HIP(hipMemcpyAsync(S->pinned.p, d, sizeof(double) * n, hipMemcpyDeviceToHost, S->stream));
     KRY_HIP(hipStreamSynchronize(S->stream));
-    memcpy(h, S->h_pinned, sizeof(double) * n);
+    memcpy(h, S->pinned.p, sizeof(double) * n);
     return KRY_OK;
 }
 
@@ -1206,10 +1205,18 @@ int pc_apply(SOLVER_ *S, const double *v, double *z) {
     }
 }
 
+__global__ void k_report_flag(const int *flag, int *host) {
+    if (threadIdx.x == 0)
+        __hip_atomic_store(host, *flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 int check_device_error(SOLVER_ *S) {
-    int e = 0;
-    KRY_HIP(hipMemcpyAsync(&e, S->err.p, sizeof(int), hipMemcpyDeviceToHost, S->stream));
+    KRY_TRY(S->pinned.alloc(PINNED_SLOTS));
+    int *host = reinterpret_cast<int *>(S->pinned.p + PINNED_FLAG);
+    hipLaunchKernelGGL(k_report_flag, dim3(1), dim3(64), 0, S->stream, S->err.p, host);
+    KRY_HIP(hipGetLastError());
     KRY_HIP(hipStreamSynchronize(S->stream));
+    const int e = *host;
     if (e == 1) return set_error(KRY_ERR_ZERO_PIVOT, "singular pivot block in the factorization");
     if (e == ERR_STALL_FLAG)
         return set_error(KRY_ERR_STALL, "a level-scheduled sweep exceeded its wait bound");
@@ -1281,7 +1288,7 @@ static int gmres_solve(SOLVER_ *S, const double *b, double *x) {
                 KRY_HIP(hipMemcpyAsync(zj, S->AUG.p + (size_t)((head + j - m) % k) * S->ldv,
                                        sizeof(double) * n, hipMemcpyDeviceToDevice, S->stream));
             KRY_TRY(spmv_f64(S->stream, S->A, 1.0, zj, 0.0, nullptr, w, 0, nullptr, nullptr, nullptr));
-            double *host = S->h_pinned + 8 + 8 * (j & 1);
+            double *host = S->pinned.p + 8 + 8 * (j & 1);
             if (lagged) KRY_TRY(dcgs_step(S, j, host));
             else KRY_TRY(cgs2_step(S, j, w, host));
             last = j;
@@ -1293,8 +1300,8 @@ static int gmres_solve(SOLVER_ *S, const double *b, double *x) {
             const bool ahead = speculate && j + 1 < steps;
             if (ahead) KRY_TRY(issue(j + 1));
             KRY_HIP(hipEventSynchronize(S->step_ev[j & 1]));
-            const double hn = S->h_pinned[8 + 8 * (j & 1) + HOST_HN];
-            const double est = S->h_pinned[8 + 8 * (j & 1) + HOST_EST];
+            const double hn = S->pinned.p[8 + 8 * (j & 1) + HOST_HN];
+            const double est = S->pinned.p[8 + 8 * (j & 1) + HOST_EST];
             nits++;
             jend = j + 1;
             S->hist.push_back(est);
@@ -1514,7 +1521,6 @@ extern "C" int SolverDestroy(SOLVER **sp) {
     if (!sp || !*sp) return KRY_OK;
     SOLVER *s = *sp;
     if (s->pc_type == KRY_PC_CUSTOM && s->cdestroy) s->cdestroy(s->cdata);
-    if (s->h_pinned) (void)hipHostFree(s->h_pinned);
     for (auto &ev : s->step_ev)
         if (ev) (void)hipEventDestroy(ev);
     delete s;

@@ -847,7 +847,8 @@ struct ConvNet {
     int adam_t = 0;
     DBuf<uint16_t> wf[4], wt[4];          // forward / input-gradient fragments
     DBuf<uint16_t> h0, h[3], dz4, dza, dzb;
-    DBuf<float> z[3], out, part, loss, tmp_io;
+    DBuf<float> z[3], out, part, tmp_io;
+    HostBuf<float> loss;   // pinned: the loss is read by the host alone
     bool training = false;
 };
 
@@ -884,8 +885,8 @@ static int net_alloc(ConvNet &N, int nx, int ny, int nz, bool training) {
     KRY_TRY(N.h0.alloc(N.cells * 4));
     for (int l = 0; l < 3; l++) KRY_TRY(N.h[l].alloc(N.cells * 32));
     KRY_TRY(N.out.alloc(N.cells * 3));
-    KRY_TRY(N.loss.alloc(4));
     if (training) {
+        KRY_TRY(N.loss.alloc(1));
         KRY_TRY(N.grad.alloc(np));
         KRY_TRY(N.m.alloc(np));
         KRY_TRY(N.v.alloc(np));
@@ -1098,10 +1099,8 @@ extern "C" int LearnedLossGrad(LEARNED *L, const float *in, const float *target,
     KRY_TRY(net_backward(L->stream, N, target));
     if (grad)
         KRY_HIP(hipMemcpyAsync(grad, N.grad.p, sizeof(float) * NET_OFF[4], hipMemcpyDeviceToDevice, L->stream));
-    float lh = 0.0f;
-    KRY_HIP(hipMemcpyAsync(&lh, N.loss.p, sizeof(float), hipMemcpyDeviceToHost, L->stream));
     KRY_HIP(hipStreamSynchronize(L->stream));
-    if (loss_host) *loss_host = lh;
+    if (loss_host) *loss_host = *N.loss.p;
     return KRY_OK;
 }
 
