@@ -190,20 +190,45 @@ __global__ void k_grid_fill_sentinel(int64_t n, T *__restrict__ y) {
 // x-line), takes D_n^-1 of i-1 from the lane's previous step, of j-1 and
 // k-1 from neighbouring lanes or from the face entries published by the
 // upstream tiles, and writes the packed sweep layout directly:
-// Lt = A_cn D_n^-1, Ut = the upper blocks of A, Dt = D_c^-1.  Positions in
-// the block rows follow from the cell's neighbours (one rowptr load per row).
+// Lt = A_cn D_n^-1, Dt = D_c^-1 (Ut, the upper blocks of A, needs no order:
+// grid_upper_body).
+//
+// Bound by the chain of steps: what a step waits for counts, and the one
+// wavefront's own loads (a row's blocks lie apart, so each load instruction
+// takes 64 requests).  The blocks of step t + 1 are loaded while step t's
+// stores drain and the next faces are polled, their places follow from the
+// stencil (row_start), and both upstream tiles are polled at once; Ut is left
+// to a launch of its own.  Measured at 64x64x64, 3x3 blocks: 1485 -> 1028 us
+// (5.4 us a step) and 31 us for Ut; with Ut here 1251 us.  Waiting for rowptr,
+// then for the blocks, then for one face after the other took 7.8 us a step.
+
+// where row (0, j, k) of a full 7-point stencil in natural order starts: seven
+// entries per row before it, less those that the grid's faces cut off
+__device__ __forceinline__ int row_start(int nx, int ny, int nz, int j, int k) {
+    const int64_t line = j + (int64_t)ny * k, plane = (int64_t)nx * ny, c = nx * line;
+    const int64_t cut = 2 * line                                     // i = 0, i = nx - 1
+                        + (int64_t)nx * (k + (j > 0))                // j = 0
+                        + (int64_t)nx * k                            // j = ny - 1
+                        + (k > 0 ? plane : c)                        // k = 0
+                        + (k == nz - 1 ? c - plane * (nz - 1) : 0);  // k = nz - 1
+    return static_cast<int>(7 * c - cut);
+}
+
 template <int BS>
-__device__ __forceinline__ void grid_factor_body(const GridTiles &G, const int *__restrict__ rowptr,
-                                                 const double *__restrict__ val,
-                                                 double *__restrict__ Lt, double *__restrict__ Ut,
-                                                 double *__restrict__ Dt, double *faces, int *ctr,
-                                                 int *err) {
+__device__ __forceinline__ void load_block(const double *__restrict__ val, int64_t p, double (&x)[BS * BS]) {
+#pragma unroll
+    for (int e = 0; e < BS * BS; e++) x[e] = val[p * (BS * BS) + e];
+}
+
+template <int BS>
+__device__ __forceinline__ void grid_factor_body(const GridTiles &G, const double *__restrict__ val,
+                                                 double *__restrict__ Lt, double *__restrict__ Dt,
+                                                 double *faces, int *ctr, int *err) {
     constexpr int B2 = BS * BS;
     using PF = StepPlanes<double, 3 * B2>;
     using PD = StepPlanes<double, B2>;
     const int lane = threadIdx.x;
     const int TJ = G.TJ, TK = G.TK, NF = G.NF, nx = G.nx, ny = G.ny, nz = G.nz, S = G.S;
-    const int64_t sJ = nx, sK = (int64_t)nx * ny;
     const int jj = lane % TJ, kk = lane / TJ;
     const int fj = jj == TJ - 1 && kk < TK ? kk : -1;       // published face entries
     const int fk = kk == TK - 1 ? TK + jj : -1;
@@ -216,14 +241,51 @@ __device__ __forceinline__ void grid_factor_body(const GridTiles &G, const int *
         const int J = JK & 0xffff, K = JK >> 16;
         const int j = J * TJ + jj, k = K * TK + kk;
         const bool lane_ok = lane < TJ * TK && j < ny && k < nz;
-        const int64_t cl = lane_ok ? sJ * j + sK * k : 0;
-        const double *srcj = (jj == 0 && J > 0 && lane_ok)
-                                 ? faces + (((int64_t)G.tidx[(J - 1) * G.NK + K] * S + (TJ - 1)) * NF + kk) * B2
-                                 : nullptr;
-        const double *srck = (kk == 0 && K > 0 && lane_ok)
-                                 ? faces + (((int64_t)G.tidx[J * G.NK + K - 1] * S + (TK - 1)) * NF + TK + jj) * B2
-                                 : nullptr;
+        // face cells of step 0 of the upstream tiles
+        const bool from_j = jj == 0 && J > 0 && lane_ok, from_k = kk == 0 && K > 0 && lane_ok;
+        const int64_t srcj = from_j ? ((int64_t)G.tidx[(J - 1) * G.NK + K] * S + (TJ - 1)) * NF + kk : -1;
+        const int64_t srck = from_k ? ((int64_t)G.tidx[J * G.NK + K - 1] * S + (TK - 1)) * NF + TK + jj : -1;
         double *frow = faces + (int64_t)T * S * NF * B2;
+        // blocks of the step's cell: lower (k-1, j-1, i-1), diagonal, and the
+        // blocks A_nc of its lower neighbours
+        double al[3][B2], ad[B2], an[3][B2];
+        // starts of the rows of the next cell to load and of its lower
+        // neighbours (k-1, j-1, i-1); rowlen: entries of a row but i-1, i+1
+        const bool up_j = j < ny - 1, up_k = k < nz - 1;
+        int pc = 0, pk = 0, pj = 0, pi = 0;
+        if (lane_ok) {
+            pc = row_start(nx, ny, nz, j, k);
+            if (k > 0) pk = row_start(nx, ny, nz, j, k - 1);
+            if (j > 0) pj = row_start(nx, ny, nz, j - 1, k);
+        }
+        const int rowlen = 1 + (j > 0) + up_j + (k > 0) + up_k;
+        const int rowlen_k = 1 + (j > 0) + up_j + (k > 1) + 1, rowlen_j = 1 + (j > 1) + 1 + (k > 0) + up_k;
+        auto load_cell = [&](int t) {
+            const int i = t - jj - kk;
+            if (!lane_ok || i < 0 || i >= nx) return;
+            const int lo_i = i > 0, up_i = i < nx - 1;
+            int64_t p = pc;
+            // A_nc sits in row n after n's lower blocks, its diagonal and
+            // the upper neighbours of n that precede this cell
+            if (k > 0) {
+                load_block<BS>(val, p++, al[0]);
+                load_block<BS>(val, pk + (k > 1) + (j > 0) + lo_i + 1 + up_i + up_j, an[0]);
+            }
+            if (j > 0) {
+                load_block<BS>(val, p++, al[1]);
+                load_block<BS>(val, pj + (k > 0) + (j > 1) + lo_i + 1 + up_i, an[1]);
+            }
+            if (i > 0) {
+                load_block<BS>(val, p++, al[2]);
+                load_block<BS>(val, pi + (k > 0) + (j > 0) + (i > 1) + 1, an[2]);
+            }
+            load_block<BS>(val, p, ad);
+            pi = pc;
+            pc += rowlen + lo_i + up_i;
+            pk += rowlen_k + lo_i + up_i;
+            pj += rowlen_j + lo_i + up_i;
+        };
+        load_cell(0);
         double dp[B2];
 #pragma unroll
         for (int e = 0; e < B2; e++) dp[e] = 0.0;
@@ -238,59 +300,48 @@ __device__ __forceinline__ void grid_factor_body(const GridTiles &G, const int *
                 dn[1][e] = __shfl_up(dp[e], 1, 64);
                 dn[2][e] = dp[e];
             }
-            if (valid && k > 0 && kk == 0 && srck) wait_values<double, B2>(srck + (int64_t)t * NF * B2, dn[0], err);
-            if (valid && j > 0 && jj == 0 && srcj) wait_values<double, B2>(srcj + (int64_t)t * NF * B2, dn[1], err);
-            double D[B2], L[3][B2], R[B2];
+            if (valid && (from_j || from_k)) {
+                const int64_t cells[2] = {from_k ? srck + (int64_t)t * NF : -1, from_j ? srcj + (int64_t)t * NF : -1};
+                double f[2][B2];
+                wait_cells<double, B2, 2>(faces, cells, f, err);
+#pragma unroll
+                for (int e = 0; e < B2; e++) {
+                    if (from_k) dn[0][e] = f[0][e];
+                    if (from_j) dn[1][e] = f[1][e];
+                }
+            }
+            double L[3][B2], R[B2];
 #pragma unroll
             for (int e = 0; e < B2; e++) {
-                D[e] = 0.0;
                 R[e] = 0.0;
 #pragma unroll
                 for (int b = 0; b < 3; b++) L[b][e] = 0.0;
             }
-            const int64_t c = cl + i;
             if (valid) {
-                // neighbours present, in column order: k-1, j-1, i-1, i+1, j+1, k+1
-                const bool has[6] = {k > 0, j > 0, i > 0, i < nx - 1, j < ny - 1, k < nz - 1};
-                const int64_t nbr[3] = {c - sK, c - sJ, c - 1};
-                // A_nc sits in row n after n's lower blocks, its diagonal and
-                // the upper neighbours of n that precede column c
-                int qn[3] = {0, 0, 0};
-                if (has[0]) qn[0] = rowptr[nbr[0]] + ((k - 1 > 0) + (j > 0) + (i > 0)) + 1 + has[3] + has[4];
-                if (has[1]) qn[1] = rowptr[nbr[1]] + ((k > 0) + (j - 1 > 0) + (i > 0)) + 1 + has[3];
-                if (has[2]) qn[2] = rowptr[nbr[2]] + ((k > 0) + (j > 0) + (i - 1 > 0)) + 1;
-                int p = rowptr[c];
-                // L = A_cn D_n^-1 for row c's lower blocks
-#pragma unroll
-                for (int b = 0; b < 3; b++) {
-                    if (!has[b]) continue;
-                    const double *a = val + (int64_t)p * B2;
-#pragma unroll
-                    for (int r = 0; r < BS; r++)
-#pragma unroll
-                        for (int cc = 0; cc < BS; cc++) {
-                            double sacc = 0.0;
-#pragma unroll
-                            for (int m = 0; m < BS; m++) sacc += a[r * BS + m] * dn[b][m * BS + cc];
-                            L[b][r * BS + cc] = sacc;
-                        }
-                    p++;
-                }
-                // diagonal block, minus L A_nc in column order
-                const double *ad = val + (int64_t)p * B2;
+                const bool has[3] = {k > 0, j > 0, i > 0};
+                // D = A_cc minus L A_nc in column order, L = A_cn D_n^-1
+                double D[B2];
 #pragma unroll
                 for (int e = 0; e < B2; e++) D[e] = ad[e];
 #pragma unroll
                 for (int b = 0; b < 3; b++) {
                     if (!has[b]) continue;
-                    const double *u = val + (int64_t)qn[b] * B2;
 #pragma unroll
                     for (int r = 0; r < BS; r++)
 #pragma unroll
                         for (int cc = 0; cc < BS; cc++) {
                             double sacc = 0.0;
 #pragma unroll
-                            for (int m = 0; m < BS; m++) sacc += L[b][r * BS + m] * u[m * BS + cc];
+                            for (int m = 0; m < BS; m++) sacc += al[b][r * BS + m] * dn[b][m * BS + cc];
+                            L[b][r * BS + cc] = sacc;
+                        }
+#pragma unroll
+                    for (int r = 0; r < BS; r++)
+#pragma unroll
+                        for (int cc = 0; cc < BS; cc++) {
+                            double sacc = 0.0;
+#pragma unroll
+                            for (int m = 0; m < BS; m++) sacc += L[b][r * BS + m] * an[b][m * BS + cc];
                             D[r * BS + cc] -= sacc;
                         }
                 }
@@ -299,58 +350,116 @@ __device__ __forceinline__ void grid_factor_body(const GridTiles &G, const int *
 #pragma unroll
                     for (int e = 0; e < B2; e++) R[e] = 0.0;
                 }
-                // upper blocks (unchanged) and the inverse, at the backward step
-                const int tb = (nx - 1 - i) + (TJ - 1 - jj) + (TK - 1 - kk);
-                double *ub = Ut + ((int64_t)T * S + tb) * PF::SIZE;
-                double *db = Dt + ((int64_t)T * S + tb) * PD::SIZE;
-                int pu = p + 1;
-#pragma unroll
-                for (int b = 0; b < 3; b++) {
-                    if (!has[3 + b]) continue;
-#pragma unroll
-                    for (int e = 0; e < B2; e++)
-                        ub[PF::at(b * B2 + e, lane)] = val[(int64_t)pu * B2 + e];
-                    pu++;
-                }
-#pragma unroll
-                for (int e = 0; e < B2; e++) db[PD::at(e, lane)] = R[e];
             }
-            // forward blocks of this step (zeros for idle lanes and steps)
-            double *lf = Lt + ((int64_t)T * S + t) * PF::SIZE;
-#pragma unroll
-            for (int b = 0; b < 3; b++)
-#pragma unroll
-                for (int e = 0; e < B2; e++) lf[PF::at(b * B2 + e, lane)] = L[b][e];
             if (fj >= 0)
 #pragma unroll
                 for (int e = 0; e < B2; e++) publish<double>(frow + ((int64_t)t * NF + fj) * B2 + e, R[e]);
             if (fk >= 0)
 #pragma unroll
                 for (int e = 0; e < B2; e++) publish<double>(frow + ((int64_t)t * NF + fk) * B2 + e, R[e]);
+            // forward blocks of this step (zeros for idle lanes and steps)
+            // and the inverse, at the backward step
+            double *lf = Lt + ((int64_t)T * S + t) * PF::SIZE;
+#pragma unroll
+            for (int b = 0; b < 3; b++)
+#pragma unroll
+                for (int e = 0; e < B2; e++) lf[PF::at(b * B2 + e, lane)] = L[b][e];
+            if (valid) {
+                const int tb = (nx - 1 - i) + (TJ - 1 - jj) + (TK - 1 - kk);
+                double *db = Dt + ((int64_t)T * S + tb) * PD::SIZE;
+#pragma unroll
+                for (int e = 0; e < B2; e++) db[PD::at(e, lane)] = R[e];
+            }
+            if (t + 1 < S) load_cell(t + 1);
 #pragma unroll
             for (int e = 0; e < B2; e++) dp[e] = R[e];
         }
     }
 }
 
+// Ut = the upper blocks of A: one wavefront per tile and backward step, four
+// steps to a workgroup of the grid's nwg
 template <int BS>
-__global__ __launch_bounds__(64) void k_grid_factor(GridTiles G, const int *__restrict__ rowptr,
-                                                    const double *__restrict__ val,
-                                                    double *__restrict__ Lt, double *__restrict__ Ut,
-                                                    double *__restrict__ Dt, double *faces, int *ctr,
-                                                    int *err) {
-    grid_factor_body<BS>(G, rowptr, val, Lt, Ut, Dt, faces, ctr, err);
+__device__ __forceinline__ void grid_upper_body(const GridTiles &G, const double *__restrict__ val,
+                                                double *__restrict__ Ut, int wg, int nwg) {
+    constexpr int B2 = BS * BS;
+    using PF = StepPlanes<double, 3 * B2>;
+    const int lane = threadIdx.x & 63, jj = lane % G.TJ, kk = lane / G.TJ;
+    const int64_t steps = (int64_t)G.ntiles * G.S;
+    for (int64_t u = wg * (int64_t)4 + (threadIdx.x >> 6); u < steps; u += (int64_t)nwg * 4) {
+        const int JK = G.order[u / G.S], t = (int)(u % G.S);
+        const int j = (JK & 0xffff) * G.TJ + jj, k = (JK >> 16) * G.TK + kk;
+        const int i = G.nx - 1 - (t - (G.TJ - 1 - jj) - (G.TK - 1 - kk));
+        if (lane >= G.TJ * G.TK || j >= G.ny || k >= G.nz || i < 0 || i >= G.nx) continue;
+        const bool up_j = j < G.ny - 1, up_k = k < G.nz - 1;
+        const int low = (j > 0) + (k > 0);
+        // the row's start, then its lower blocks and its diagonal
+        int64_t p = row_start(G.nx, G.ny, G.nz, j, k) + (int64_t)i * (1 + low + up_j + up_k) + (i > 0 ? 2 * i - 1 : 0);
+        p += low + (i > 0) + 1;
+        double *ub = Ut + u * PF::SIZE;
+        const bool has[3] = {i < G.nx - 1, up_j, up_k};
+#pragma unroll
+        for (int b = 0; b < 3; b++)
+            if (has[b]) {
+                double x[B2];
+                load_block<BS>(val, p++, x);
+#pragma unroll
+                for (int e = 0; e < B2; e++) ub[PF::at(b * B2 + e, lane)] = x[e];
+            }
+    }
+}
+
+template <int BS>
+__global__ __launch_bounds__(256) void k_grid_upper(GridTiles G, const double *__restrict__ val,
+                                                    double *__restrict__ Ut) {
+    grid_upper_body<BS>(G, val, Ut, blockIdx.x, gridDim.x);
+}
+
+template <int BS>
+__global__ __launch_bounds__(64) void k_grid_factor(GridTiles G, const double *__restrict__ val,
+                                                    double *__restrict__ Lt, double *__restrict__ Dt,
+                                                    double *faces, int *ctr, int *err) {
+    grid_factor_body<BS>(G, val, Lt, Dt, faces, ctr, err);
+}
+
+// A pointer read from a descriptor, as an offset from `origin`, a kernel
+// argument that is null: derived from a kernel argument, its accesses are
+// global instructions; those of a pointer read from memory are flat ones,
+// which also wait on the LDS counter.
+template <typename T>
+__device__ __forceinline__ T *as_global(char *origin, T *p) {
+    return reinterpret_cast<T *>(origin + reinterpret_cast<uintptr_t>(p));
+}
+__device__ __forceinline__ void globalize(char *origin, GridTiles &G) {
+    G.order = as_global(origin, const_cast<int *>(G.order));
+    G.tidx = as_global(origin, const_cast<int *>(G.tidx));
+    G.qtiles = as_global(origin, const_cast<int *>(G.qtiles));
+    G.qjk = as_global(origin, const_cast<int *>(G.qjk));
+    G.qoff = as_global(origin, const_cast<int *>(G.qoff));
 }
 
 // the factorizations of several independent grids in one launch: grid g
 // owns the workgroups [wg0, next wg0)
 template <int BS>
 __global__ __launch_bounds__(64) void k_grid_factor_multi(const FactorMulti *__restrict__ d,
-                                                          int ngrid, int *err) {
+                                                          int ngrid, int *err, char *origin) {
     int g = 0;
     while (g + 1 < ngrid && (int)blockIdx.x >= d[g + 1].wg0) g++;
-    const FactorMulti D = d[g];
-    grid_factor_body<BS>(D.G, D.rowptr, D.val, D.lt, D.ut, D.dt, D.faces, D.ctr, err);
+    FactorMulti D = d[g];
+    globalize(origin, D.G);
+    grid_factor_body<BS>(D.G, as_global(origin, const_cast<double *>(D.val)), as_global(origin, D.lt),
+                         as_global(origin, D.dt), as_global(origin, D.faces), as_global(origin, D.ctr), err);
+}
+
+template <int BS>
+__global__ __launch_bounds__(256) void k_grid_upper_multi(const FactorMulti *__restrict__ d, int ngrid,
+                                                          char *origin) {
+    int g = 0;
+    while (g + 1 < ngrid && (int)blockIdx.x >= d[g + 1].wg0) g++;
+    FactorMulti D = d[g];
+    globalize(origin, D.G);
+    grid_upper_body<BS>(D.G, as_global(origin, const_cast<double *>(D.val)), as_global(origin, D.ut),
+                        blockIdx.x - D.wg0, (g + 1 < ngrid ? d[g + 1].wg0 : (int)gridDim.x) - D.wg0);
 }
 
 // tiling of the (j, k) plane and the tile order (J + K diagonals)
@@ -514,7 +623,6 @@ int grid_factor_rearm(hipStream_t s, IluFactor &F, DBuf<double> &faces, DBuf<int
 int grid_factor_desc(const MAT_ *A, const IluFactor &F, DBuf<double> &faces, DBuf<int> &fctr,
                      int wg0, FactorMulti &d, int *wgs) {
     d.G = F.G;
-    d.rowptr = A->rowptr.p;
     d.val = A->val.p;
     d.lt = F.lt64.p;
     d.ut = F.ut64.p;
@@ -529,10 +637,14 @@ int grid_factor_desc(const MAT_ *A, const IluFactor &F, DBuf<double> &faces, DBu
 int grid_factor_multi(hipStream_t s, int bs, const FactorMulti *d_desc, int ngrid, int total_wgs,
                       int *err) {
     TimedScope t("ras_grid_factor", s);
-    if (bs == 1)
-        hipLaunchKernelGGL(k_grid_factor_multi<1>, dim3(total_wgs), dim3(64), 0, s, d_desc, ngrid, err);
-    else
-        hipLaunchKernelGGL(k_grid_factor_multi<3>, dim3(total_wgs), dim3(64), 0, s, d_desc, ngrid, err);
+    char *const origin = nullptr;
+    if (bs == 1) {
+        hipLaunchKernelGGL(k_grid_factor_multi<1>, dim3(total_wgs), dim3(64), 0, s, d_desc, ngrid, err, origin);
+        hipLaunchKernelGGL(k_grid_upper_multi<1>, dim3(total_wgs), dim3(256), 0, s, d_desc, ngrid, origin);
+    } else {
+        hipLaunchKernelGGL(k_grid_factor_multi<3>, dim3(total_wgs), dim3(64), 0, s, d_desc, ngrid, err, origin);
+        hipLaunchKernelGGL(k_grid_upper_multi<3>, dim3(total_wgs), dim3(256), 0, s, d_desc, ngrid, origin);
+    }
     KRY_HIP(hipGetLastError());
     return KRY_OK;
 }
@@ -561,12 +673,16 @@ int ilu_grid_factor_setup(hipStream_t s, const MAT_ *A, const double *d_val, Ilu
     const int wgs = std::min(G.ntiles, 1024);
     {
         TimedScope t("ilu_grid_factor", s);
-        if (A->bs == 1)
-            hipLaunchKernelGGL(k_grid_factor<1>, dim3(wgs), dim3(64), 0, s, G, A->rowptr.p, d_val,
-                               F.lt64.p, F.ut64.p, F.dt64.p, faces.p, ctr.p, d_err);
-        else
-            hipLaunchKernelGGL(k_grid_factor<3>, dim3(wgs), dim3(64), 0, s, G, A->rowptr.p, d_val,
-                               F.lt64.p, F.ut64.p, F.dt64.p, faces.p, ctr.p, d_err);
+        const dim3 gu((unsigned)std::min<int64_t>((steps + 3) / 4, 4096));
+        if (A->bs == 1) {
+            hipLaunchKernelGGL(k_grid_factor<1>, dim3(wgs), dim3(64), 0, s, G, d_val, F.lt64.p, F.dt64.p,
+                               faces.p, ctr.p, d_err);
+            hipLaunchKernelGGL(k_grid_upper<1>, gu, dim3(256), 0, s, G, d_val, F.ut64.p);
+        } else {
+            hipLaunchKernelGGL(k_grid_factor<3>, dim3(wgs), dim3(64), 0, s, G, d_val, F.lt64.p, F.dt64.p,
+                               faces.p, ctr.p, d_err);
+            hipLaunchKernelGGL(k_grid_upper<3>, gu, dim3(256), 0, s, G, d_val, F.ut64.p);
+        }
     }
     KRY_HIP(hipGetLastError());
     // the face buffer and counter are freed on return
@@ -1590,21 +1706,6 @@ __global__ __launch_bounds__(GWG) void k_grid_bwd(GridTiles G, const TF *__restr
 // owns the workgroups [wg0, wg0 + wgs) of each kernel (multiples of
 // GRID_QUEUES, so a workgroup's queue, and XCD, keep their mapping)
 // ---------------------------------------------------------------------------
-// A pointer read from a descriptor, as an offset from `origin`, a kernel
-// argument that is null: derived from a kernel argument, its accesses are
-// global instructions; those of a pointer read from memory are flat ones,
-// which also wait on the LDS counter.
-template <typename T>
-__device__ __forceinline__ T *as_global(char *origin, T *p) {
-    return reinterpret_cast<T *>(origin + reinterpret_cast<uintptr_t>(p));
-}
-__device__ __forceinline__ void globalize(char *origin, GridTiles &G) {
-    G.order = as_global(origin, const_cast<int *>(G.order));
-    G.tidx = as_global(origin, const_cast<int *>(G.tidx));
-    G.qtiles = as_global(origin, const_cast<int *>(G.qtiles));
-    G.qjk = as_global(origin, const_cast<int *>(G.qjk));
-    G.qoff = as_global(origin, const_cast<int *>(G.qoff));
-}
 __device__ __forceinline__ int find_grid(const GridMulti *__restrict__ d, int ngrid, int blk) {
     int g = 0;
     while (g + 1 < ngrid && blk >= d[g + 1].wg0) g++;

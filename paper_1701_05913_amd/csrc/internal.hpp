@@ -426,7 +426,6 @@ int grid_multi_apply(hipStream_t s, int bs, const GridMulti *d_desc, int ngrid, 
 // face buffer and tile counter, and its first workgroup.
 struct FactorMulti {
     GridTiles G;
-    const int *rowptr;
     const double *val;
     double *lt, *ut, *dt, *faces;
     int *ctr;
