@@ -465,8 +465,7 @@ def main():
     K.KernelTimingEnable(False)
     abytes = algorithmic_bytes(nb, nnzb)
     kernels = {}
-    for kname in list(abytes) + ["cgs2", "dcgs2", "ilu_grid_untile",
-                                 "ilu_grid_factor", "spmv_csr"]:
+    for kname in list(abytes) + ["cgs2", "dcgs2", "ilu_grid_factor", "spmv_csr"]:
         cnt, ms = K.KernelTimingQuery(kname)
         if cnt == 0:
             continue
@@ -497,8 +496,7 @@ def main():
     torch.cuda.synchronize()
     K.KernelTimingEnable(False)
     vkern = {}
-    for kname in list(abytes) + ["spmv_csr", "ilu_grid_untile", "learned_stage", "ras_apply",
-                                 "amg_vcycle"]:
+    for kname in list(abytes) + ["spmv_csr", "learned_stage", "ras_apply", "amg_vcycle"]:
         cnt, ms = K.KernelTimingQuery(kname)
         if cnt == 0 or kname in head_kernels:
             continue

@@ -12,7 +12,7 @@
 // each subdomain on workgroups of its own, so a sweep's dependency chain has
 // mx + my + mz - 2 hyperplanes for an mx x my x mz box instead of
 // nx + ny + nz - 2.  R_s is a strided view of v (the box's cells at the
-// grid's strides); the untile launch writes each box's owned cells (R0_s^T)
+// grid's strides); the backward sweep writes each box's owned cells (R0_s^T)
 // straight into z.  A repeated setup for new values of the same matrix only
 // gathers the values and refactors.  Slabs too thin for the grid kernels
 // (one layer) use the level-scheduled sweeps in turn; boxes have no such
