@@ -104,91 +104,144 @@ static bool schedule_is_acyclic(int nb, const LevelSlices &L, F for_deps) {
 }
 
 // ---------------------------------------------------------------------------
-// host: blocks of consecutive rows
+// blocks of consecutive rows
 // ---------------------------------------------------------------------------
 constexpr int RB_ROWS = 256;             // rows of a block, one lane each
 constexpr int RB_SLICES = RB_ROWS / 64;  // its compute wavefronts
 constexpr int RB_IMPORT = 4;             // its importing wavefronts
 constexpr int RB_THREADS = RB_ROWS + 64 * RB_IMPORT;
 constexpr int RB_WIDE = 6;               // most dependencies of a row
-
-struct RowBlocks {
-    int nblk = 0, maxw = 0, maximp = 0;
-    std::vector<int> perm;   // nblk * RB_ROWS: row of each lane, -1 = none
-    std::vector<int> off;    // nblk * RB_SLICES + 1 slot offsets
-    std::vector<int> cell;   // off.back() * 64: LDS cell a dependency is read from
-    std::vector<int> woff;   // nblk + 1 offsets into words
-    std::vector<int> words;  // imported vector elements of each block
-};
+constexpr int RB_TABLE = 2048;           // hash table of a block's outside rows
+static_assert(RB_TABLE > RB_ROWS * RB_WIDE, "the table never fills");
 
 // Blocks in the order in which they are started: ascending rows for the
 // lower pattern, descending for the upper one, so that a block reads only
-// blocks started before it.  Rows of a block are put to lanes by level.  A
-// dependency inside the block is LDS cell `lane`, one outside of it cell
-// RB_ROWS + n, n counting the block's distinct outside rows by first use.
-static bool build_row_blocks(int nb, int bs, const std::vector<int> &lev, int nlev, bool upper,
-                             const std::vector<int> &rp, const std::vector<int> &ci,
-                             const std::vector<int> &dg, RowBlocks &R) {
-    const int nblk = (nb + RB_ROWS - 1) / RB_ROWS, ns = nblk * RB_SLICES;
-    auto block_of = [&](int i) { return (upper ? nb - 1 - i : i) / RB_ROWS; };
-    auto first = [&](int i) { return upper ? dg[i] + 1 : rp[i]; };
-    auto last = [&](int i) { return upper ? rp[i + 1] : dg[i]; };
-    R.nblk = nblk;
-    R.maxw = R.maximp = 0;
-    R.perm.assign((size_t)nblk * RB_ROWS, -1);
-    R.off.assign((size_t)ns + 1, 0);
-    R.woff.assign(nblk + 1, 0);
-    // rows by level, then each to the next lane of its block
-    std::vector<int> start(nlev + 1, 0), order(nb), fill(nblk, 0), lane_of(nb);
-    for (int i = 0; i < nb; i++) start[lev[i] + 1]++;
-    for (int l = 0; l < nlev; l++) start[l + 1] += start[l];
-    for (int i = 0; i < nb; i++) order[start[lev[i]]++] = i;
-    for (int i : order) {
-        const int blk = block_of(i);
-        lane_of[i] = fill[blk]++;
-        R.perm[(size_t)blk * RB_ROWS + lane_of[i]] = i;
+// blocks started before it.  Rows of a block are put to lanes by level, then
+// by number.  A dependency inside the block is LDS cell `lane`, one outside
+// of it cell RB_ROWS + n, n counting the block's distinct outside rows by
+// first use (lane by lane).
+//   One workgroup per block and direction (y: 0 lower, 1 upper), a thread a
+// row.  WRITE = false: the rows of the lanes, each slice's width into off and
+// each block's number of outside rows into woff.  WRITE = true, off and woff
+// being offsets now: the cells and the vector elements to import.
+//   Made here and not by the host, where it took longer than the
+// factorization at every assembly.  Red-black order, 3x3 blocks: an assembly
+// of 262 144 rows 13.4 -> 4.0 ms, of 1 572 864 rows 83 -> 17 ms (the level
+// schedule: 5.0 and 29 ms).
+template <bool WRITE>
+__global__ __launch_bounds__(RB_ROWS) void k_row_blocks(int nb, int bs, const int *__restrict__ rowptr,
+                                                        const int *__restrict__ col,
+                                                        const int *__restrict__ diag,
+                                                        const int *__restrict__ lev_l,
+                                                        const int *__restrict__ lev_u, RowBlocks lower,
+                                                        RowBlocks upper) {
+    __shared__ __attribute__((aligned(16))) int lev[RB_ROWS];
+    __shared__ int lane_of[RB_ROWS], uses[RB_ROWS], width[RB_SLICES], sums[RB_SLICES];
+    __shared__ int key[RB_TABLE], first[RB_TABLE];   // a row, its first use (later its number)
+    const bool up = blockIdx.y != 0;
+    const RowBlocks P = up ? upper : lower;
+    const int blk = blockIdx.x, t = threadIdx.x;
+    const int r1 = up ? nb - blk * RB_ROWS : min(nb, (blk + 1) * RB_ROWS);
+    const int r0 = up ? max(0, r1 - RB_ROWS) : blk * RB_ROWS;
+    // the thread's row: the block's t-th, in the second pass lane t's
+    const int i = WRITE ? P.perm[(int64_t)blk * RB_ROWS + t] : r0 + t < r1 ? r0 + t : -1;
+    const bool live = i >= 0;
+    int p0 = 0, n = 0, k[RB_WIDE];
+    if (live) {
+        p0 = up ? diag[i] + 1 : rowptr[i];
+        n = (up ? rowptr[i + 1] : diag[i]) - p0;
     }
-    for (int s = 0; s < ns; s++) {
-        int w = 0;
-        for (int q = 0; q < 64; q++) {
-            const int i = R.perm[(size_t)s * 64 + q];
-            if (i >= 0) w = std::max(w, last(i) - first(i));
+#pragma unroll
+    for (int d = 0; d < RB_WIDE; d++) k[d] = d < n ? col[p0 + d] : -1;
+    if (!WRITE) lev[t] = live ? (up ? lev_u : lev_l)[i] : INT_MAX;
+    if (t < RB_SLICES) width[t] = 0;
+    for (int e = t; e < RB_TABLE; e += RB_ROWS) {
+        key[e] = -1;
+        first[e] = INT_MAX;
+    }
+    __syncthreads();
+    int lane = t;   // rows that there are not come last
+    if (!WRITE && live) {
+        const int4 *l4 = reinterpret_cast<const int4 *>(lev);
+        const int own = lev[t];
+        lane = 0;
+#pragma unroll 4
+        for (int q = 0; q < RB_ROWS / 4; q++) {
+            const int4 l = l4[q];
+            lane += (l.x < own + (4 * q < t)) + (l.y < own + (4 * q + 1 < t)) + (l.z < own + (4 * q + 2 < t)) +
+                    (l.w < own + (4 * q + 3 < t));
         }
-        R.off[s + 1] = R.off[s] + w;
-        R.maxw = std::max(R.maxw, w);
     }
-    R.cell.assign((size_t)R.off[ns] * 64, -1);
-    struct Use { int block, cell; };          // the last block that read a row, its cell there
-    std::vector<Use> use(nb, Use{-1, 0});
-    R.words.resize((size_t)R.off[ns] * 64 * bs);
-    int *words = R.words.data();
-    for (int blk = 0; blk < nblk; blk++) {
-        const int r1 = upper ? nb - blk * RB_ROWS : std::min(nb, (blk + 1) * RB_ROWS);
-        const int r0 = upper ? std::max(0, r1 - RB_ROWS) : blk * RB_ROWS;
-        int n = 0;
-        for (int q = 0; q < fill[blk]; q++) {
-            const int i = R.perm[(size_t)blk * RB_ROWS + q], p0 = first(i);
-            int *cell = R.cell.data() + (size_t)R.off[blk * RB_SLICES + q / 64] * 64 + q % 64;
-            for (int p = p0; p < last(i); p++, cell += 64) {
-                const int k = ci[p];
-                if (upper ? k <= i : k >= i) return false;
-                if (k >= r0 && k < r1) {
-                    *cell = lane_of[k];
-                    continue;
-                }
-                Use &u = use[k];
-                if (u.block != blk) {
-                    u = Use{blk, RB_ROWS + n++};
-                    for (int r = 0; r < bs; r++) *words++ = k * bs + r;
-                }
-                *cell = u.cell;
-            }
+    if (live) lane_of[i - r0] = lane;
+    // the outside rows into the table, with the least use of each
+    int at[RB_WIDE];
+#pragma unroll
+    for (int d = 0; d < RB_WIDE; d++) {
+        at[d] = -1;
+        if (d >= n || (k[d] >= r0 && k[d] < r1)) continue;
+        int h = static_cast<int>(static_cast<uint32_t>(k[d]) * 2654435761u >> 21);
+        static_assert(RB_TABLE == 1 << (32 - 21), "the hash has the table's range");
+        for (int old; (old = atomicCAS(&key[h], -1, k[d])) != -1 && old != k[d];) h = (h + 1) & (RB_TABLE - 1);
+        atomicMin(&first[h], lane * RB_WIDE + d);
+        at[d] = h;
+    }
+    if (live) atomicMax(&width[lane >> 6], n);
+    __syncthreads();
+    // a row that an earlier use has counted has its number from there
+    unsigned firsts = 0;
+#pragma unroll
+    for (int d = 0; d < RB_WIDE; d++)
+        if (at[d] >= 0 && first[at[d]] == lane * RB_WIDE + d) firsts |= 1u << d;
+    uses[lane] = __popc(firsts);
+    __syncthreads();
+    // the uses of the lanes before each lane
+    const int own = uses[t], wave = t >> 6;
+    int sum = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(sum, o);
+        if ((t & 63) >= o) sum += v;
+    }
+    if ((t & 63) == 63) sums[wave] = sum;
+    __syncthreads();
+    for (int w = 0; w < wave; w++) sum += sums[w];
+    if (!WRITE) {
+        P.perm[(int64_t)blk * RB_ROWS + lane] = live ? i : -1;
+        if (t < RB_SLICES) P.off[blk * RB_SLICES + t] = width[t];
+        if (t == RB_ROWS - 1) P.woff[blk] = sum;
+        return;
+    }
+    uses[t] = sum - own;
+    __syncthreads();
+    int num = uses[lane];
+    int *words = P.words + P.woff[blk];
+#pragma unroll
+    for (int d = 0; d < RB_WIDE; d++)
+        if (firsts >> d & 1u) {
+            for (int r = 0; r < bs; r++) words[num * bs + r] = k[d] * bs + r;
+            first[at[d]] = num++;
         }
-        R.maximp = std::max(R.maximp, n);
-        R.woff[blk + 1] = (int)(words - R.words.data());
+    __syncthreads();
+    const int s = blk * RB_SLICES + (lane >> 6), o0 = P.off[s], w = P.off[s + 1] - o0;
+#pragma unroll
+    for (int d = 0; d < RB_WIDE; d++)
+        if (d < w)
+            P.cell[(int64_t)(o0 + d) * 64 + (lane & 63)] =
+                d >= n ? -1 : at[d] >= 0 ? RB_ROWS + first[at[d]] : lane_of[k[d] - r0];
+}
+
+// counts to offsets: h[0..n) exclusively summed (times unit), h[n] the total;
+// the largest count
+static int counts_to_offsets(int *h, int n, int unit) {
+    int sum = 0, most = 0;
+    for (int e = 0; e < n; e++) {
+        const int c = h[e];
+        h[e] = sum;
+        sum += c * unit;
+        most = std::max(most, c);
     }
-    R.words.resize(words - R.words.data());
-    return true;
+    h[n] = sum;
+    return most;
 }
 
 // ---------------------------------------------------------------------------
@@ -258,32 +311,42 @@ __global__ __launch_bounds__(256) void k_ilu_factor_level(
 // ---------------------------------------------------------------------------
 // packing into level-ordered slices
 // ---------------------------------------------------------------------------
-template <int BS, bool UPPER>
-__global__ void k_ilu_pack(int nslices, const int *__restrict__ perm, const int *__restrict__ off,
-                           const int *__restrict__ rowptr, const int *__restrict__ diag,
-                           const int *__restrict__ col, const double *__restrict__ lu,
-                           const double *__restrict__ uinv, int *__restrict__ scol,
-                           double *__restrict__ sval, double *__restrict__ dinv) {
+// one sweep's slices: rows and slot offsets, where columns and values go
+struct PackTarget {
+    int nslices;
+    const int *perm, *off;
+    int *col;
+    double *val;
+};
+
+// L (blockIdx.y = 0) and U with the inverses of its diagonal blocks
+template <int BS>
+__global__ void k_ilu_pack(PackTarget lower, PackTarget upper, const int *__restrict__ rowptr,
+                           const int *__restrict__ diag, const int *__restrict__ col,
+                           const double *__restrict__ lu, const double *__restrict__ uinv,
+                           double *__restrict__ dinv) {
     constexpr int B2 = BS * BS;
+    const bool up = blockIdx.y != 0;
+    const PackTarget P = up ? upper : lower;
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     const int s = g >> 6, lane = g & 63;
-    if (s >= nslices) return;
-    const int row = perm[g];
-    const int o0 = off[s], w = off[s + 1] - o0;
+    if (s >= P.nslices) return;
+    const int row = P.perm[g];
+    const int o0 = P.off[s], w = P.off[s + 1] - o0;
     int p0 = 0, len = 0;
     if (row >= 0) {
-        p0 = UPPER ? diag[row] + 1 : rowptr[row];
-        len = UPPER ? rowptr[row + 1] - p0 : diag[row] - p0;
+        p0 = up ? diag[row] + 1 : rowptr[row];
+        len = up ? rowptr[row + 1] - p0 : diag[row] - p0;
     }
     for (int t = 0; t < w; t++) {
         const int64_t slot = o0 + t;
         const bool have = t < len;
-        scol[slot * 64 + lane] = have ? col[p0 + t] : -1;
+        P.col[slot * 64 + lane] = have ? col[p0 + t] : -1;
 #pragma unroll
         for (int e = 0; e < B2; e++)
-            sval[(slot * B2 + e) * 64 + lane] = have ? lu[(int64_t)(p0 + t) * B2 + e] : 0.0;
+            P.val[(slot * B2 + e) * 64 + lane] = have ? lu[(int64_t)(p0 + t) * B2 + e] : 0.0;
     }
-    if (UPPER) {
+    if (up) {
 #pragma unroll
         for (int e = 0; e < B2; e++)
             dinv[((int64_t)s * B2 + e) * 64 + lane] = row >= 0 ? uinv[(int64_t)row * B2 + e] : 0.0;
@@ -302,8 +365,10 @@ __global__ void k_round_bf16(int64_t n, const double *__restrict__ x, uint16_t *
         y[i] = f32_to_bf16_rne(static_cast<float>(x[i]));
 }
 
+// y unwritten, the counters zero
 template <typename T>
-__global__ void k_fill_sentinel(int64_t n, T *y) {
+__global__ void k_sweep_start(int64_t n, T *y, int *ctr) {
+    if (blockIdx.x == 0 && threadIdx.x < 2 * GRID_QUEUES) ctr[threadIdx.x] = 0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         y[i] = sentinel_value<T>();
@@ -748,26 +813,48 @@ static int upload_layout(hipStream_t s, const LevelSlices &L, Sell &S, int bs) {
     return KRY_OK;
 }
 
-// perm, off, words and storage of one sweep over row blocks; the cells are
-// uploaded after the pack, which fills the same slots with column numbers
-static int upload_row_blocks(hipStream_t s, const RowBlocks &R, Sell &S, RowImports &I, int bs) {
-    S.bs = bs;
-    S.nslices = R.nblk * RB_SLICES;
-    S.maxw = R.maxw;
-    S.h_off = R.off;
-    S.nslots = R.off.back();
-    I.ncells = RB_ROWS + R.maximp + 1;
-    I.imports = R.maximp;
-    KRY_TRY(S.off.alloc(R.off.size()));
-    KRY_TRY(S.perm.alloc(R.perm.size()));
-    KRY_TRY(S.col.alloc(std::max<int64_t>(1, S.nslots) * 64));
-    KRY_TRY(S.val.alloc(std::max<int64_t>(1, S.nslots) * 64 * bs * bs));
-    KRY_TRY(I.off.alloc(R.woff.size()));
-    KRY_TRY(I.words.alloc(std::max<size_t>(1, R.words.size())));
-    KRY_HIP(hipMemcpyAsync(S.off.p, R.off.data(), sizeof(int) * R.off.size(), hipMemcpyHostToDevice, s));
-    KRY_HIP(hipMemcpyAsync(S.perm.p, R.perm.data(), sizeof(int) * R.perm.size(), hipMemcpyHostToDevice, s));
-    KRY_HIP(hipMemcpyAsync(I.off.p, R.woff.data(), sizeof(int) * R.woff.size(), hipMemcpyHostToDevice, s));
-    KRY_HIP(hipMemcpyAsync(I.words.p, R.words.data(), sizeof(int) * R.words.size(), hipMemcpyHostToDevice, s));
+// The row blocks of both sweeps up to their offsets, and the storage that
+// these measure out: F.plan holds [off, woff] of the lower and of the upper
+// blocks and the rows of their lanes, F.lists cells and words.  lev: the
+// rows' forward and backward levels; h: the offsets, for as long as the
+// stream may read them.
+static int plan_row_blocks(hipStream_t s, const MAT_ *A, const int *lev, std::vector<int> &h, IluFactor &F) {
+    const int nb = A->nb, bs = A->bs;
+    const int nblk = (nb + RB_ROWS - 1) / RB_ROWS, ns = nblk * RB_SLICES, nh = ns + nblk + 2;
+    KRY_TRY(F.plan.alloc(2 * ((size_t)nh + (size_t)nblk * RB_ROWS)));
+    RowBlocks *const blocks[2] = {&F.Lrows, &F.Urows};
+    for (int q = 0; q < 2; q++) {
+        blocks[q]->off = F.plan.p + (size_t)q * nh;
+        blocks[q]->woff = blocks[q]->off + ns + 1;
+        blocks[q]->perm = F.plan.p + 2 * (size_t)nh + (size_t)q * nblk * RB_ROWS;
+    }
+    hipLaunchKernelGGL(k_row_blocks<false>, dim3(nblk, 2), dim3(RB_ROWS), 0, s, nb, bs, A->rowptr.p,
+                       A->col.p, A->diag.p, lev, lev + nb, F.Lrows, F.Urows);
+    KRY_HIP(hipGetLastError());
+    h.resize(2 * (size_t)nh);
+    KRY_HIP(hipMemcpyAsync(h.data(), F.plan.p, sizeof(int) * h.size(), hipMemcpyDeviceToHost, s));
+    KRY_HIP(hipStreamSynchronize(s));
+    int64_t cells[2], nlists = 0;
+    Sell *const sell[2] = {&F.L, &F.U};
+    for (int q = 0; q < 2; q++) {
+        int *off = h.data() + (size_t)q * nh, *woff = off + ns + 1;
+        Sell &S = *sell[q];
+        S.bs = bs;
+        S.nslices = ns;
+        S.maxw = counts_to_offsets(off, ns, 1);
+        S.nslots = off[ns];
+        blocks[q]->imports = counts_to_offsets(woff, nblk, bs);
+        blocks[q]->ncells = RB_ROWS + blocks[q]->imports + 1;
+        cells[q] = std::max<int64_t>(1, S.nslots) * 64;
+        nlists += cells[q] + std::max(1, woff[nblk]);
+        KRY_TRY(S.val.alloc(cells[q] * bs * bs));
+    }
+    KRY_TRY(F.lists.alloc(nlists));
+    F.Lrows.cell = F.lists.p;
+    F.Urows.cell = F.Lrows.cell + cells[0];
+    F.Lrows.words = F.Urows.cell + cells[1];
+    F.Urows.words = F.Lrows.words + std::max(1, h[ns + 1 + nblk]);
+    KRY_HIP(hipMemcpyAsync(F.plan.p, h.data(), sizeof(int) * h.size(), hipMemcpyHostToDevice, s));
     return KRY_OK;
 }
 
@@ -818,34 +905,34 @@ int ilu_setup(hipStream_t s, const MAT_ *A, const double *d_val, IluFactor &F, i
     for (int i = 0; i < nb; i++) wide = std::max(wide, std::max(dg[i] - rp[i], rp[i + 1] - dg[i] - 1));
     F.rows = !use_grid && wide <= RB_WIDE;
     LevelSlices LF, LB;
-    RowBlocks RF, RB;
     build_slices(nb, levf, nlf, [&](int r) { return dg[r] - rp[r]; }, LF);
-    bool ok;
-    if (F.rows) {
-        ok = build_row_blocks(nb, bs, levf, nlf, false, rp, ci, dg, RF) &&
-             build_row_blocks(nb, bs, levb, nlb, true, rp, ci, dg, RB);
-    } else {
+    if (!use_grid && !F.rows) {
         build_slices(nb, levb, nlb, [&](int r) { return rp[r + 1] - dg[r] - 1; }, LB);
-        ok = schedule_is_acyclic(nb, LF, [&](int i, auto f) {
-                 for (int p = rp[i]; p < dg[i]; p++) f(ci[p]);
-             }) &&
-             schedule_is_acyclic(nb, LB, [&](int i, auto f) {
-                 for (int p = dg[i] + 1; p < rp[i + 1]; p++) f(ci[p]);
-             });
-    }
-    if (!ok) return set_error(KRY_ERR_ARG, "ILU: inconsistent level schedule");
-
-    // the levels' rows, which the factorization walks
-    DBuf<int> level_perm;
-    KRY_TRY(level_perm.alloc(LF.perm.size()));
-    KRY_HIP(hipMemcpyAsync(level_perm.p, LF.perm.data(), sizeof(int) * LF.perm.size(),
-                           hipMemcpyHostToDevice, s));
-    if (F.rows) {
-        KRY_TRY(upload_row_blocks(s, RF, F.L, F.Limp, bs));
-        KRY_TRY(upload_row_blocks(s, RB, F.U, F.Uimp, bs));
-    } else if (!use_grid) {
+        const bool ok = schedule_is_acyclic(nb, LF, [&](int i, auto f) {
+                            for (int p = rp[i]; p < dg[i]; p++) f(ci[p]);
+                        }) &&
+                        schedule_is_acyclic(nb, LB, [&](int i, auto f) {
+                            for (int p = dg[i] + 1; p < rp[i + 1]; p++) f(ci[p]);
+                        });
+        if (!ok) return set_error(KRY_ERR_ARG, "ILU: inconsistent level schedule");
         KRY_TRY(upload_layout(s, LF, F.L, bs));
         KRY_TRY(upload_layout(s, LB, F.U, bs));
+    }
+    // the levels' rows, which the factorization walks, and (row blocks) the
+    // rows' levels, in one copy
+    DBuf<int> levels;
+    std::vector<int> &up = LF.perm, offsets;
+    const size_t np = up.size();
+    const int *level_perm = F.L.perm.p;
+    if (use_grid || F.rows) {
+        if (F.rows) {
+            up.insert(up.end(), levf.begin(), levf.end());
+            up.insert(up.end(), levb.begin(), levb.end());
+        }
+        KRY_TRY(levels.alloc(up.size()));
+        level_perm = levels.p;
+        KRY_HIP(hipMemcpyAsync(levels.p, up.data(), sizeof(int) * up.size(), hipMemcpyHostToDevice, s));
+        if (F.rows) KRY_TRY(plan_row_blocks(s, A, levels.p + np, offsets, F));
     }
 
     // numeric factorization on a working copy of the values
@@ -858,10 +945,10 @@ int ilu_setup(hipStream_t s, const MAT_ *A, const double *d_val, IluFactor &F, i
         const int nl = (LF.lev_slice[l + 1] - LF.lev_slice[l]) * 64;
         dim3 g((nl + 255) / 256);
         if (bs == 1)
-            hipLaunchKernelGGL(k_ilu_factor_level<1>, g, dim3(256), 0, s, first, nl, level_perm.p,
+            hipLaunchKernelGGL(k_ilu_factor_level<1>, g, dim3(256), 0, s, first, nl, level_perm,
                                A->rowptr.p, A->col.p, A->diag.p, lu.p, uinv.p, d_err);
         else
-            hipLaunchKernelGGL(k_ilu_factor_level<3>, g, dim3(256), 0, s, first, nl, level_perm.p,
+            hipLaunchKernelGGL(k_ilu_factor_level<3>, g, dim3(256), 0, s, first, nl, level_perm,
                                A->rowptr.p, A->col.p, A->diag.p, lu.p, uinv.p, d_err);
     }
     KRY_HIP(hipGetLastError());
@@ -872,29 +959,18 @@ int ilu_setup(hipStream_t s, const MAT_ *A, const double *d_val, IluFactor &F, i
     // pack L and U (+ diagonal inverses) in level order
     KRY_TRY(F.dinv.alloc((size_t)F.U.nslices * 64 * b2));
     {
-        dim3 gl((F.L.nslices * 64 + 255) / 256), gu((F.U.nslices * 64 + 255) / 256);
-        if (bs == 1) {
-            hipLaunchKernelGGL((k_ilu_pack<1, false>), gl, dim3(256), 0, s, F.L.nslices, F.L.perm.p,
-                               F.L.off.p, A->rowptr.p, A->diag.p, A->col.p, lu.p, uinv.p,
-                               F.L.col.p, F.L.val.p, nullptr);
-            hipLaunchKernelGGL((k_ilu_pack<1, true>), gu, dim3(256), 0, s, F.U.nslices, F.U.perm.p,
-                               F.U.off.p, A->rowptr.p, A->diag.p, A->col.p, lu.p, uinv.p,
-                               F.U.col.p, F.U.val.p, F.dinv.p);
-        } else {
-            hipLaunchKernelGGL((k_ilu_pack<3, false>), gl, dim3(256), 0, s, F.L.nslices, F.L.perm.p,
-                               F.L.off.p, A->rowptr.p, A->diag.p, A->col.p, lu.p, uinv.p,
-                               F.L.col.p, F.L.val.p, nullptr);
-            hipLaunchKernelGGL((k_ilu_pack<3, true>), gu, dim3(256), 0, s, F.U.nslices, F.U.perm.p,
-                               F.U.off.p, A->rowptr.p, A->diag.p, A->col.p, lu.p, uinv.p,
-                               F.U.col.p, F.U.val.p, F.dinv.p);
-        }
+        const PackTarget lo = F.rows ? PackTarget{F.L.nslices, F.Lrows.perm, F.Lrows.off, F.Lrows.cell, F.L.val.p}
+                                     : PackTarget{F.L.nslices, F.L.perm.p, F.L.off.p, F.L.col.p, F.L.val.p};
+        const PackTarget hi = F.rows ? PackTarget{F.U.nslices, F.Urows.perm, F.Urows.off, F.Urows.cell, F.U.val.p}
+                                     : PackTarget{F.U.nslices, F.U.perm.p, F.U.off.p, F.U.col.p, F.U.val.p};
+        const dim3 g((std::max(F.L.nslices, F.U.nslices) * 64 + 255) / 256, 2);
+        hipLaunchKernelGGL(bs == 1 ? k_ilu_pack<1> : k_ilu_pack<3>, g, dim3(256), 0, s, lo, hi, A->rowptr.p,
+                           A->diag.p, A->col.p, lu.p, uinv.p, F.dinv.p);
+        if (F.rows)   // cells in the place of the packed columns
+            hipLaunchKernelGGL(k_row_blocks<true>, dim3(F.L.nslices / RB_SLICES, 2), dim3(RB_ROWS), 0, s, nb,
+                               bs, A->rowptr.p, A->col.p, A->diag.p, levels.p + np,
+                               levels.p + np + nb, F.Lrows, F.Urows);
         KRY_HIP(hipGetLastError());
-        if (F.rows) {
-            KRY_HIP(hipMemcpyAsync(F.L.col.p, RF.cell.data(), sizeof(int) * RF.cell.size(),
-                                   hipMemcpyHostToDevice, s));
-            KRY_HIP(hipMemcpyAsync(F.U.col.p, RB.cell.data(), sizeof(int) * RB.cell.size(),
-                                   hipMemcpyHostToDevice, s));
-        }
     }
     // reduced-precision copies: off-diagonal blocks to FP32 or BF16,
     // diagonal inverses to FP32
@@ -924,16 +1000,15 @@ int ilu_setup(hipStream_t s, const MAT_ *A, const double *d_val, IluFactor &F, i
     }
     // sweep state: forward output all-unwritten, counters zero
     const int64_t n = (int64_t)nb * bs;
+    KRY_TRY(F.ctr.alloc(2 * GRID_QUEUES));
     if (prec == KRY_PREC_F64) {
         KRY_TRY(F.y64.alloc(n));
-        hipLaunchKernelGGL(k_fill_sentinel<double>, dim3(1024), dim3(256), 0, s, n, F.y64.p);
+        hipLaunchKernelGGL(k_sweep_start<double>, dim3(1024), dim3(256), 0, s, n, F.y64.p, F.ctr.p);
     } else {
         KRY_TRY(F.y32.alloc(n));
-        hipLaunchKernelGGL(k_fill_sentinel<float>, dim3(1024), dim3(256), 0, s, n, F.y32.p);
+        hipLaunchKernelGGL(k_sweep_start<float>, dim3(1024), dim3(256), 0, s, n, F.y32.p, F.ctr.p);
     }
     KRY_HIP(hipGetLastError());
-    KRY_TRY(F.ctr.alloc(2 * GRID_QUEUES));
-    KRY_HIP(hipMemsetAsync(F.ctr.p, 0, 2 * GRID_QUEUES * sizeof(int), s));
     F.grid_waves = std::min(std::max(F.L.nslices, F.U.nslices), sweep_waves_cap());
     // the working copy is freed on return: wait for the kernels using it
     KRY_HIP(hipStreamSynchronize(s));
@@ -965,15 +1040,15 @@ static int sweep_rows(hipStream_t s, IluFactor &F, const TF *lval, const TF *uva
     {
         TimedScope t(F.timer_fwd ? F.timer_fwd : sweep_timer_name(true, BS, sizeof(TF), ADD), s);
         hipLaunchKernelGGL((k_ilu_fwd_rows<BS, W, TF, TC, TIN, TO>), grid, block,
-                           F.Limp.lds_bytes(BS, sizeof(TC)), s, F.Limp.ncells, F.L.perm.p,
-                           F.L.off.p, F.L.col.p, F.Limp.off.p, F.Limp.words.p, lval, b, y, xo,
+                           F.Lrows.lds_bytes(BS, sizeof(TC)), s, F.Lrows.ncells, F.Lrows.perm,
+                           F.Lrows.off, F.Lrows.cell, F.Lrows.woff, F.Lrows.words, lval, b, y, xo,
                            F.ctr.p, F.ctr.p + 1, err);
     }
     {
         TimedScope t(F.timer_bwd ? F.timer_bwd : sweep_timer_name(false, BS, sizeof(TF), ADD), s);
         hipLaunchKernelGGL((k_ilu_bwd_rows<BS, W, TF, TD, TC, TO, ADD, TAI, TAO>), grid, block,
-                           F.Uimp.lds_bytes(BS, sizeof(TO)), s, F.Uimp.ncells, F.U.perm.p,
-                           F.U.off.p, F.U.col.p, F.Uimp.off.p, F.Uimp.words.p, uval, dinv, y, xo,
+                           F.Urows.lds_bytes(BS, sizeof(TO)), s, F.Urows.ncells, F.Urows.perm,
+                           F.Urows.off, F.Urows.cell, F.Urows.woff, F.Urows.words, uval, dinv, y, xo,
                            add_in, add_out, F.ctr.p + 1, F.ctr.p, err);
     }
     KRY_HIP(hipGetLastError());

@@ -244,15 +244,17 @@ struct GridTiles {
     const int *qoff = nullptr;
 };
 
-// what a row block of a sweep (ilu.hip) reads of other blocks
-struct RowImports {
+// the row blocks of one sweep (ilu.hip): the row of each lane, slot offsets
+// of the slices, the LDS cell of each dependency, and the vector elements
+// that a block reads of other blocks, by first use, with their offsets
+struct RowBlocks {
     int ncells = 0;          // LDS cells of a block: its rows, its imports and a zero
     int imports = 0;
+    int *perm = nullptr, *off = nullptr, *cell = nullptr, *woff = nullptr, *words = nullptr;
     // the cells and the list of the elements to import
     size_t lds_bytes(int bs, size_t value) const {
         return (size_t)ncells * bs * value + (size_t)imports * bs * sizeof(int);
     }
-    DBuf<int> off, words;    // blocks + 1 offsets; vector elements by first use
 };
 
 struct IluFactor {
@@ -268,8 +270,9 @@ struct IluFactor {
     int nlev_f = 0, nlev_b = 0;
     Sell L;                 // forward order, strictly lower blocks
     Sell U;                 // backward order, strictly upper blocks
-    bool rows = false;      // L, U hold row blocks (col: LDS cells), not levels
-    RowImports Limp, Uimp;
+    bool rows = false;      // L, U hold the values of row blocks, not of levels
+    RowBlocks Lrows, Urows; // pointers into plan and lists
+    DBuf<int> plan, lists;
     DBuf<double> dinv;      // U_ii^-1 in U slice layout
     DBuf<float> dinvf;
     DBuf<double> y64;       // forward result (sentinel between sweeps)
