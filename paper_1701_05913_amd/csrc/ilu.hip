@@ -897,10 +897,15 @@ int ilu_setup(hipStream_t s, const MAT_ *A, const double *d_val, IluFactor &F, i
     F.nlev_b = nlb;
     // Rows with at most RB_WIDE dependencies (every stencil of the reservoir
     // systems, with holes and a few extra connections) are swept by row
-    // blocks (125 us a sweep at 60x52x41 with 12 % of the cells inactive,
-    // level by level 535 us).  Their lanes hold the entries in registers: six
-    // 3x3 blocks in FP64 take 188 of the 256 that a workgroup of eight
-    // wavefronts can have.  Wider rows are swept level by level.
+    // blocks.  An application, level by level -> row blocks (3x3 blocks, FP64):
+    // 60x52x41 with 12 % of the cells inactive 1090 -> 285 us.  Locality is not
+    // asked for, since orders that put most dependencies in other blocks gain
+    // too, if less: the same in random order 254 -> 100 us, 128x128x96 in
+    // random order 855 -> 773 us, red-black 647 -> 500 us, six distant
+    // dependencies a row (200 000 rows) 2395 -> 1050 us.  The lanes hold the
+    // entries in registers: six 3x3 blocks in FP64 take 188 of the 256 that a
+    // workgroup of eight wavefronts can have.  Wider rows are swept level by
+    // level, and a single one sends the whole matrix there.
     int wide = 0;
     for (int i = 0; i < nb; i++) wide = std::max(wide, std::max(dg[i] - rp[i], rp[i + 1] - dg[i] - 1));
     F.rows = !use_grid && wide <= RB_WIDE;
