@@ -141,10 +141,17 @@ def algorithmic_bytes(nb, nnzb):
         # BF16 factors: 22 B per block, FP32 diagonal inverses
         "ilu_fwd_bsr3_bf16": 22 * nl + ptr + 24 * nb + 12 * nb,
         "ilu_bwd_bsr3_bf16": 22 * nl + 36 * nb + ptr + 12 * nb + 24 * nb,
-        # CPR second stage: the backward sweep also reads the pressure
-        # correction (one value per cell) and writes the combined FP64 result
-        "ilu_bwd_bsr3_f64_inject": 76 * nl + 72 * nb + ptr + 48 * nb + 8 * nb + 24 * nb,
-        "ilu_bwd_bsr3_f32_inject": 40 * nl + 36 * nb + ptr + 12 * nb + 12 * nb + 4 * nb + 24 * nb,
+        # CPR's backward sweeps with their epilogue, which store the combined
+        # result alone: the full-system stage after the pressure stage also
+        # reads the pressure correction (one value per cell) and writes FP64;
+        # the corrections of the variants with several stages also read a
+        # whole vector and write the compute precision
+        "ilu_bwd_bsr3_f64_inject": 76 * nl + 72 * nb + ptr + 24 * nb + 8 * nb + 24 * nb,
+        "ilu_bwd_bsr3_f32_inject": 40 * nl + 36 * nb + ptr + 12 * nb + 4 * nb + 24 * nb,
+        "ilu_bwd_bsr3_bf16_inject": 22 * nl + 36 * nb + ptr + 12 * nb + 4 * nb + 24 * nb,
+        "ilu_bwd_bsr3_f64_add": 76 * nl + 72 * nb + ptr + 24 * nb + 24 * nb + 24 * nb,
+        "ilu_bwd_bsr3_f32_add": 40 * nl + 36 * nb + ptr + 12 * nb + 12 * nb + 12 * nb,
+        "ilu_bwd_bsr3_bf16_add": 22 * nl + 36 * nb + ptr + 12 * nb + 12 * nb + 12 * nb,
     }
 
 

@@ -1811,7 +1811,7 @@ static int grid_pair(hipStream_t s, IluFactor &F, const TF *lt, const TF *ut, co
                            yt, ff, fb, F.ctr.p, F.ctr.p + F.G.NQ, err);
     }
     {
-        TimedScope t(F.timer_bwd ? F.timer_bwd : sweep_timer_name(false, BS, sizeof(TF), 0), s);
+        TimedScope t(F.timer_bwd ? F.timer_bwd : sweep_timer_name(false, BS, sizeof(TF), ADD), s);
         hipLaunchKernelGGL((k_grid_bwd<BS, TF, TD, TC, TO, ADD, TAI, TAO>), dim3(wgs), dim3(GWG), 0,
                            s, F.G, ut, dt, yt, fb, ff, F.ctr.p + F.G.NQ, F.ctr.p, err, xo, add_in,
                            add_out);
