@@ -1059,7 +1059,13 @@ __device__ __forceinline__ void block_sub(TC (&acc)[BS], const TC (&v)[NV], int 
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // 16 bytes that see other workgroups' published values (device scope), the
-// load waited for in the same statement
+// load waited for in the same statement.
+//   The values in them validate themselves one by one, so each has to arrive
+// whole: no 8-byte half of a piece may be seen half written.  This is taken
+// from the hardware: a lane's piece is aligned to 16 bytes (records are padded
+// to whole pieces), so it lies within one cache line and is stored and read by
+// one request each.  The programming model promises it for atomic accesses of
+// up to 8 bytes alone.
 __device__ __forceinline__ u32x4 load_published(const void *a) {
     u32x4 r;
     asm volatile("global_load_dwordx4 %0, %1, off sc1\n\t"
@@ -1069,8 +1075,15 @@ __device__ __forceinline__ u32x4 load_published(const void *a) {
                  : "memory");
     return r;
 }
+// A vector instruction may overwrite the data registers of a 16-byte store no
+// sooner than two wait states after it; the compiler keeps that distance for
+// its own stores but does not see this one, hence the wait states here.
 __device__ __forceinline__ void store_published(void *a, u32x4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(a), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\t"
+                 "s_nop 1"
+                 :
+                 : "v"(a), "v"(v)
+                 : "memory");
 }
 
 // What the publisher's lane u holds of a step's face record: 16 bytes of it
