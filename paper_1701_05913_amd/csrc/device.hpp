@@ -210,11 +210,8 @@ __device__ __forceinline__ void wait_cells(const T *base, const int64_t (&cells)
 }
 
 // Synchronisation between the wavefronts of one workgroup through LDS.
-// The fences are restricted to the LDS address space, so they wait only for
-// LDS operations (lgkmcnt) and never for outstanding global stores.
-__device__ __forceinline__ void lds_release() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-}
+// The fence is restricted to the LDS address space, so it waits only for LDS
+// operations (lgkmcnt) and never for outstanding global stores.
 __device__ __forceinline__ void lds_acquire() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
@@ -224,9 +221,9 @@ __device__ __forceinline__ int lds_get(int *p) {
 __device__ __forceinline__ void lds_put(int *p, int v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-// Every wait below is on a wavefront of the same workgroup that itself only
-// waits on earlier steps, so it ends; the bound turns a broken protocol
-// into an error flag instead of a hang.
+// The wait is on a wavefront of the same workgroup that itself only waits on
+// earlier steps, so it ends; the bound turns a broken protocol into an error
+// flag instead of a hang.
 __device__ __forceinline__ void lds_wait_eq(int *p, int v, int *err) {
     for (uint32_t it = 0; lds_get(p) != v; ++it) {
         if (it > 4 * SPIN_LIMIT) {
@@ -237,41 +234,6 @@ __device__ __forceinline__ void lds_wait_eq(int *p, int v, int *err) {
     }
     lds_acquire();
 }
-__device__ __forceinline__ void lds_wait_ge(int *p, int v, int *err) {
-    for (uint32_t it = 0; lds_get(p) < v; ++it) {
-        if (it > 4 * SPIN_LIMIT) {
-            __hip_atomic_store(err, ERR_STALL_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-    }
-    lds_acquire();
-}
-
-// wait for *p == v and, when w >= 0, *q == w: both flags in one poll
-__device__ __forceinline__ void lds_wait_pair(int *p, int v, int *q, int w, int *err) {
-    for (uint32_t it = 0;; ++it) {
-        const int a = lds_get(p);
-        const int b = w >= 0 ? lds_get(q) : w;
-        if (a == v && b == w) break;
-        if (it > 4 * SPIN_LIMIT) {
-            __hip_atomic_store(err, ERR_STALL_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-    }
-    lds_acquire();
-}
-// lds_wait_pair, skipped when stamps read ahead of time (pa from p, pb
-// from q, during the previous step) already show the step ready; the
-// acquire still orders the data reads that follow after the stamps
-__device__ __forceinline__ void lds_wait_pair_pre(int pa, int pb, int *p, int v, int *q, int w,
-                                                  int *err) {
-    const int a = __builtin_amdgcn_readfirstlane(pa), b = __builtin_amdgcn_readfirstlane(pb);
-    if (a == v && (w < 0 || b == w)) lds_acquire();
-    else lds_wait_pair(p, v, q, w, err);
-}
-
 // Inverse of a BS x BS block by Gaussian elimination with partial
 // pivoting (first maximal pivot on ties); false (R undefined) for a
 // non-finite or tiny pivot: |pivot| < 1e-300 for BS = 1, < 1e-14 ||A||_inf
