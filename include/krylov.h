@@ -50,8 +50,8 @@ extern "C" {
 #define KRY_ERR_BREAKDOWN   -5   /* Krylov breakdown / non-finite values   */
 #define KRY_ERR_HIP         -6   /* HIP runtime error                      */
 #define KRY_ERR_UNSUPPORTED -7   /* option not implemented                 */
-#define KRY_ERR_STALL       -8   /* a level-scheduled sweep waited longer
-                                    than its bound (inconsistent schedule) */
+#define KRY_ERR_STALL       -8   /* a triangular sweep waited longer than
+                                    its bound (inconsistent schedule)      */
 
 /* ---- enumerations -------------------------------------------------------- */
 enum { KRY_HOST = 0, KRY_DEVICE = 1 };
@@ -263,10 +263,11 @@ int SolverSetRAS(SOLVER *s, int nsub, int overlap);
  * sides >= 3 in x and y and >= 2 in z unless px = py = 1 (KRY_ERR_UNSUPPORTED
  * at SolverAssemble).  SolverSetRAS(s, n, o) = SolverSetRASBoxes(s, 1, 1, n, o). */
 int SolverSetRASBoxes(SOLVER *s, int px, int py, int pz, int overlap);
-/* SolverSetSweepLayout: KRY_SWEEP_AUTO (default), KRY_SWEEP_LEVELS (generic
- * level-scheduled sweeps), or KRY_SWEEP_GRID (grid-tiled sweeps; assembly
- * fails with KRY_ERR_ARG if the matrix is not a 7-point grid stencil).
- * Both layouts apply the same factor. */
+/* SolverSetSweepLayout: KRY_SWEEP_AUTO (default), KRY_SWEEP_LEVELS (the sweeps
+ * of general patterns: by blocks of consecutive rows while no row has more than
+ * six dependencies in a sweep, else level by level), or KRY_SWEEP_GRID
+ * (grid-tiled sweeps; assembly fails with KRY_ERR_ARG if the matrix is not a
+ * 7-point grid stencil).  All of them apply the same factor. */
 int SolverSetSweepLayout(SOLVER *s, int layout);
 /* SolverSetOrthog: Gram-Schmidt of the Arnoldi step (Algorithm 1, whose
  * modified Gram-Schmidt both kinds equal in exact arithmetic).

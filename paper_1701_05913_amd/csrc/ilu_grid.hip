@@ -9,7 +9,8 @@
 // processes i = t - jj - kk, so
 //   * (i-1) is the lane's own result of the previous step (a register),
 //   * (j-1) and (k-1) are the results of lanes jj-1 and kk-1 of the
-//     previous step (cross-lane moves),
+//     previous step (a ring in LDS; the factorization moves them across
+//     lanes),
 //   * only lanes on the tile's low faces need values of neighbouring
 //     tiles, which those tiles publish into small per-step face buffers.
 // A dependency chain therefore crosses memory only when it crosses a tile
@@ -30,9 +31,12 @@
 //            (lane kk), then the TJ k-face cells (lane jj), each part padded
 //            to whole 16-byte pieces.
 // Missing neighbours, idle lanes and steps outside the line hold zero
-// factors and zero right-hand sides.  Such lanes only ever see zeros, so
-// they compute exact zeros, and a real cell multiplies a zero block only
-// by an exact zero: the sweeps need no per-lane predication.
+// factors and zero right-hand sides.  Lanes and steps of a tile that have no
+// cell so compute exact zeros, and a real cell multiplies a zero block only by
+// one of these or by a halo of zeros: the sweeps need no per-lane predication.
+// (A value that is not finite makes NaNs of them, but only where the cells
+// beside them depend on that value too.)  Lanes past TJ TK read parts of the
+// result ring that nothing wrote, and no lane of the tile reads theirs.
 #include <algorithm>
 #include <type_traits>
 

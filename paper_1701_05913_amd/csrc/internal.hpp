@@ -222,7 +222,7 @@ int ensure_sell_f32(hipStream_t s, Sell &S);
 int ensure_col0_f32(hipStream_t s, MAT_ *A);
 
 // ---------------------------------------------------------------------------
-// ILU(0) / block ILU(0) factor in level-scheduled layout (ilu.hip)
+// ILU(0) / block ILU(0) factor and its sweeps (ilu.hip, ilu_grid.hip)
 // ---------------------------------------------------------------------------
 // 7-point grid tiling: a tile is TJ x TK x-lines (one lane each) of a
 // wavefront; S = nx + TJ + TK - 2 hyperplane steps per tile; order[t] =
@@ -459,7 +459,7 @@ struct RasSub {
     DBuf<int> pos;                        // A's value blocks of the subdomain matrix
     DBuf<double> faces;                   // grid factorization work buffers
     DBuf<int> fctr;
-    DBuf<double> x;                       // local solution (level-scheduled slabs)
+    DBuf<double> x;                       // local solution (slabs that are no grid)
 };
 struct RasPC {
     int px = 1, py = 1, pz = 1, overlap = 1, bs = 1, layout = 0;

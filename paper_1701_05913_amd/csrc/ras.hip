@@ -15,7 +15,7 @@
 // grid's strides); the backward sweep writes each box's owned cells (R0_s^T)
 // straight into z.  A repeated setup for new values of the same matrix only
 // gathers the values and refactors.  Slabs too thin for the grid kernels
-// (one layer) use the level-scheduled sweeps in turn; boxes have no such
+// (one layer) use the general patterns' sweeps in turn; boxes have no such
 // fallback.
 #include <algorithm>
 

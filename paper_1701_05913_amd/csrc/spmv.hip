@@ -134,7 +134,7 @@ int ensure_col0_f32(hipStream_t s, MAT_ *A) {
 // ---------------------------------------------------------------------------
 // The matrix streams through once, so a product is bound by HBM as long as
 // enough of it is in flight.  A slot's x waits for its column number, and a
-// loop over slots waits once per slot: hence SPMV_SLOTS slots at a time, all
+// loop over slots waits once per slot: hence spmv_slots slots at a time, all
 // their columns and values loaded before the first use (padding holds
 // column -1 and value 0 and gathers x[0], dropped).  The values are loaded
 // non-temporally, which leaves the L2 to x, whose neighbour rows are read
