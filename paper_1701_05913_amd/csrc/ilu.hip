@@ -14,19 +14,19 @@
 //    partial pivoting) and reused by every later row and by the solve.
 //  * Layout: rows are permuted by level and each level is padded to whole
 //    64-row slices, so a wavefront always holds rows of one level, which
-//    are mutually independent.  Values sit in entry-major planes (sliced
+//    are mutually independent; for the row blocks rows are permuted by level
+//    inside blocks of 256 only.  Values sit in entry-major planes (sliced
 //    ELLPACK), so the factor streams from HBM in full cache lines.
 //  * Sweeps: one launch per sweep.  Rows with few dependencies are swept by
 //    blocks of consecutive rows (see there).  For wider ones wavefronts take
 //    slices in level order from an atomic counter; a row waits only for the
-//    rows it reads.  Each
-//    output value is published with a relaxed agent-scope store into a
-//    slot pre-filled with a reserved NaN payload, and consumers poll the
-//    slot itself -- no flags, no fences, no grid barriers.  A slice's
-//    dependencies are always in earlier slices, which were handed to
-//    wavefronts that are already running, so the sweep cannot deadlock; a
-//    bounded spin turns any broken schedule into an error instead of a
-//    hang.
+//    rows it reads.  Each output value is published with a relaxed
+//    agent-scope store into a slot pre-filled with a reserved NaN payload,
+//    and consumers poll the slot itself -- no flags, no fences, no grid
+//    barriers.  What a slice (a block) reads lies in earlier slices (blocks),
+//    which were handed to wavefronts that are already running, so the sweep
+//    cannot deadlock; a bounded spin turns any broken schedule into an error
+//    instead of a hang.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
